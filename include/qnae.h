@@ -131,6 +131,11 @@ int qnae_build_cost_diagonal_pred(qnae_ctx *ctx, const int32_t *clauses, int32_t
  *   out          host result
  *   stream       hipStream_t the work is enqueued on
  *
+ * From n = 20 on every call checks whether the diagonal is flip-symmetric,
+ * C(x) = C(NOT x) for every x, as every NAE diagonal is (Section 2.2). Then
+ * the amplitudes are too and only half of them are computed (see
+ * qnae_qaoa_run_z2); a kept state is whole all the same.
+ *
  * Synchronous: returns after *out is filled. Cost values above m give
  * undefined results. Errors: QNAE_EINVAL, QNAE_ENOMEM, QNAE_EHIP. */
 int qnae_qaoa_run(qnae_ctx *ctx, const void *cost_dev, int32_t cost_dtype,
@@ -174,7 +179,8 @@ int qnae_qaoa_run_noalloc(qnae_ctx *ctx, const void *cost_dev, int32_t cost_dtyp
  * applies the inverse layers to lam and psi together and restarts psi from
  * each checkpoint, so rounding in the uncomputed psi spans at most one segment.
  * Device memory: ceil(p / checkpoint_every) + 1 states of 2^n complex64 (n >
- * 13), held by the context.
+ * 13; half of each for a flip-symmetric diagonal with n > 24), held by the
+ * context.
  *
  *   dgammas, dbetas  host, p doubles each (may be NULL when p = 0)
  *   out              host readout of the forward state (as qnae_qaoa_run)

@@ -296,7 +296,13 @@ __device__ __forceinline__ void q_mix_up(float2* lds, float2 (&l)[16], float2 (&
 // WEIGH (first sweep of the reverse pass, natural order): lam is not read but
 // formed as W psi from the loaded psi and cost, which saves a pass over both
 // states.
-template <typename CT, int KIND, bool WEIGH, bool STREAM, bool USE1>
+//
+// VIRT (half state, the group mixes bit n-1, tile bit 12): elements with that
+// bit set are the mirrored ones, stored at mir - y for the index y of their
+// other bits. Layout Q0 holds the bit in the wave index, so a wave is
+// mirrored as a whole (pairs along tile bit 0 one lower, in reverse order);
+// layout Q3 holds it in slot bit 2.
+template <typename CT, int KIND, bool WEIGH, bool STREAM, bool USE1, bool VIRT>
 __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_kernel(
     const AdjointArgs a) {
     constexpr int TB = kAdjointTileBits;
@@ -311,7 +317,9 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     __shared__ float2 lut_s[PHASE && LUT_LDS ? 256 : 1];
     __shared__ double red[3][NWV];
 
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave =
+        VIRT ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : threadIdx.x >> 6;
     const uint32_t t = blockIdx.x;
     const uint32_t ntiles = 1u << a.nw;
     uint64_t bitval[TB];
@@ -320,7 +328,7 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     auto scat = [&](uint32_t e) -> uint64_t {
         uint64_t x = 0;
 #pragma unroll
-        for (int i = 0; i < TB; ++i)
+        for (int i = 0; i < (VIRT ? TB - 1 : TB); ++i)
             if ((e >> i) & 1u) x |= bitval[i];
         return x;
     };
@@ -342,18 +350,34 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     // cost[x ^ a.cost_flip]. The tile's thread part t and slot part s of an
     // element have disjoint bits, so (t | s) ^ (2^n - 1) = (t ^ (2^n - 1)) - s.
     const uint64_t all = (1ull << a.n) - 1ull;
+    constexpr uint32_t kTop = 1u << (TB - 1);
+    const bool top = VIRT && (wave >> 2) != 0u;
+    // a thread's place in layout Q0 and the sign its slot offsets count with
+    const uint64_t q0fwd = base + scat(qt<0>(lane, wave));
+    const uint64_t q0at = top ? a.mir - 1ull - q0fwd : q0fwd;
+    auto d0 = [&](uint32_t se) -> int64_t {
+        const int64_t d = (int64_t)scat(se);
+        return top ? -d : d;
+    };
+    // element (thread part at o, slot part se) of layout Q3
+    auto at3 = [&](uint64_t o, uint32_t se) -> uint64_t {
+        return VIRT && (se & kTop) ? a.mir - o - scat(se) : o + scat(se);
+    };
     uint32_t cvp[NC];
     if (PHASE) {
         const uint64_t ct = base + scat(qt<3>(lane, wave));
-        const bool cf = a.cost_flip != 0ull;
+        const bool cf = !VIRT && a.cost_flip != 0ull;
         const CT* const c3 = (const CT*)a.cost + (cf ? ct ^ all : ct);
+        const CT* const cv = VIRT ? (const CT*)a.cost + (a.mir - ct) : c3;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             uint32_t wv = 0u;
 #pragma unroll
             for (int q = 0; q < PK; ++q) {
-                const uint64_t d = scat(qs<3>(PK * i + q));
-                wv |= (uint32_t)(cf ? c3[-(int64_t)d] : c3[d]) << (8 * sizeof(CT) * q);
+                const uint32_t se = qs<3>(PK * i + q);
+                const uint64_t d = scat(se);
+                const CT c = VIRT ? ((se & kTop) ? cv[-(int64_t)d] : c3[d]) : (cf ? c3[-(int64_t)d] : c3[d]);
+                wv |= (uint32_t)c << (8 * sizeof(CT) * q);
             }
             cvp[i] = wv;
         }
@@ -374,31 +398,33 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     // Layout Q0 pairs tile bit 0 (global bit 0) in one float4: flipped, the
     // pair (x, x + 1) sits at (x ^ (2^n - 1) ^ 1, its successor) in reverse
     // order.
-    const bool pf = a.psi_flip != 0;
+    const bool pf = !VIRT && a.psi_flip != 0;
     float2 l[16], p[16];
     {
-        const uint64_t o0 = base + scat(qt<0>(lane, wave));
+        const uint64_t o0 = q0at;
         const float2* const pb = a.psi + (pf ? o0 ^ all ^ 1ull : o0);
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
-            const uint64_t d = scat(qs<0>(2 * jj));
+            const int64_t d = d0(qs<0>(2 * jj));
             const float4 qp = ld4<STREAM>(pf ? pb - d : pb + d);
-            p[2 * jj] = pf ? make_float2(qp.z, qp.w) : make_float2(qp.x, qp.y);
-            p[2 * jj + 1] = pf ? make_float2(qp.x, qp.y) : make_float2(qp.z, qp.w);
+            const bool pr = VIRT ? top : pf;
+            p[2 * jj] = pr ? make_float2(qp.z, qp.w) : make_float2(qp.x, qp.y);
+            p[2 * jj + 1] = pr ? make_float2(qp.x, qp.y) : make_float2(qp.z, qp.w);
             if (WEIGH) {
                 // lam = W psi: the pair's two costs are adjacent (tile bit 0)
                 using PT = typename std::conditional<sizeof(CT) == 1, uint16_t, uint32_t>::type;
                 constexpr uint32_t CB = 8 * sizeof(CT);
                 const PT cc = *(const PT*)((const CT*)a.cost + o0 + d);
-                const uint32_t c0 = (uint32_t)cc & ((1u << CB) - 1u), c1 = (uint32_t)cc >> CB;
+                const uint32_t ca = (uint32_t)cc & ((1u << CB) - 1u), cb = (uint32_t)cc >> CB;
+                const uint32_t c0 = top ? cb : ca, c1 = top ? ca : cb;
                 const float w0 = fmaf(a.w_energy, (float)c0, c0 == 0u ? a.w_psucc : 0.f);
                 const float w1 = fmaf(a.w_energy, (float)c1, c1 == 0u ? a.w_psucc : 0.f);
                 l[2 * jj] = make_float2(w0 * p[2 * jj].x, w0 * p[2 * jj].y);
                 l[2 * jj + 1] = make_float2(w1 * p[2 * jj + 1].x, w1 * p[2 * jj + 1].y);
             } else {
                 const float4 ql = ld4<STREAM>(a.lam + o0 + d);
-                l[2 * jj] = make_float2(ql.x, ql.y);
-                l[2 * jj + 1] = make_float2(ql.z, ql.w);
+                l[2 * jj] = top ? make_float2(ql.z, ql.w) : make_float2(ql.x, ql.y);
+                l[2 * jj + 1] = top ? make_float2(ql.x, ql.y) : make_float2(ql.z, ql.w);
             }
         }
     }
@@ -432,51 +458,49 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
         // compiler sinks them below the stores and holds the states' values
         // from before the last butterflies across them (40 spilled registers).
         asm volatile("" : "+v"(acc_post));
-        const uint64_t o0 = base + scat(qt<0>(lane, wave));
+        const uint64_t o0 = q0at;
         float2* const pb = a.psi + (pf ? o0 ^ all ^ 1ull : o0);
+        // pair jj of a state, in storage order
+        auto pair = [&](const float2(&x)[16], int jj, bool rev) {
+            const float2 lo = rev ? x[2 * jj + 1] : x[2 * jj], hi = rev ? x[2 * jj] : x[2 * jj + 1];
+            return make_float4(lo.x, lo.y, hi.x, hi.y);
+        };
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            const uint64_t d = scat(qs<0>(2 * jj));
-            st4<STREAM>(a.lam + o0 + d, make_float4(l[2 * jj].x, l[2 * jj].y, l[2 * jj + 1].x, l[2 * jj + 1].y));
-        }
+        for (int jj = 0; jj < 8; ++jj) st4<STREAM>(a.lam + o0 + d0(qs<0>(2 * jj)), pair(l, jj, top));
         if (a.store_psi) {
             if (pf) {
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj)
-                    st4<STREAM>(pb - scat(qs<0>(2 * jj)),
-                                make_float4(p[2 * jj + 1].x, p[2 * jj + 1].y, p[2 * jj].x, p[2 * jj].y));
+                for (int jj = 0; jj < 8; ++jj) st4<STREAM>(pb - scat(qs<0>(2 * jj)), pair(p, jj, true));
             } else {
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj)
-                    st4<STREAM>(pb + scat(qs<0>(2 * jj)),
-                                make_float4(p[2 * jj].x, p[2 * jj].y, p[2 * jj + 1].x, p[2 * jj + 1].y));
+                for (int jj = 0; jj < 8; ++jj) st4<STREAM>(pb + d0(qs<0>(2 * jj)), pair(p, jj, top));
             }
         }
     } else {
         const uint64_t o3 = base + scat(qt<3>(lane, wave));
 #pragma unroll
-        for (int j = 0; j < 16; ++j) st2<STREAM>(a.lam + o3 + scat(qs<3>(j)), l[j]);
+        for (int j = 0; j < 16; ++j) st2<STREAM>(a.lam + at3(o3, qs<3>(j)), l[j]);
         if (a.store_psi) {
-            float2* const pb = a.psi + (pf ? o3 ^ all : o3);
+            float2* const pb = a.psi + (pf ? o3 ^ all : 0ull);
             if (pf) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j) st2<STREAM>(pb - scat(qs<3>(j)), p[j]);
             } else {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) st2<STREAM>(pb + scat(qs<3>(j)), p[j]);
+                for (int j = 0; j < 16; ++j) st2<STREAM>(a.psi + at3(o3, qs<3>(j)), p[j]);
             }
         }
     }
-    double d0 = acc_pre, d1 = acc_g, d2 = acc_post;
+    double r0 = acc_pre, r1 = acc_g, r2 = acc_post;
     for (int off = 32; off > 0; off >>= 1) {
-        d0 += __shfl_xor(d0, off);
-        d1 += __shfl_xor(d1, off);
-        d2 += __shfl_xor(d2, off);
+        r0 += __shfl_xor(r0, off);
+        r1 += __shfl_xor(r1, off);
+        r2 += __shfl_xor(r2, off);
     }
     if (lane == 0) {
-        red[0][wave] = d0;
-        red[1][wave] = d1;
-        red[2][wave] = d2;
+        red[0][wave] = r0;
+        red[1][wave] = r1;
+        red[2][wave] = r2;
     }
     __syncthreads();
     if (threadIdx.x < 3) {
@@ -624,20 +648,24 @@ __global__ __launch_bounds__(kResidentGradThreads) void resident_grad_batch_kern
     resident_grad_body<CT>(a);
 }
 
-template <typename CT, bool NT, bool USE1>
+template <typename CT, bool NT, bool USE1, bool VIRT>
 hipError_t launch_adjoint_q(int kind, const AdjointArgs& a, hipStream_t s, bool weigh) {
     const dim3 grid(1u << a.nw), block(kQThreads);
     if (weigh) {
         if (kind != AK_MIDDLE || a.psi_flip || a.cost_flip) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((adjoint_kernel<CT, AK_MIDDLE, true, NT, USE1>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((adjoint_kernel<CT, AK_MIDDLE, true, NT, USE1, VIRT>), grid, block, 0, s, a);
         return hipGetLastError();
     }
     switch (kind) {
-        case AK_MIDDLE: hipLaunchKernelGGL((adjoint_kernel<CT, AK_MIDDLE, false, NT, USE1>), grid, block, 0, s, a); break;
-        case AK_BOUNDARY:
-            hipLaunchKernelGGL((adjoint_kernel<CT, AK_BOUNDARY, false, NT, USE1>), grid, block, 0, s, a);
+        case AK_MIDDLE:
+            hipLaunchKernelGGL((adjoint_kernel<CT, AK_MIDDLE, false, NT, USE1, VIRT>), grid, block, 0, s, a);
             break;
-        case AK_END: hipLaunchKernelGGL((adjoint_kernel<CT, AK_END, false, NT, USE1>), grid, block, 0, s, a); break;
+        case AK_BOUNDARY:
+            hipLaunchKernelGGL((adjoint_kernel<CT, AK_BOUNDARY, false, NT, USE1, VIRT>), grid, block, 0, s, a);
+            break;
+        case AK_END:
+            hipLaunchKernelGGL((adjoint_kernel<CT, AK_END, false, NT, USE1, VIRT>), grid, block, 0, s, a);
+            break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -648,16 +676,20 @@ hipError_t launch_adjoint_q(int kind, const AdjointArgs& a, hipStream_t s, bool 
 template <typename CT, bool NT>
 hipError_t launch_adjoint_ct(int kind, const AdjointArgs& a, hipStream_t s, bool weigh) {
     const uint32_t masks = a.pre_mask | (kind == AK_BOUNDARY ? a.post_mask : 0u);
-    return (masks & 0xfu) != 0u ? launch_adjoint_q<CT, NT, true>(kind, a, s, weigh)
-                                : launch_adjoint_q<CT, NT, false>(kind, a, s, weigh);
+    const bool use1 = (masks & 0xfu) != 0u;
+    if (a.virt)
+        return use1 ? launch_adjoint_q<CT, NT, true, true>(kind, a, s, weigh)
+                    : launch_adjoint_q<CT, NT, false, true>(kind, a, s, weigh);
+    return use1 ? launch_adjoint_q<CT, NT, true, false>(kind, a, s, weigh)
+                : launch_adjoint_q<CT, NT, false, false>(kind, a, s, weigh);
 }
 
 }  // namespace
 
-// Nontemporal state accesses once the two states (16 B per amplitude) exceed
-// the 256 MiB last-level cache.
+// Nontemporal state accesses once the two states (16 B per stored amplitude)
+// exceed the 256 MiB last-level cache.
 hipError_t launch_adjoint(int dtype, int kind, const AdjointArgs& a, hipStream_t s, bool weigh) {
-    const bool nt = a.n >= 24;
+    const bool nt = a.nw + kAdjointTileBits >= 24;
     if (dtype == 1)
         return nt ? launch_adjoint_ct<uint8_t, true>(kind, a, s, weigh)
                   : launch_adjoint_ct<uint8_t, false>(kind, a, s, weigh);

@@ -159,7 +159,7 @@ struct BatchPlan {
     };
     struct Launch {
         int kind, dtype, step, tb;
-        bool half;
+        bool virt;
         std::vector<int> members;
         size_t args_at, first_at;
         uint32_t blocks;
@@ -226,13 +226,14 @@ int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, BatchPl
     P.lut_at = B.take(sizeof(float2) * P.lut_elems);
     P.form_at = B.take(sizeof(MixForm) * P.form_elems);
     P.fixed_at = B.take(0);
-    // Sweep launches: step s, bucket (kind, cost type, half, tile bits).
+    // Sweep launches: step s, bucket (kind, cost type, virtual bit, tile bits).
     for (int st = 0; st < steps; ++st) {
         std::map<std::tuple<int, int, bool, int>, size_t> bucket;
         for (int i = 0; i < count; ++i) {
             const BatchPlan::Job& J = P.jobs[i];
             if (J.resident || st >= (int)J.plan.ops.size()) continue;
-            const auto key = std::make_tuple(J.plan.ops[st].kind, inst[i].cost_dtype, J.plan.half, P.ident[i].tb);
+            const Op& op = J.plan.ops[st];
+            const auto key = std::make_tuple(op.kind, inst[i].cost_dtype, op_virtual(J.plan, op), P.ident[i].tb);
             auto it = bucket.find(key);
             if (it == bucket.end()) {
                 it = bucket.emplace(key, P.launches.size()).first;
@@ -335,7 +336,7 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
             return fail(QNAE_EINVAL, "instance %d: half-state solves need n > %d", i, kResidentMaxN);
     }
     if (count == 0) return QNAE_OK;
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
 
     // ---- the batch's shape: a plan seen before, or a new one ----------------
@@ -439,7 +440,7 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
             HIP_TRY(run(K_BATCH_SWEEP, L.bytes, [&] {
                 return qnae::launch_sweep_batch(L.tb, L.dtype, L.kind, (const SweepArgs*)(d + L.args_at),
                                                 (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, st,
-                                                L.half);
+                                                L.virt);
             }));
         }
         for (int i : P->sweep_members) {

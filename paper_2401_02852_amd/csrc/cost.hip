@@ -169,6 +169,54 @@ __global__ __launch_bounds__(256) void cost_batch_kernel(const CostArgs* args, c
     cost_chunk<NP, WIDE, U16>(a, (uint64_t)(blockIdx.x - first[lo]) * blockDim.x + threadIdx.x);
 }
 
+// What precedes a run in one launch: its tables from pinned host memory to the
+// device (a copy command of their own took a 3-4 us kernel and a launch gap),
+// and, with a cost, whether the diagonal is flip-symmetric: 16 bytes of the
+// lower half against the 16 bytes at the mirrored place, reversed. Bound by
+// the one read of the diagonal; a difference anywhere ends every workgroup's
+// loop early.
+__device__ __forceinline__ uint32_t flip_word(uint32_t w, bool u16) {
+    return u16 ? (w >> 16) | (w << 16) : __builtin_bswap32(w);
+}
+
+constexpr int kProThreads = 256, kProUnroll = 4;
+template <bool U16>
+__global__ __launch_bounds__(kProThreads) void prologue_kernel(const PrologueArgs a) {
+    const uint64_t id = (uint64_t)blockIdx.x * kProThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kProThreads;
+    for (uint64_t i = id; i < a.copies; i += stride) a.dst[i] = a.src[i];
+    if (!a.cost) return;
+    // a.quads 16-byte pieces: piece i faces a.quads - 1 - i
+    const uint64_t half = a.quads / 2;
+    uint32_t diff = 0u;
+    for (uint64_t i = id; i < half; i += kProUnroll * stride) {
+        uint4 x[kProUnroll], y[kProUnroll];
+#pragma unroll
+        for (int u = 0; u < kProUnroll; ++u) {
+            const uint64_t j = i + u * stride < half ? i + u * stride : i;
+            x[u] = a.cost[j];
+            y[u] = a.cost[a.quads - 1 - j];
+        }
+#pragma unroll
+        for (int u = 0; u < kProUnroll; ++u)
+            diff |= (x[u].x ^ flip_word(y[u].w, U16)) | (x[u].y ^ flip_word(y[u].z, U16)) |
+                    (x[u].z ^ flip_word(y[u].y, U16)) | (x[u].w ^ flip_word(y[u].x, U16));
+        // more to read, and no workgroup has found a difference?
+        if (diff != 0u || (i + kProUnroll * stride < half &&
+                           __hip_atomic_load(a.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != 0u))
+            break;
+    }
+    // One counter: workgroups done, and 2^16 for each that found a difference.
+    const uint32_t mine = __syncthreads_or(diff != 0u) ? 0x10001u : 1u;
+    if (threadIdx.x == 0) {
+        const uint32_t v = mine + __hip_atomic_fetch_add(a.word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((v & 0xffffu) == gridDim.x) {
+            __hip_atomic_store(a.word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.answer, 2u * a.ticket + (v >> 16 ? 1u : 0u), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
 template <int NP, bool U16>
 hipError_t launch_np(const CostArgs& a, bool wide, hipStream_t s) {
     const uint64_t nthreads = a.n >= 5 ? (1ull << (a.n - 5)) : 1ull;
@@ -191,6 +239,18 @@ hipError_t launch_cost(const CostArgs& a, int dtype, bool wide, hipStream_t s) {
     }
     if (need <= 12) return launch_np<12, true>(a, wide, s);
     return launch_np<16, true>(a, wide, s);
+}
+
+hipError_t launch_prologue(const PrologueArgs& a, int dtype, hipStream_t s) {
+    if (a.cost && a.quads < 2) return hipErrorInvalidValue;
+    constexpr uint64_t kPer = (uint64_t)kProThreads * kProUnroll;
+    const uint64_t check = a.cost ? (a.quads / 2 + kPer - 1) / kPer : 1;
+    const uint64_t copy = (a.copies + kProThreads - 1) / kProThreads;
+    const uint64_t want = check > copy ? check : copy;
+    const dim3 grid((uint32_t)(want < 1024 ? want : 1024)), block(kProThreads);
+    if (dtype == 1) hipLaunchKernelGGL(prologue_kernel<false>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(prologue_kernel<true>, grid, block, 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_cost_batch(const CostArgs* args, const uint32_t* first, int count, uint32_t blocks, int dtype,

@@ -7,7 +7,9 @@
 // the ends of segments); then for each segment from the last, reverse sweeps
 // take lam (the first one forms lam = W psi_p) and that segment's checkpoint
 // (psi, uncomputed in place) through the inverse layers, summing the inner
-// products per tile.
+// products per tile. With a flip-symmetric cost psi and lam are symmetric too
+// and both passes keep x < 2^(n-1) only; every sum over the stored elements
+// is then half of the whole one.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -32,12 +34,12 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     if (!std::isfinite(w_psucc) || !std::isfinite(w_energy)) return fail(QNAE_EINVAL, "non-finite weights");
     // a segment longer than p layers is one segment (and p + every stays in range)
     const int every = checkpoint_every > 0 ? std::min(checkpoint_every, std::max(p, 1)) : 4;
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
     const int lut_len = m + 1;
-    const size_t N = (size_t)1 << n;
 
     if (n <= 13) {
+        const size_t N = (size_t)1 << n;
         // tables: forward phases exp(-i gamma c) (unit), (cos b, sin b)
         Blob B;
         const size_t lut_at = B.take(sizeof(float2) * (size_t)(p > 0 ? p : 1) * lut_len);
@@ -87,12 +89,6 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     const int TB = qnae::kAdjointTileBits;
     const int nseg = p > 0 ? (p + every - 1) / every : 1;
     const std::vector<Group> groups = make_groups(n, TB, ctx->min_low_run, ctx->page_bit, 0);
-    const uint32_t tiles = 1u << (n - TB);
-    // checkpoints 0 .. nseg-1 (state after each segment), then lam
-    HIP_TRY(ctx->g_states.reserve(sizeof(float2) * N * (size_t)(nseg + 1)));
-    float2* ck = (float2*)ctx->g_states.ptr;
-    float2* lam = ck + N * (size_t)nseg;
-
     // The forward pass is one plan over all p layers, in place in the last
     // checkpoint's buffer; the boundary sweep that completes the last layer
     // of segment j < nseg - 1 also stores checkpoint j.
@@ -147,38 +143,54 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     Blob B;
     const size_t flut_at = B.take(sizeof(float2) * ftab.size());
     const size_t blut_at = B.take(sizeof(float2) * btab.size());
-    const size_t rp_at = B.take(sizeof(double*) * (total_aops + 1));
-    const size_t rb_at = B.take(sizeof(uint32_t) * (total_aops + 1));
-    const size_t ro_at = B.take(sizeof(double*) * (total_aops + 1));
-    const size_t res_at = B.take(sizeof(double) * 3 * (total_aops + 1));
+    B.take(16);
+    const size_t res_at = B.take(sizeof(double) * 3 * (total_aops + 1));  // pinned only
     HIP_TRY(ctx->h_blob.reserve(B.size));
     HIP_TRY(ctx->g_blob.reserve(B.size));
-    HIP_TRY(ctx->g_partials.reserve(sizeof(double) * 3 * tiles * (size_t)(total_aops + 1)));
     char* h = (char*)ctx->h_blob.ptr;
     char* d = (char*)ctx->g_blob.ptr;
-    double* parts = (double*)ctx->g_partials.ptr;
-    double* res_dev = (double*)(d + res_at);
     std::memcpy(h + flut_at, ftab.data(), sizeof(float2) * ftab.size());
     std::memcpy(h + blut_at, btab.data(), sizeof(float2) * btab.size());
-    {
-        const double** rp = (const double**)(h + rp_at);
-        uint32_t* rb = (uint32_t*)(h + rb_at);
-        double** ro = (double**)(h + ro_at);
-        for (int q = 0; q <= total_aops; ++q) {  // entry total_aops: forward readout
-            rp[q] = parts + 3 * (size_t)tiles * q;
-            rb[q] = tiles;
-            ro[q] = res_dev + 3 * (size_t)q;
-        }
+    const bool check = p > 0 && n >= kFlipMinN, early = check && n <= kFlipEarlyMaxN;
+    // Elements of a state's buffer: with the first sweep launched on the whole
+    // state ahead of the answer, whole states, used up to the lower half.
+    size_t room = (size_t)1 << n;
+    // checkpoints 0 .. nseg-1 (state after each segment), then lam
+    auto reserve = [&]() -> hipError_t {
+        if (hipError_t e = ctx->g_states.reserve(sizeof(float2) * room * (size_t)(nseg + 1))) return e;
+        return ctx->g_partials.reserve(sizeof(double) * 3 * (room >> TB) * (size_t)(total_aops + 1));
+    };
+    if (!check || early) HIP_TRY(reserve());
+    if (int rc = prologue(ctx, d, h, blut_at + sizeof(float2) * btab.size(), check ? cost_dev : nullptr, cost_dtype, n,
+                          s))
+        return rc;
+    bool half = false;
+    if (check && !early) {
+        if (int rc = flip_answer(ctx, s, &half)) return rc;
+        if (half) room >>= 1;
+        HIP_TRY(reserve());
     }
-    HIP_TRY(hipMemcpyAsync(d, h, B.size, hipMemcpyHostToDevice, s));
+    float2* ck = (float2*)ctx->g_states.ptr;
+    float2* lam = ck + room * (size_t)nseg;
+    double* parts = (double*)ctx->g_partials.ptr;
     const float2* d_flut = (const float2*)(d + flut_at);
     const float2* d_blut = (const float2*)(d + blut_at);
 
     // forward pass
-    double* fwd_parts = parts + 3 * (size_t)tiles * total_aops;
-    float2* const run = ck + N * (size_t)(nseg - 1);
+    float2* const run = ck + room * (size_t)(nseg - 1);
+    F.half = half;
+    size_t N = room;  // stored elements of a state
+    uint32_t tiles = (uint32_t)(N >> TB);
     for (size_t q = 0; q < F.ops.size(); ++q) {
         const Op& op = F.ops[q];
+        if (early && q == 1) {
+            if (int rc = flip_answer(ctx, s, &half)) return rc;
+            F.half = half;
+            N >>= half ? 1 : 0;
+            tiles = (uint32_t)(N >> TB);
+        }
+        // row total_aops of the partial sums: the forward readout
+        double* const fwd_parts = parts + 3 * (size_t)tiles * total_aops;
         SweepArgs a;
         sweep_args(F, op, run, cost_dev, d_flut, fwd_parts, &a);
         if (ckpt_of[q] < 0) {
@@ -187,12 +199,13 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
             continue;
         }
         const std::complex<double> f = mixer_form(betas[op.lut_layer - 1], n).scale;
-        a.ckpt = ck + N * (size_t)ckpt_of[q];
+        a.ckpt = ck + room * (size_t)ckpt_of[q];
         a.ckpt_scale = make_float2((float)f.real(), (float)f.imag());
-        HIP_TRY(timed(ctx, op_profile_kind(op), op_bytes(F, op) + std::ldexp(8.0, n), s,
+        HIP_TRY(timed(ctx, op_profile_kind(op), op_bytes(F, op) + 8.0 * (double)N, s,
                       [&] { return qnae::launch_sweep_ckpt(cost_dtype, a, s); }));
     }
-    if (p > 0 && F.flips_before[p]) HIP_TRY(qnae::launch_reverse(run, N, s));
+    // a symmetric state equals its all-qubit flip: relabelling is the identity
+    if (!half && p > 0 && F.flips_before[p]) HIP_TRY(qnae::launch_reverse(run, N, s));
     // lam = W psi_p is formed by the first reverse sweep, which mixes one
     // group only (a layer spans at least two groups here, n > TB), from the
     // psi_p and cost it loads
@@ -207,7 +220,7 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     int relabel = 0;
     for (int j = nseg - 1; j >= 0; --j) {
         const Seg& S = segs[j];
-        float2* psi = ck + N * (size_t)j;
+        float2* psi = ck + room * (size_t)j;
         const int psi_flip = relabel;
         std::vector<int> done(S.inv.size(), 0);
         for (const AdjOp& op : S.aops) {
@@ -220,13 +233,18 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
             a.lut = op.phase_layer >= 0 ? d_blut + S.blut_at + (size_t)op.phase_layer * lut_len : nullptr;
             a.partials = parts + 3 * (size_t)tiles * q;
             a.n = n;
-            a.nw = n - TB;
             a.lut_len = lut_len;
+            // half: bit n-1, when the group has it, is the virtual bit
             for (int i = 0; i < TB; ++i) {
                 a.pos[i] = (uint8_t)g.pos[i];
-                a.tile_bits |= 1ull << g.pos[i];
+                if (half && g.pos[i] == n - 1) a.virt = 1;
+                else a.tile_bits |= 1ull << g.pos[i];
             }
-            a.wmask = ((1ull << n) - 1ull) & ~a.tile_bits;
+            a.mir = N - 1;
+            a.wmask = (N - 1) & ~a.tile_bits;
+            // (its mirror covers the highest stored bit outside the tile)
+            if (a.virt) a.wmask &= ~(1ull << (63 - __builtin_clzll(a.wmask)));
+            a.nw = __builtin_popcountll(a.wmask);
             a.pre_mask = op.pre_layer >= 0 ? g.mask : 0u;
             a.post_mask = op.post_layer >= 0 ? g.mask : 0u;
             const int qubits = __builtin_popcount(g.mask);
@@ -246,7 +264,7 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
             double gw = 0.0;
             if (op.phase_layer >= 0) {
                 const int i = op.phase_layer;
-                relabel ^= S.inv[i].form.flip;
+                relabel ^= half ? 0 : S.inv[i].form.flip;
                 a.cost_flip = relabel ? (uint64_t)N - 1ull : 0ull;
                 gw = std::pow(factor2(i), n);
             }
@@ -263,9 +281,9 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
             a.w_psucc = (float)w_psucc;
             a.w_energy = (float)w_energy;
             const double cost_bytes = cost_dtype == QNAE_U8 ? 1.0 : 2.0;
-            const double bytes = std::ldexp(32.0 - (a.store_psi ? 0.0 : 8.0) - (weigh ? 8.0 : 0.0) +
-                                                (op.phase_layer >= 0 || weigh ? cost_bytes : 0.0),
-                                            n);
+            const double bytes = (32.0 - (a.store_psi ? 0.0 : 8.0) - (weigh ? 8.0 : 0.0) +
+                                  (op.phase_layer >= 0 || weigh ? cost_bytes : 0.0)) *
+                                 (double)N;
             HIP_TRY(timed(ctx, K_ADJOINT, bytes, s,
                           [&] { return qnae::launch_adjoint(cost_dtype, op.kind, a, s, weigh); }));
             order.emplace_back(j, &op);
@@ -273,21 +291,19 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
             ++q;
         }
     }
-    HIP_TRY(qnae::launch_final_reduce_batch((const double* const*)(d + rp_at), (const uint32_t*)(d + rb_at),
-                                            (double* const*)(d + ro_at), total_aops + 1, s));
-    HIP_TRY(hipMemcpyAsync(h + res_at, d + res_at, sizeof(double) * 3 * (total_aops + 1), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipEventRecord(ctx->staging_done, s));
+    const double* r = (const double*)(h + res_at);  // the reduction writes pinned memory: no copy follows it
+    HIP_TRY(qnae::launch_final_reduce_rows(parts, tiles, (double*)(h + res_at), total_aops + 1, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const double* r = (const double*)(h + res_at);
+    const double twice = half ? 4.0 : 2.0;
     for (int l = 0; l < p; ++l) dgammas[l] = dbetas[l] = 0.0;
     for (int k = 0; k < total_aops; ++k) {
         const Seg& S = segs[order[k].first];
         const AdjOp& op = *order[k].second;
-        if (op.pre_layer >= 0) dbetas[S.b - 1 - op.pre_layer] += 2.0 * r[3 * k];
-        if (op.phase_layer >= 0) dgammas[S.b - 1 - op.phase_layer] += 2.0 * gamma_weight[k] * r[3 * k + 1];
-        if (op.post_layer >= 0) dbetas[S.b - 1 - op.post_layer] += 2.0 * r[3 * k + 2];
+        if (op.pre_layer >= 0) dbetas[S.b - 1 - op.pre_layer] += twice * r[3 * k];
+        if (op.phase_layer >= 0) dgammas[S.b - 1 - op.phase_layer] += twice * gamma_weight[k] * r[3 * k + 1];
+        if (op.post_layer >= 0) dbetas[S.b - 1 - op.post_layer] += twice * r[3 * k + 2];
     }
-    const double sc = std::norm(final_scale);
+    const double sc = std::norm(final_scale) * (half ? 2.0 : 1.0);
     out->p_success = r[3 * total_aops] * sc;
     out->expected_cost = r[3 * total_aops + 1] * sc;
     out->norm = r[3 * total_aops + 2] * sc;
@@ -309,7 +325,7 @@ int qnae_qaoa_grad_batched(qnae_ctx* ctx, const qnae_grad_job* jobs, int32_t cou
     }
     if (count == 0) return QNAE_OK;
     const int every = checkpoint_every > 0 ? checkpoint_every : 4;
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
     // Small jobs: per job its tables and outputs in one blob, checkpoints in
     // one device buffer, one launch per cost type.

@@ -58,7 +58,11 @@ struct HostBuf {
 
 // Event-timed kernel tallies (qnae_profile_*).
 enum { K_COST, K_FIRST, K_MIDDLE, K_BOUNDARY, K_FINAL, K_RESIDENT, K_REDUCE, K_BATCH_COST, K_BATCH_RESIDENT,
-       K_BATCH_SWEEP, K_BATCH_REDUCE, K_ADJOINT, K_KINDS };
+       K_BATCH_SWEEP, K_BATCH_REDUCE, K_ADJOINT, K_PROLOGUE, K_KINDS };
+
+// Byte offsets in a context's small device and pinned buffers.
+constexpr size_t kSmallBytes = 64;
+constexpr size_t kSmallFlipAt = 48;  // device: the flip check's counter; pinned: its answer
 
 struct Profiler {
     struct Rec {
@@ -136,8 +140,8 @@ struct qnae_ctx {
     int device = 0;
     qnae_host::Profiler prof;
     // single-instance path
-    qnae_host::DevBuf state, partials, luts, clauses, forms, small;  // small: zeros counter + 3 result doubles
-    qnae_host::HostBuf h_luts, h_clauses, h_forms, h_small;
+    qnae_host::DevBuf state, partials, luts, clauses, small;  // small: zeros counter + 3 result doubles
+    qnae_host::HostBuf h_luts, h_clauses, h_small;
     // batched path: uploaded tables and work lists, states, partial sums, results
     qnae_host::DevBuf b_blob, b_states, b_partials, b_results;
     // gradient: checkpoints + adjoint state, tables, partial sums
@@ -148,9 +152,11 @@ struct qnae_ctx {
     bool use_graphs = true;
     hipStream_t capture_stream = nullptr;
     std::vector<std::unique_ptr<qnae_host::BatchPlan, qnae_host::BatchPlanFree>> batch_plans;
-    // batched cost builds: their own staging, so a run's host work can overlap their kernels
+    // batched cost builds: their own staging
     qnae_host::DevBuf c_blob;
     qnae_host::HostBuf h_cblob;
+    // the last cost build, single or batched (each waits for the one before): their staging is their own,
+    // so a run's host work overlaps their kernels
     hipEvent_t cost_staging_done = nullptr;
     // sweep tile shapes chosen per (n, cost type), by qnae_autotune or qnae_set_tune
     std::map<std::pair<int, int>, qnae_tune> tunes;
@@ -158,6 +164,7 @@ struct qnae_ctx {
     // sampling: tile masses and prefix sums, uniforms and outcomes
     qnae_host::DevBuf s_dev;
     qnae_host::HostBuf h_sample;
+    uint32_t flip_ticket = 0;           // flip checks launched so far
     int tile_bits = 13;                 // tile size of the plain sweeps (log2 amplitudes)
     int min_low_run = 4;                // minimum contiguous low run (log2 amplitudes)
     int page_bit = 18;                  // first index bit above a 2 MiB page of amplitudes
@@ -172,12 +179,29 @@ struct qnae_ctx {
 
 namespace qnae_host {
 
-// Makes the context's device current and waits until pinned staging is free.
-int enter(qnae_ctx* ctx);
+// Makes the context's device current, waits until pinned staging is free and
+// orders s behind the context's last cost build.
+int enter(qnae_ctx* ctx, hipStream_t s);
 // With the context's device current: looks up that device's static scratch
 // array of qnae_qaoa_run_noalloc (once per device) and reserves the
 // context's fixed pinned staging for it.
 int noalloc_setup(qnae_ctx* ctx);
+// Smallest n whose single runs and gradients are checked for a flip-symmetric
+// cost (and then use half the state).
+constexpr int kFlipMinN = 20;
+// Up to this n the first sweep is launched on the whole state before the
+// check's answer is known: it covers the wait (about 10 us), and its lower
+// half is what a half-state run goes on from. Above, a whole first sweep
+// costs more than the wait.
+constexpr int kFlipEarlyMaxN = 24;
+// The launch ahead of a run: copies `bytes` (rounded up to 16; both buffers
+// hold that many) of pinned src to dst and, unless cost is null, checks the
+// diagonal; flip_answer waits for the check's answer by watching the pinned
+// word that it writes, so that work queued behind it need not be waited for.
+// One check at a time on a context.
+int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void* cost, int dtype, int n,
+             hipStream_t s);
+int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric);
 // fn(i) for i in [0, count), spread over the context's host threads when the
 // work is large enough to pay for the hand-off (`items` units of it).
 void parallel_for(qnae_ctx* ctx, int count, size_t items, const std::function<void(int)>& fn);
@@ -301,6 +325,7 @@ struct SweepPlan {
     int n = 0, m = 0, p = 0, TB = 13, dtype = QNAE_U8, lut_len = 1;
     bool keep = false;
     bool half = false;  // state and cost over x < 2^(n-1) (NAE global-flip symmetry)
+    bool expand = false;  // half, keep: the kept state is the whole one
     std::vector<Group> groups;
     std::vector<Op> ops;
     std::vector<qnae::MixForm> forms;
@@ -327,7 +352,7 @@ void sweep_args(const SweepPlan& P, const Op& op, float2* psi, const void* cost,
 // flips_before: p + 1) and the op's group (TB bit positions and mix mask).
 struct PlanRef {
     int n, p, TB, lut_len;
-    bool keep, half;
+    bool keep, half, expand;
     const qnae::MixForm* forms;
     const int* flips_before;
     std::complex<double> final_scale;
@@ -339,6 +364,10 @@ void sweep_args_for(const PlanRef& P, const int* pos, uint32_t mask, const Op& o
 // angles changed.
 void sweep_args_angles(const PlanRef& P, const Op& op, qnae::SweepArgs* a);
 void sweep_args_angles(const SweepPlan& P, const Op& op, qnae::SweepArgs* a);
+// Does the op's group hold the virtual bit of a half-state plan (bit n-1)?
+inline bool op_virtual(const SweepPlan& P, const Op& op) {
+    return P.half && P.groups[op.group].pos[P.TB - 1] == P.n - 1;
+}
 // Algorithmic bytes of one op and its profiling kind.
 double op_bytes(const SweepPlan& P, const Op& op);
 int op_profile_kind(const Op& op);

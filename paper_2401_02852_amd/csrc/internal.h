@@ -42,6 +42,23 @@ hipError_t launch_cost(const CostArgs& a, int dtype, bool wide, hipStream_t s);
 hipError_t launch_cost_batch(const CostArgs* args, const uint32_t* first, int count, uint32_t blocks, int dtype,
                              int max_clauses, bool wide, hipStream_t s);
 
+// Launch ahead of a run: copies `copies` 16-byte pieces from src (pinned host
+// memory) to dst and, with a cost (of `quads` >= 2 16-byte pieces), checks the
+// diagonal for flip symmetry, cost[x] == cost[2^n - 1 - x] for every x. word:
+// a device word that is zero before and after; the last workgroup writes
+// 2 * ticket + (0 symmetric, 1 not) to *answer (pinned).
+struct PrologueArgs {
+    uint4* dst;
+    const uint4* src;
+    uint64_t copies;
+    const uint4* cost;
+    uint64_t quads;
+    uint32_t* word;
+    uint32_t* answer;
+    uint32_t ticket;
+};
+hipError_t launch_prologue(const PrologueArgs& a, int dtype, hipStream_t s);
+
 // ---------------------------------------------------------------------------
 // State sweeps
 // ---------------------------------------------------------------------------
@@ -95,7 +112,8 @@ struct SweepArgs {
     // 2^(n-1) - 1. Without a virtual bit (vbit < 0) a half sweep is a plain
     // sweep over n-1 bits.
     int32_t half;
-    int32_t vbit;
+    int32_t vbit;          // -1 or TB - 1
+    int32_t expand;        // readout kinds with store, half: also store the upper half (psi holds 2^n)
     uint64_t mir;
     // Checkpointing boundary sweep (gradient forward pass): the state right
     // after the pre mixing, which completes a layer, times ckpt_scale (that
@@ -106,17 +124,16 @@ struct SweepArgs {
 };
 
 hipError_t launch_sweep(int tb, int dtype, int kind, const SweepArgs& a, hipStream_t s);
-// A boundary sweep that also stores a checkpoint (a.ckpt), 13-bit tiles,
-// full state.
+// A boundary sweep that also stores a checkpoint (a.ckpt), 13-bit tiles.
 hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s);
 
 // One sweep step over `count` states at once. Instance i owns blocks
 // first[i] .. first[i+1]-1 (first has count+1 entries, first[count] =
 // blocks), one per tile of its own geometry; args[i].partials receives 3
 // doubles per tile for readout kinds. Every instance uses tiles of tb bits
-// (12, 13 or 14). half: every instance is a half-state sweep (args[i].half).
+// (12, 13 or 14). virt: every instance's group holds the virtual bit (args[i].vbit >= 0), or none does.
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool half = false);
+                              uint32_t blocks, hipStream_t s, bool virt = false);
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
 
 // Whole circuit for n <= 14 in one workgroup (state resident in LDS).
@@ -176,6 +193,12 @@ struct AdjointArgs {
     float pre_t, pre_r, pre_w, post_t, post_r, post_w;
     uint64_t cost_flip;  // 0 or 2^n - 1: the phase of element x reads cost[x ^ cost_flip]
     int32_t psi_flip;    // psi of element x sits at x ^ (2^n - 1) (relabelled against lam)
+    // Half state (flip-symmetric cost): both states hold x < 2^(n-1). virt:
+    // the group mixes bit n-1 as tile bit 12, which maps a stored index y to
+    // mir - y, mir = 2^(n-1) - 1; other groups run as full sweeps over n-1
+    // bits. Relabelling is the identity there (psi_flip = cost_flip = 0).
+    int32_t virt;
+    uint64_t mir;
     int32_t store_psi;
     float w_psucc, w_energy;  // weigh: lam = (w_psucc [C = 0] + w_energy C) psi instead of a load
 };
@@ -208,6 +231,9 @@ hipError_t launch_final_reduce(const double* partials, int64_t blocks, double* o
 // Instance i: sum of blocks[i] triples at partials[i] -> outs[i][0..2].
 hipError_t launch_final_reduce_batch(const double* const* partials, const uint32_t* blocks, double* const* outs,
                                      int count, hipStream_t s);
+
+// Sum i of `count`: `blocks` triples at partials + 3 blocks i -> out[3 i ..].
+hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, double* out, int count, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Sampling outcomes of a state (sample.hip)

@@ -16,7 +16,6 @@ namespace {
 using qnae::MixForm;
 
 // Scratch layout (bytes). Every call on a device shares that device's copy.
-constexpr size_t kResultAt = 0;                    // 3 doubles
 constexpr int kMaxTable = 1 << 18;                 // phase table entries, p * (m + 1)
 constexpr size_t kTablesAt = 256;                  // float2 [kMaxTable]
 constexpr int kMaxLayers = 4096;                   // p
@@ -94,37 +93,38 @@ extern "C" int qnae_qaoa_run_noalloc(qnae_ctx* ctx, const void* cost_dev, int32_
     if (tiles > kMaxTiles)
         return fail(QNAE_EINVAL, "n=%d with %d-bit tiles needs %lld tile sums, above the static scratch's %d (n <= %d)",
                     n, TB, (long long)tiles, kMaxTiles, 18 + TB);
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     if (!ctx->na_dev || ctx->na_host.bytes < kHostBytes) return fail(QNAE_EINVAL, "context without no-alloc scratch");
     hipStream_t s = (hipStream_t)stream;
     const bool keep = state_dev != nullptr;
 
     char* const dev = (char*)ctx->na_dev;
     float2* const d_tables = (float2*)(dev + kTablesAt);
-    MixForm* const d_forms = (MixForm*)(dev + kFormsAt);
+    MixForm* const d_forms = (MixForm*)(d_tables + (size_t)T * lut_len);  // tables, then forms
     double* const d_partials = (double*)(dev + kPartialsAt);
-    double* const d_result = (double*)(dev + kResultAt);
     char* const host = (char*)ctx->na_host.ptr;
     float2* const h_tables = (float2*)(host + kHostTablesAt);
-    MixForm* const h_forms = (MixForm*)(host + kHostFormsAt);
+    MixForm* const h_forms = (MixForm*)(h_tables + (size_t)T * lut_len);
     int* const h_flips = (int*)(host + kHostFlipsAt);
     double* const h_result = (double*)(host + kHostResultAt);
 
     const std::complex<double> final_scale = build_tables(n, m, gammas, betas, p, h_tables, h_forms);
     h_flips[0] = 0;
     for (int l = 0; l < p; ++l) h_flips[l + 1] = h_flips[l] ^ h_forms[l].flip;
-    const double readout_scale = std::norm(final_scale);
-    HIP_TRY(hipMemcpyAsync(d_tables, h_tables, sizeof(float2) * (size_t)T * lut_len, hipMemcpyHostToDevice, s));
+    const bool check = p > 0 && n >= kFlipMinN;  // as qnae_qaoa_run
+    if (int rc = prologue(ctx, d_tables, h_tables, sizeof(float2) * ((size_t)T * lut_len + p),
+                          check ? cost_dev : nullptr, cost_dtype, n, s))
+        return rc;
+    bool half = false;
 
     if (resident) {
-        if (p > 0) HIP_TRY(hipMemcpyAsync(d_forms, h_forms, sizeof(MixForm) * p, hipMemcpyHostToDevice, s));
         qnae::ResidentArgs a;
         a.state_in = nullptr;
         a.cost = cost_dev;
         a.luts = d_tables;
         a.forms = d_forms;
         a.state_out = (float2*)state_dev;
-        a.out = d_result;
+        a.out = h_result;
         a.store_scale = make_float2((float)final_scale.real(), (float)final_scale.imag());
         a.n = n;
         a.p = p;
@@ -133,24 +133,30 @@ extern "C" int qnae_qaoa_run_noalloc(qnae_ctx* ctx, const void* cost_dev, int32_
     } else {
         GroupSpec spec[kMaxGroups];
         const int ngroups = make_group_specs(n, TB, tune.low_run_bits, tune.page_bit, tune.split, spec);
-        const PlanRef plan{n, p, TB, lut_len, keep, false, h_forms, h_flips, final_scale};
+        PlanRef plan{n, p, TB, lut_len, keep, false, keep, h_forms, h_flips, final_scale};
         float2* const psi = (float2*)state_dev;
+        int rc = QNAE_OK;
         hipError_t e = hipSuccess;
+        int waiting = check ? (n <= kFlipEarlyMaxN ? 1 : 0) : -1;  // sweeps ahead of the check's answer
         for_each_op(ngroups, p, false, [&](const Op& op) {
-            if (e != hipSuccess) return;
+            if (e != hipSuccess || rc) return;
+            if (waiting-- == 0) {
+                if ((rc = flip_answer(ctx, s, &half))) return;
+                plan.half = half;
+            }
             int pos[16];
             for (int i = 0; i < TB; ++i) pos[i] = spec[op.group].pos[i];
             qnae::SweepArgs a;
             sweep_args_for(plan, pos, spec[op.group].mask, op, psi, cost_dev, d_tables, d_partials, &a);
             e = qnae::launch_sweep(TB, cost_dtype, op.kind, a, s);
         });
+        if (rc) return rc;
         HIP_TRY(e);
-        if (keep && p > 0 && h_flips[p]) HIP_TRY(qnae::launch_reverse(psi, 1ull << n, s));
-        HIP_TRY(qnae::launch_final_reduce(d_partials, tiles, d_result, s));
+        if (keep && !half && p > 0 && h_flips[p]) HIP_TRY(qnae::launch_reverse(psi, 1ull << n, s));
+        HIP_TRY(qnae::launch_final_reduce(d_partials, tiles >> (half ? 1 : 0), h_result, s));
     }
-    HIP_TRY(hipMemcpyAsync(h_result, d_result, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipEventRecord(ctx->staging_done, s));
     HIP_TRY(hipStreamSynchronize(s));
+    const double readout_scale = std::norm(final_scale) * (half ? 2.0 : 1.0);
     out->p_success = h_result[0] * readout_scale;
     out->expected_cost = h_result[1] * readout_scale;
     out->norm = h_result[2] * readout_scale;

@@ -27,8 +27,9 @@ int qnae_create(qnae_ctx** out, int device) try {
     hipError_t e = hipEventCreateWithFlags(&ctx->staging_done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->cost_staging_done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = ctx->small.reserve(64);
-    if (e == hipSuccess) e = ctx->h_small.reserve(64);
+    if (e == hipSuccess) e = ctx->small.reserve(kSmallBytes);
+    if (e == hipSuccess) e = hipMemset(ctx->small.ptr, 0, kSmallBytes);
+    if (e == hipSuccess) e = ctx->h_small.reserve(kSmallBytes);
     if (e != hipSuccess) {
         qnae_destroy(ctx);
         return fail(QNAE_EHIP, "qnae_create: %s", hipGetErrorString(e));
@@ -57,12 +58,12 @@ int qnae_destroy(qnae_ctx* ctx) try {
     if (!ctx) return QNAE_OK;
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
-    for (DevBuf* b : {&ctx->state, &ctx->partials, &ctx->luts, &ctx->clauses, &ctx->forms, &ctx->small, &ctx->b_blob,
+    for (DevBuf* b : {&ctx->state, &ctx->partials, &ctx->luts, &ctx->clauses, &ctx->small, &ctx->b_blob,
                       &ctx->c_blob,
                       &ctx->b_states, &ctx->b_partials, &ctx->b_results, &ctx->g_states, &ctx->g_blob,
                       &ctx->g_partials, &ctx->tune_cost, &ctx->s_dev})
         b->release();
-    for (HostBuf* b : {&ctx->h_luts, &ctx->h_clauses, &ctx->h_forms, &ctx->h_small, &ctx->h_blob, &ctx->h_results,
+    for (HostBuf* b : {&ctx->h_luts, &ctx->h_clauses, &ctx->h_small, &ctx->h_blob, &ctx->h_results,
                        &ctx->h_sample, &ctx->na_host, &ctx->h_cblob})
         b->release();
     if (ctx->staging_done) (void)hipEventDestroy(ctx->staging_done);
@@ -102,7 +103,9 @@ int build_cost(qnae_ctx* ctx, const int32_t* clauses, int32_t m, int32_t n, int3
     if (!cost_dev) return fail(QNAE_EINVAL, "null cost_dev");
     if (int rc = check_aligned(cost_dev, "cost_dev")) return rc;
     if (int rc = check_literals(clauses, m, n, k)) return rc;
-    if (int rc = enter(ctx)) return rc;
+    if (!ctx) return fail(QNAE_EINVAL, "null context");
+    HIP_TRY(hipSetDevice(ctx->device));
+    HIP_TRY(hipEventSynchronize(ctx->cost_staging_done));
     hipStream_t s = (hipStream_t)stream;
     const int states = half ? n - 1 : n;
 
@@ -125,7 +128,7 @@ int build_cost(qnae_ctx* ctx, const int32_t* clauses, int32_t m, int32_t n, int3
     a.zeros = num_solutions ? zeros : nullptr;
     const double cost_bytes = (double)(cost_dtype == QNAE_U8 ? 1 : 2) * std::ldexp(1.0, states);
     HIP_TRY(timed(ctx, K_COST, cost_bytes, s, [&] { return qnae::launch_cost(a, cost_dtype, n > 32, s); }));
-    HIP_TRY(hipEventRecord(ctx->staging_done, s));
+    HIP_TRY(hipEventRecord(ctx->cost_staging_done, s));
     if (num_solutions) {
         HIP_TRY(hipMemcpyAsync(ctx->h_small.ptr, zeros, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -160,32 +163,39 @@ namespace {
 
 // Depth-p run from |+>. half: state and cost hold x < 2^(n-1) only (NAE
 // global-flip symmetry); the readout sums then count every amplitude twice.
+// A whole diagonal that turns out flip-symmetric (every NAE instance's is)
+// runs on the half state too, in the lower half of the state buffer; the
+// last sweep of a kept state then writes both halves. Checked from
+// kFlipMinN on: one read of the diagonal against half of 16 bytes per
+// amplitude and sweep.
 int run(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int32_t n, int32_t m, const double* gammas,
-        const double* betas, int32_t p, void* state_dev, qnae_result* out, void* stream, bool half) {
+        const double* betas, int32_t p, void* state_dev, qnae_result* out, void* stream, bool half_api) {
+    bool half = half_api;
     if (int rc = check_run_args(n, m, cost_dtype, cost_dev, gammas, betas, p)) return rc;
     if (!out) return fail(QNAE_EINVAL, "null result pointer");
     if (int rc = check_aligned(state_dev, "state_dev")) return rc;
     if (half && n <= kResidentMaxN)
         return fail(QNAE_EINVAL, "n=%d: half-state runs need n > %d (smaller n: qnae_qaoa_run)", n, kResidentMaxN);
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
     const bool keep = state_dev != nullptr;
     const int T = p > 0 ? p : 1;
     const int lut_len = m + 1;
 
-    HIP_TRY(ctx->h_luts.reserve(sizeof(float2) * (size_t)T * lut_len));
-    HIP_TRY(ctx->h_forms.reserve(sizeof(MixForm) * (size_t)T));
+    const size_t entries = (size_t)T * lut_len;
+    HIP_TRY(ctx->h_luts.reserve(sizeof(float2) * (entries + p + 1)));
     float2* tables = (float2*)ctx->h_luts.ptr;
-    MixForm* forms = (MixForm*)ctx->h_forms.ptr;
+    MixForm* forms = (MixForm*)(tables + entries);  // tables, then forms
     const std::complex<double> final_scale = build_tables(n, m, gammas, betas, p, tables, forms);
-    const double readout_scale = std::norm(final_scale) * (half ? 2.0 : 1.0);
     const float2 store_scale = make_float2((float)final_scale.real(), (float)final_scale.imag());
 
-    double* out_dev = (double*)((char*)ctx->small.ptr + 16);
+    // The kernel that ends the run writes the three sums to pinned memory, so
+    // no copy follows it.
+    double* const sums = (double*)ctx->h_small.ptr;
     const double rb = std::ldexp((double)(cost_dtype == QNAE_U8 ? 1 : 2) * T + (keep ? 8.0 : 0.0), n);
     static_assert(sizeof(MixForm) == sizeof(float2), "a mixer form fills one table slot");
 
-    if (n <= kResidentMaxN && (int64_t)T * lut_len + p <= qnae::kResidentInline) {
+    if (n <= kResidentMaxN && (int64_t)entries + p <= qnae::kResidentInline) {
         // small tables travel in the kernel arguments: one launch, no copies ahead of it
         qnae::ResidentInlineArgs ia;
         qnae::ResidentArgs& a = ia.a;
@@ -194,69 +204,79 @@ int run(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int32_t n, int3
         a.luts = nullptr;
         a.forms = nullptr;
         a.state_out = (float2*)state_dev;
-        a.out = out_dev;
+        a.out = sums;
         a.store_scale = store_scale;
         a.n = n;
         a.p = p;
         a.lut_len = lut_len;
-        std::memcpy(ia.tab, tables, sizeof(float2) * (size_t)T * lut_len);
-        if (p > 0) std::memcpy(ia.tab + (size_t)T * lut_len, forms, sizeof(MixForm) * p);
+        std::memcpy(ia.tab, tables, sizeof(float2) * (entries + p));
         HIP_TRY(timed(ctx, K_RESIDENT, rb, s, [&] { return qnae::launch_resident_inline(cost_dtype, ia, s); }));
     } else if (n <= kResidentMaxN) {
-        HIP_TRY(ctx->luts.reserve(sizeof(float2) * (size_t)T * lut_len));
-        HIP_TRY(hipMemcpyAsync(ctx->luts.ptr, tables, sizeof(float2) * (size_t)T * lut_len, hipMemcpyHostToDevice, s));
-        HIP_TRY(ctx->forms.reserve(sizeof(MixForm) * (size_t)T));
-        if (p > 0) HIP_TRY(hipMemcpyAsync(ctx->forms.ptr, forms, sizeof(MixForm) * p, hipMemcpyHostToDevice, s));
+        HIP_TRY(ctx->luts.reserve(sizeof(float2) * (entries + p + 1)));
+        if (int rc = prologue(ctx, ctx->luts.ptr, tables, sizeof(float2) * (entries + p), nullptr, cost_dtype, n, s))
+            return rc;
         qnae::ResidentArgs a;
         a.state_in = nullptr;
         a.cost = cost_dev;
         a.luts = (const float2*)ctx->luts.ptr;
-        a.forms = (const MixForm*)ctx->forms.ptr;
+        a.forms = (const MixForm*)(a.luts + entries);
         a.state_out = (float2*)state_dev;
-        a.out = out_dev;
+        a.out = sums;
         a.store_scale = store_scale;
         a.n = n;
         a.p = p;
         a.lut_len = lut_len;
         HIP_TRY(timed(ctx, K_RESIDENT, rb, s, [&] { return qnae::launch_resident(cost_dtype, a, s); }));
     } else {
-        HIP_TRY(ctx->luts.reserve(sizeof(float2) * (size_t)T * lut_len));
-        HIP_TRY(hipMemcpyAsync(ctx->luts.ptr, tables, sizeof(float2) * (size_t)T * lut_len, hipMemcpyHostToDevice, s));
+        const bool check = !half && p > 0 && n >= kFlipMinN, early = check && n <= kFlipEarlyMaxN;
         const qnae_tune tune = tune_for(ctx, n, cost_dtype);
         const int TB = tune.tile_bits;
-        const int stored = half ? n - 1 : n;
+        HIP_TRY(ctx->luts.reserve(sizeof(float2) * (entries + 1)));
         float2* psi = (float2*)state_dev;
-        if (!psi) {
-            HIP_TRY(ctx->state.reserve(sizeof(float2) << stored));
-            psi = (float2*)ctx->state.ptr;
-        }
-        const int64_t blocks = 1ll << (stored - TB);
-        HIP_TRY(ctx->partials.reserve(sizeof(double) * 3 * (size_t)blocks));
+        auto reserve = [&](int stored) -> hipError_t {
+            if (!state_dev) {
+                if (hipError_t e = ctx->state.reserve(sizeof(float2) << stored)) return e;
+                psi = (float2*)ctx->state.ptr;
+            }
+            return ctx->partials.reserve(sizeof(double) * 3 * ((size_t)1 << (stored - TB)));
+        };
+        if (!check || early) HIP_TRY(reserve(half ? n - 1 : n));
+        if (int rc = prologue(ctx, ctx->luts.ptr, tables, sizeof(float2) * entries, check ? cost_dev : nullptr,
+                              cost_dtype, n, s))
+            return rc;
         SweepPlan P;
         plan_sweeps(P, n, m, p, cost_dtype, TB, tune.low_run_bits, tune.page_bit, tune.split, keep, forms,
                     final_scale);
         P.half = half;
-        for (const Op& op : P.ops) {
+        P.expand = keep && !half_api;
+        if (check && !early) {
+            if (int rc = flip_answer(ctx, s, &P.half)) return rc;
+            HIP_TRY(reserve(P.half ? n - 1 : n));
+        }
+        for (size_t q = 0; q < P.ops.size(); ++q) {
+            const Op& op = P.ops[q];
+            if (early && q == 1)
+                if (int rc = flip_answer(ctx, s, &P.half)) return rc;
             SweepArgs a;
             sweep_args(P, op, psi, cost_dev, (const float2*)ctx->luts.ptr, (double*)ctx->partials.ptr, &a);
             HIP_TRY(timed(ctx, op_profile_kind(op), op_bytes(P, op), s,
                           [&] { return qnae::launch_sweep(TB, cost_dtype, op.kind, a, s); }));
         }
+        half = P.half;
+        const int64_t blocks = 1ll << ((half ? n - 1 : n) - TB);
         // a symmetric state equals its all-qubit flip: nothing to undo when half
         if (keep && !half && p > 0 && P.flips_before[p])
             HIP_TRY(timed(ctx, K_FINAL, 16.0 * std::ldexp(1.0, n), s,
                           [&] { return qnae::launch_reverse(psi, 1ull << n, s); }));
         HIP_TRY(timed(ctx, K_REDUCE, 24.0 * blocks, s, [&] {
-            return qnae::launch_final_reduce((const double*)ctx->partials.ptr, blocks, out_dev, s);
+            return qnae::launch_final_reduce((const double*)ctx->partials.ptr, blocks, sums, s);
         }));
     }
-    HIP_TRY(hipMemcpyAsync(ctx->h_small.ptr, out_dev, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipEventRecord(ctx->staging_done, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const double* r = (const double*)ctx->h_small.ptr;
-    out->p_success = r[0] * readout_scale;
-    out->expected_cost = r[1] * readout_scale;
-    out->norm = r[2] * readout_scale;
+    const double readout_scale = std::norm(final_scale) * (half ? 2.0 : 1.0);
+    out->p_success = sums[0] * readout_scale;
+    out->expected_cost = sums[1] * readout_scale;
+    out->norm = sums[2] * readout_scale;
     return QNAE_OK;
 }
 

@@ -248,7 +248,7 @@ void HostBuf::release() {
 const char* Profiler::name(int k) {
     static const char* names[K_KINDS] = {"cost", "sweep_first", "sweep_middle", "sweep_boundary", "sweep_final",
                                          "resident", "final_reduce", "batch_cost", "batch_resident", "batch_sweep",
-                                         "batch_reduce", "adjoint"};
+                                         "batch_reduce", "adjoint", "prologue"};
     return names[k];
 }
 
@@ -263,10 +263,11 @@ hipEvent_t Profiler::get() {
     return e;
 }
 
-int enter(qnae_ctx* ctx) {
+int enter(qnae_ctx* ctx, hipStream_t s) {
     if (!ctx) return fail(QNAE_EINVAL, "null context");
     HIP_TRY(hipSetDevice(ctx->device));
     HIP_TRY(hipEventSynchronize(ctx->staging_done));
+    HIP_TRY(hipStreamWaitEvent(s, ctx->cost_staging_done, 0));
     return QNAE_OK;
 }
 
@@ -521,7 +522,7 @@ void plan_sweeps(SweepPlan& P, int n, int m, int p, int dtype, int TB, int cmin,
 void sweep_args(const SweepPlan& P, const Op& op, float2* psi, const void* cost, const float2* luts, double* partials,
                 qnae::SweepArgs* a) {
     const Group& g = P.groups[op.group];
-    const PlanRef ref{P.n, P.p, P.TB, P.lut_len, P.keep, P.half, P.forms.data(), P.flips_before.data(), P.final_scale};
+    const PlanRef ref{P.n, P.p, P.TB, P.lut_len, P.keep, P.half, P.expand, P.forms.data(), P.flips_before.data(), P.final_scale};
     sweep_args_for(ref, g.pos.data(), g.mask, op, psi, cost, luts, partials, a);
 }
 
@@ -547,6 +548,7 @@ void sweep_args_for(const PlanRef& P, const int* pos, uint32_t mask, const Op& o
     a->store = P.keep ? 1 : 0;
     a->half = 0;
     a->vbit = -1;
+    a->expand = P.half && P.keep && P.expand ? 1 : 0;
     a->mir = 0;
     if (P.half) {
         // Stored indices are x < 2^(n-1); full index x with bit n-1 set lives
@@ -583,7 +585,7 @@ void sweep_args_angles(const PlanRef& P, const Op& op, qnae::SweepArgs* a) {
 }
 
 void sweep_args_angles(const SweepPlan& P, const Op& op, qnae::SweepArgs* a) {
-    const PlanRef ref{P.n, P.p, P.TB, P.lut_len, P.keep, P.half, P.forms.data(), P.flips_before.data(), P.final_scale};
+    const PlanRef ref{P.n, P.p, P.TB, P.lut_len, P.keep, P.half, P.expand, P.forms.data(), P.flips_before.data(), P.final_scale};
     sweep_args_angles(ref, op, a);
 }
 
@@ -594,7 +596,7 @@ double op_bytes(const SweepPlan& P, const Op& op) {
         case qnae::SK_FIRST: per_amp = 8.0 + cb; break;
         case qnae::SK_MIDDLE: per_amp = 16.0; break;
         case qnae::SK_BOUNDARY: per_amp = 16.0 + cb; break;
-        case qnae::SK_FINAL: per_amp = 8.0 + cb + (P.keep ? 8.0 : 0.0); break;
+        case qnae::SK_FINAL: per_amp = 8.0 + cb + (P.keep ? P.expand ? 16.0 : 8.0 : 0.0); break;
         default: per_amp = cb + (P.keep ? 8.0 : 0.0);
     }
     return per_amp * std::ldexp(1.0, P.half ? P.n - 1 : P.n);

@@ -22,7 +22,7 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
     for (int q = 0; q < count; ++q)
         if (!(uniforms[q] >= 0.0 && uniforms[q] < 1.0))
             return fail(QNAE_EINVAL, "uniforms[%d]=%g outside [0, 1)", q, uniforms[q]);
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
     const size_t T = (((size_t)1 << n) + (1u << qnae::kSampleTileBits) - 1) >> qnae::kSampleTileBits;
     Blob B;

@@ -252,7 +252,7 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     if (round_bytes > 0) rounds = std::min(rounds, std::max<size_t>(1, (size_t)(tick_bytes / round_bytes)));
     struct Launch {
         int kind, dtype;
-        bool half;
+        bool virt;
         int tb;
         std::vector<Request*> members;
         size_t args_at, first_at;
@@ -263,10 +263,10 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     for (Request* r : large) {
         for (size_t k = 0; k < rounds && r->next_op + k < r->plan.ops.size(); ++k) {
             const Op& op = r->plan.ops[r->next_op + k];
-            Launch& L = sweeps[k][std::make_tuple(op.kind, r->dtype, r->half, r->shape.tile_bits)];
+            Launch& L = sweeps[k][std::make_tuple(op.kind, r->dtype, op_virtual(r->plan, op), r->shape.tile_bits)];
             L.kind = op.kind;
             L.dtype = r->dtype;
-            L.half = r->half;
+            L.virt = op_virtual(r->plan, op);
             L.tb = r->shape.tile_bits;
             L.members.push_back(r);
         }
@@ -386,7 +386,7 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
             const Launch& L = kv.second;
             HIP_TRY(qnae::launch_sweep_batch(L.tb, L.dtype, L.kind, (const SweepArgs*)(d + L.args_at),
                                              (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, s,
-                                             L.half));
+                                             L.virt));
             ++launches;
         }
     if (!finishing.empty()) {

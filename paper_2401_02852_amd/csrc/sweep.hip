@@ -30,11 +30,6 @@ namespace {
 
 using namespace tile;
 
-// Global index of tile element e = (thread part te) | (slot part se) in a
-// half-state sweep with a virtual bit: the unit tile bits deposit additively
-// (fwd = base + unit bits of te), and when the virtual bit of e is set the
-// index is mirrored, mir - (fwd + unit bits of se). HALF = false: plain
-// additive addresses.
 // Every sweep streams the state through nontemporal loads and stores: each
 // amplitude is touched once per sweep, and keeping it out of the caches'
 // normal replacement measured faster in every kind (with the current qubit
@@ -55,17 +50,11 @@ __device__ __forceinline__ void st_state(float2* p, float2 q) {
     __builtin_nontemporal_store(v, (f2v*)p);
 }
 
-struct HalfAddr {
-    uint64_t fwd, mir;
-    bool tp;  // virtual bit in the thread part
-};
-
 // Waves per SIMD a sweep kernel is register-allocated for. The final kind's
 // plane transposes leave LDS room for 4 workgroups per CU; capping its
 // registers at 3 waves per SIMD keeps most of that (the other kinds fit
 // their LDS-bound occupancy without a cap).
-constexpr int sweep_waves(int tb, int kind, bool half) {
-    if (half) return 1;
+constexpr int sweep_waves(int tb, int kind) {
     if (tb == 14) return kind == SK_BOUNDARY || kind == SK_FINAL ? 4 : 1;
     return kind == SK_FINAL ? 3 : 1;
 }
@@ -74,15 +63,15 @@ constexpr int sweep_waves(int tb, int kind, bool half) {
 // (PLANES) one component plane after the other in half the LDS. CROSS: the
 // layouts differ in the wave index (workgroup barriers); otherwise each wave
 // stays inside its own quarter of the tile.
-template <int TB, bool PLANES, int A, int B, bool CROSS>
+template <int TB, bool PLANES, int A, int B, bool CROSS, bool VIRT>
 __device__ __forceinline__ void move(float* lds, float2 (&v)[32], uint32_t lane, uint32_t wave) {
     if constexpr (PLANES) {
-        relayout<TB, A, B, CROSS>(lds, v, lane, wave);
+        relayout<TB, A, B, CROSS, VIRT>(lds, v, lane, wave);
     } else {
-        to_lds<TB, A>((float2*)lds, v, lane, wave);
+        to_lds<TB, A, VIRT>((float2*)lds, v, lane, wave);
         if (CROSS) __syncthreads();
         else wave_lds_sync();
-        from_lds<TB, B>((const float2*)lds, v, lane, wave);
+        from_lds<TB, B, VIRT>((const float2*)lds, v, lane, wave);
     }
 }
 
@@ -93,7 +82,11 @@ __device__ __forceinline__ void move(float* lds, float2 (&v)[32], uint32_t lane,
 // register demand (with 14-bit tiles at four waves per SIMD the boundary
 // kind spilled 21 instead of 3 dwords per lane, the final kind 15 instead of
 // none).
-template <int TB, typename CT, int KIND, bool HALF, bool CKPT = false, int L1M = 0>
+// VIRT: a half-state sweep whose group mixes bit n-1, which is the tile's top
+// bit (a group's bits ascend); the elements with it set are stored at mir - y
+// for the index y of their other bits. Half-state sweeps of other groups are
+// whole-state sweeps over n-1 bits.
+template <int TB, typename CT, int KIND, bool VIRT, bool CKPT = false, int L1M = 0>
 __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, double* partial) {
     constexpr int WB = TB - 11;
     constexpr int NT = 64 << WB;
@@ -105,9 +98,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
     // Kinds that move state one way (only stored, or only read for the
     // readout) gain from more resident workgroups: their transposes go
     // through LDS one component plane at a time.
-    // (Half-state final sweeps need too many registers for that to pay.)
-    constexpr bool PLANES = KIND == SK_FIRST || (KIND == SK_FINAL && !HALF) ||
-                            (TB == 14 && !HALF && (KIND == SK_MIDDLE || KIND == SK_BOUNDARY));
+    constexpr bool PLANES = KIND == SK_FIRST || KIND == SK_FINAL ||
+                            (TB == 14 && (KIND == SK_MIDDLE || KIND == SK_BOUNDARY));
     // Straight-line butterflies in the kinds that mix the tile once and hold
     // no readout state: measured faster there (the boundary kind measured
     // slower, and the final kind needs the registers). With 14-bit tiles the
@@ -115,11 +107,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
     // (21 and 15 dwords instead of 38 and 36): n = 33 590 -> 561 ms, n = 24
     // 0.96 -> 0.85 ms per 10-layer run.
     constexpr bool UNCOND = KIND == SK_FIRST || KIND == SK_MIDDLE ||
-                            (TB == 14 && !HALF && (KIND == SK_BOUNDARY || KIND == SK_FINAL));
-    // The first sweep (no cost flip) of a group without the virtual bit reads
-    // its costs in layout L0 and mixes L0, L1, L2 in that order (see below).
-    // Decided the same way in half and full kernels, whose addressing agrees
-    // for such groups, so both give the same rounding.
+                            (TB == 14 && (KIND == SK_BOUNDARY || KIND == SK_FINAL));
     constexpr bool NEED_COST = INIT || PHASE || REDUCE;
     constexpr bool NEED_LUT = INIT || PHASE;
     constexpr bool LUT_LDS = sizeof(CT) == 1;
@@ -130,26 +118,24 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
     __shared__ float2 lut_s[NEED_LUT && LUT_LDS ? 256 : 1];
     __shared__ double red[3][1 << WB];
 
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u;
+    // (uniform: a mirrored wave's place is a scalar choice)
+    const uint32_t wave = VIRT ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : threadIdx.x >> 6;
     const uint32_t ntiles = 1u << a.nw;
     // Tile bit i sits at bit pos[i] of x; the tile index fills the other
     // bits (wmask, ascending). Both maps are bit deposits, so offsets are
     // additive (XOR-linear) over disjoint bit sets of e: an address splits
     // into a per-thread offset and a per-slot offset that is the same for
     // every lane (scalar registers).
-    // Half sweeps: the virtual bit contributes no unit offset (bitval 0); it
-    // selects the mirrored address instead.
-    // (a half sweep whose group lacks bit n-1 has vbit < 0: plain addresses)
-    const bool has_v = HALF && a.vbit >= 0;
-    const bool first_l0 = KIND == SK_FIRST && !has_v;
-    const uint32_t vb = has_v ? (uint32_t)a.vbit : 0u;
+    // VIRT: the top tile bit contributes no offset.
+    constexpr uint32_t kTop = 1u << (TB - 1);
     uint64_t bitval[TB];
 #pragma unroll
-    for (int i = 0; i < TB; ++i) bitval[i] = (has_v && (uint32_t)i == vb) ? 0ull : 1ull << a.pos[i];
+    for (int i = 0; i < TB; ++i) bitval[i] = 1ull << a.pos[i];
     auto scat = [&](uint32_t e) -> uint64_t {
         uint64_t x = 0;
 #pragma unroll
-        for (int i = 0; i < TB; ++i)
+        for (int i = 0; i < (VIRT ? TB - 1 : TB); ++i)
             if ((e >> i) & 1u) x |= bitval[i];
         return x;
     };
@@ -171,39 +157,38 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         if (w & 1ull) base |= m & (~m + 1ull);
         w >>= 1;
     }
-    auto vpar = [&](uint32_t e) -> bool { return has_v && ((e >> vb) & 1u); };
-    auto haddr = [&](uint32_t te) -> HalfAddr {
-        HalfAddr h;
-        h.fwd = base + scat(te);
-        h.mir = a.mir - h.fwd;
-        h.tp = vpar(te);
-        return h;
-    };
-    // index of element (te | se) for a thread's HalfAddr
-    auto hidx = [&](const HalfAddr& h, uint32_t se) -> uint64_t {
-        const uint64_t so = scat(se);
-        return (h.tp != vpar(se)) ? h.mir - so : h.fwd + so;
-    };
+    // Layout L0 holds the top tile bit in the wave index: a mirrored wave's
+    // elements, in storage order, start where the tile's mirror image does.
+    const uint64_t base0 = VIRT && (wave >> (WB - 1)) != 0u ? a.mir - base - a.tile_bits : base;
 
     // Cost values of the 32 amplitudes in layout L2, loaded first; packed 4
     // (uint8) or 2 (uint16) per register. With cflip the stored state is the
     // true one with every qubit flipped (see MixForm), so cost values are read
     // at the complemented index: complemented tile base, thread part and slot.
     uint32_t cvp[NC];
-    if (NEED_COST && HALF && !first_l0) {
-        // symmetric cost: no complemented reads, mirrored indices instead
-        const HalfAddr h = haddr(L::t2(lane, wave));
-        const CT* const cp = (const CT*)a.cost;
+    if (NEED_COST && VIRT && KIND != SK_FIRST) {
+        // symmetric cost: no complemented reads, mirrored places instead
+        const uint64_t fwd = base + scat(L::t2(lane, wave));
+        const CT* const cf = (const CT*)a.cost + fwd;
+        const CT* const cv = (const CT*)a.cost + (a.mir - fwd);
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             uint32_t wv = 0u;
 #pragma unroll
-            for (int q = 0; q < PK; ++q) wv |= (uint32_t)cp[hidx(h, L::s2(PK * i + q))] << (8 * sizeof(CT) * q);
+            for (int q = 0; q < PK; ++q) {
+                const uint32_t se = L::s2(PK * i + q);
+                const int64_t so = (int64_t)scat(se);
+                wv |= (uint32_t)((se & kTop) ? cv[-so] : cf[so]) << (8 * sizeof(CT) * q);
+            }
             cvp[i] = wv;
+        }
+        if constexpr (TB == 14) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) asm volatile("" : "+v"(cvp[i]));
         }
         if (NEED_LUT && LUT_LDS)
             for (int i = threadIdx.x; i < a.lut_len; i += NT) lut_s[i] = a.lut[i];
-    } else if (NEED_COST && !first_l0) {
+    } else if (NEED_COST && KIND != SK_FIRST) {
         const bool cf = a.cflip != 0;
         const uint64_t cbase = cf ? base ^ ((((uint64_t)1 << a.n) - 1ull) ^ a.tile_bits) : base;
         const uint32_t ct = cf ? L::t2(lane, wave) ^ L::t2(63u, (1u << WB) - 1u) : L::t2(lane, wave);
@@ -235,15 +220,27 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         return (cvp[j / PK] >> (8 * sizeof(CT) * (j % PK))) & (sizeof(CT) == 1 ? 0xffu : 0xffffu);
     };
 
-    if (KIND == SK_FIRST && first_l0) {
+    // The tile from layout L2 to the state.
+    auto store2 = [&](const float2(&x)[32]) {
+        const uint64_t fwd = base + scat(L::t2(lane, wave));
+        float2* const pf = a.psi + fwd;
+        float2* const pv = VIRT ? a.psi + (a.mir - fwd) : pf;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const uint32_t se = L::s2(j);
+            const uint64_t so = scat(se);
+            st_state(VIRT && (se & kTop) ? pv - so : pf + so, x[j]);
+        }
+    };
+    if (KIND == SK_FIRST) {
         // In layout L0 the pair of a thread's slots along tile bit 0 are
         // adjacent costs, and the 64 lanes cover tile bits 1..6, so a wave
         // reads 128 consecutive cost bytes per load (layout L2 reads four
         // runs of 16). The tile is then mixed in L0, L1, L2 and stored from
         // L2; the order of the mixings within a layer does not matter.
         using PT = typename std::conditional<sizeof(CT) == 1, uint16_t, uint32_t>::type;
-        const CT* const c0 = (const CT*)a.cost + base + scat(L::t0(lane, wave));
         PT cp[16];
+        const CT* const c0 = (const CT*)a.cost + base0 + scat(L::t0(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) cp[jj] = *(const PT*)(c0 + scat(L::s0(2 * jj)));
         if (LUT_LDS)
@@ -260,17 +257,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         const float tt = a.post_t;
         mix32<UNCOND>(v, L::sm0(m), tt);
         if (L1M == 1 || (L1M == 0 && L::sm1(m))) {
-            move<TB, PLANES, 0, 1, false>(lds, v, lane, wave);  // inside the wave's quarter
+            move<TB, PLANES, 0, 1, false, VIRT>(lds, v, lane, wave);  // inside the wave's quarter
             mix32<UNCOND>(v, L::sm1(m), tt);
             wave_lds_sync();
-            move<TB, PLANES, 1, 2, true>(lds, v, lane, wave);
+            move<TB, PLANES, 1, 2, true, VIRT>(lds, v, lane, wave);
         } else {
-            move<TB, PLANES, 0, 2, true>(lds, v, lane, wave);
+            move<TB, PLANES, 0, 2, true, VIRT>(lds, v, lane, wave);
         }
         mix32<UNCOND>(v, L::sm2(m), tt);
-        float2* const p2 = a.psi + base + scat(L::t2(lane, wave));
-#pragma unroll
-        for (int j = 0; j < 32; ++j) st_state(p2 + scat(L::s2(j)), v[j]);
+        store2(v);
         return;
     }
 
@@ -279,21 +274,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         __syncthreads();  // phase table visible
 #pragma unroll
         for (int j = 0; j < 32; ++j) v[j] = lut(cval(j));
-    } else if (HALF) {
-        // pairs along tile bit 0 (x bit 0): a mirrored pair is stored in
-        // reverse order one slot lower
-        const HalfAddr h = haddr(L::t0(lane, wave));
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const uint32_t se = L::s0(2 * jj);
-            const bool neg = h.tp != vpar(se);
-            const uint64_t so = scat(se);
-            const float4 q = ld_state(a.psi_in + (neg ? h.mir - so - 1ull : h.fwd + so));
-            v[2 * jj] = neg ? make_float2(q.z, q.w) : make_float2(q.x, q.y);
-            v[2 * jj + 1] = neg ? make_float2(q.x, q.y) : make_float2(q.z, q.w);
-        }
     } else {
-        const float2* const p0 = a.psi_in + base + scat(L::t0(lane, wave));
+        const float2* const p0 = a.psi_in + base0 + scat(L::t0(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
             const float4 q = ld_state(p0 + scat(L::s0(2 * jj)));
@@ -306,12 +288,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         const float tt = a.pre_t;
         mix32<UNCOND>(v, L::sm0(m), tt);
         if (L1M == 1 || (L1M == 0 && L::sm1(m))) {
-            move<TB, PLANES, 0, 1, false>(lds, v, lane, wave);  // inside the wave's quarter
+            move<TB, PLANES, 0, 1, false, VIRT>(lds, v, lane, wave);  // inside the wave's quarter
             mix32<UNCOND>(v, L::sm1(m), tt);
             wave_lds_sync();
-            move<TB, PLANES, 1, 2, true>(lds, v, lane, wave);
+            move<TB, PLANES, 1, 2, true, VIRT>(lds, v, lane, wave);
         } else {
-            move<TB, PLANES, 0, 2, true>(lds, v, lane, wave);
+            move<TB, PLANES, 0, 2, true, VIRT>(lds, v, lane, wave);
         }
         mix32<UNCOND>(v, L::sm2(m), tt);
     }
@@ -321,7 +303,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         const uint64_t all = (1ull << a.n) - 1ull;
         const uint64_t o2 = base + scat(L::t2(lane, wave));
         const float2 f = a.ckpt_scale;
-        if (a.cflip) {
+        if (VIRT) {
+#pragma unroll
+            for (int j = 0; j < 32; ++j) {
+                const uint32_t se = L::s2(j);
+                const uint64_t so = scat(se);
+                st_state((se & kTop) ? a.ckpt + (a.mir - o2) - so : a.ckpt + o2 + so, cmul(v[j], f));
+            }
+        } else if (a.cflip) {
             float2* const c2 = a.ckpt + (o2 ^ all);
 #pragma unroll
             for (int j = 0; j < 32; ++j) st_state(c2 - scat(L::s2(j)), cmul(v[j], f));
@@ -341,43 +330,44 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         mix32<UNCOND>(v, L::sm2(m), tt);
         if (PRE) __syncthreads();  // every wave has read its L2 part
         if (L1M == 1 || (L1M == 0 && L::sm1(m))) {
-            move<TB, PLANES, 2, 1, true>(lds, v, lane, wave);
+            move<TB, PLANES, 2, 1, true, VIRT>(lds, v, lane, wave);
             mix32<UNCOND>(v, L::sm1(m), tt);
             wave_lds_sync();
-            move<TB, PLANES, 1, 0, false>(lds, v, lane, wave);  // inside the wave's quarter
+            move<TB, PLANES, 1, 0, false, VIRT>(lds, v, lane, wave);  // inside the wave's quarter
         } else {
-            move<TB, PLANES, 2, 0, true>(lds, v, lane, wave);
+            move<TB, PLANES, 2, 0, true, VIRT>(lds, v, lane, wave);
         }
         mix32<UNCOND>(v, L::sm0(m), tt);
-        if (HALF) {
-            const HalfAddr h = haddr(L::t0(lane, wave));
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) {
-                const uint32_t se = L::s0(2 * jj);
-                const bool neg = h.tp != vpar(se);
-                const uint64_t so = scat(se);
-                const float2 lo = neg ? v[2 * jj + 1] : v[2 * jj], hi = neg ? v[2 * jj] : v[2 * jj + 1];
-                st_state(a.psi + (neg ? h.mir - so - 1ull : h.fwd + so), make_float4(lo.x, lo.y, hi.x, hi.y));
-            }
-            return;
-        }
-        float2* const p0 = a.psi + base + scat(L::t0(lane, wave));
+        float2* const p0 = a.psi + base0 + scat(L::t0(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj)
             st_state(p0 + scat(L::s0(2 * jj)), make_float4(v[2 * jj].x, v[2 * jj].y, v[2 * jj + 1].x, v[2 * jj + 1].y));
         return;
     }
     if (REDUCE) {
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+        // Balanced trees over the slot bits, so a thread's sums do not depend
+        // on the order of its slots: a tile and its mirror image sum alike,
+        // and a run on the half state and one on the whole of a symmetric
+        // state agree to the rounding of the FP64 sums that follow.
+        float t0[6], t1[6], t2[6];
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
             const float pr = fmaf(v[j].x, v[j].x, v[j].y * v[j].y);
             const uint32_t c = cval(j);
-            s2 += pr;
-            s1 = fmaf((float)c, pr, s1);
-            s0 += c == 0u ? pr : 0.f;
+            float x0 = c == 0u ? pr : 0.f, x1 = (float)c * pr, x2 = pr;
+            asm("" : "+v"(x1));  // a product of its own
+            int k = 0;
+#pragma unroll
+            for (; k < 5 && ((j >> k) & 1); ++k) {
+                x0 += t0[k];
+                x1 += t1[k];
+                x2 += t2[k];
+            }
+            t0[k] = x0;
+            t1[k] = x1;
+            t2[k] = x2;
         }
-        double d0 = s0, d1 = s1, d2 = s2;
+        double d0 = t0[5], d1 = t1[5], d2 = t2[5];
         for (int off = 32; off > 0; off >>= 1) {
             d0 += __shfl_xor(d0, off);
             d1 += __shfl_xor(d1, off);
@@ -400,23 +390,29 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
 #pragma unroll
             for (int j = 0; j < 32; ++j) v[j] = cmul(v[j], a.store_scale);
         }
-        if (HALF) {
-            const HalfAddr h = haddr(L::t2(lane, wave));
+        store2(v);
+        // Whole-state output of a half-state run: the upper half mirrors the
+        // lower one.
+        if (KIND == SK_FINAL && a.expand) {
+            const uint64_t all = (1ull << a.n) - 1ull;
+            const uint64_t fwd = base + scat(L::t2(lane, wave));
+            float2* const pf = a.psi + (all - fwd);
+            float2* const pv = VIRT ? a.psi + (all - a.mir + fwd) : pf;
 #pragma unroll
-            for (int j = 0; j < 32; ++j) st_state(a.psi + hidx(h, L::s2(j)), v[j]);
-        } else {
-            float2* const p2 = a.psi + base + scat(L::t2(lane, wave));
-#pragma unroll
-            for (int j = 0; j < 32; ++j) st_state(p2 + scat(L::s2(j)), v[j]);
+            for (int j = 0; j < 32; ++j) {
+                const uint32_t se = L::s2(j);
+                const uint64_t so = scat(se);
+                st_state(VIRT && (se & kTop) ? pv + so : pf - so, v[j]);
+            }
         }
     }
 }
 
 // One sweep over one state: block b handles tile b.
-template <int TB, typename CT, int KIND, bool HALF = false, bool CKPT = false, int L1M = 0>
-__global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu(sweep_waves(TB, KIND, HALF)))) void sweep_kernel(
+template <int TB, typename CT, int KIND, bool VIRT = false, bool CKPT = false, int L1M = 0>
+__global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu(sweep_waves(TB, KIND)))) void sweep_kernel(
     const SweepArgs a) {
-    sweep_tile<TB, CT, KIND, HALF, CKPT, L1M>(a, blockIdx.x, a.partials + 3 * (size_t)blockIdx.x);
+    sweep_tile<TB, CT, KIND, VIRT, CKPT, L1M>(a, blockIdx.x, a.partials + 3 * (size_t)blockIdx.x);
 }
 
 // L1M of a single-state launch: 1 when a mask the kind mixes has bits that
@@ -443,13 +439,13 @@ __device__ __forceinline__ int batch_item(const uint32_t* first, int count, uint
 
 // One sweep step over many states at once (ragged): instance i owns blocks
 // first[i] .. first[i+1]-1, one per tile, with its own arguments.
-template <int TB, typename CT, int KIND, bool HALF>
-__global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu(sweep_waves(TB, KIND, HALF)))) void sweep_batch_kernel(const SweepArgs* args, const uint32_t* first,
+template <int TB, typename CT, int KIND, bool VIRT>
+__global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu(sweep_waves(TB, KIND)))) void sweep_batch_kernel(const SweepArgs* args, const uint32_t* first,
                                                                       int count) {
     const int i = batch_item(first, count, blockIdx.x);
     const SweepArgs a = args[i];
     const uint32_t t = blockIdx.x - first[i];
-    sweep_tile<TB, CT, KIND, HALF>(a, t, a.partials + 3 * (size_t)t);
+    sweep_tile<TB, CT, KIND, VIRT>(a, t, a.partials + 3 * (size_t)t);
 }
 
 // psi[x] <-> psi[N - 1 - x]: undoes an X on every qubit (N >= 4).
@@ -630,6 +626,11 @@ __global__ __launch_bounds__(1024) void final_reduce_kernel(const double* partia
     final_reduce_body(partials, blocks, out);
 }
 
+// One workgroup per row of `blocks` triples.
+__global__ __launch_bounds__(1024) void final_reduce_rows_kernel(const double* partials, int64_t blocks, double* out) {
+    final_reduce_body(partials + 3 * blocks * blockIdx.x, blocks, out + 3 * (size_t)blockIdx.x);
+}
+
 // One workgroup per instance i: blocks[i] triples at partials[i] -> outs[i].
 __global__ __launch_bounds__(1024) void final_reduce_batch_kernel(const double* const* partials, const uint32_t* blocks,
                                                                    double* const* outs) {
@@ -660,9 +661,9 @@ hipError_t launch_kind(const SweepArgs& a, hipStream_t s) {
 }
 
 template <int TB, typename CT, int KIND>
-hipError_t launch_batch_kind(const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool half,
+hipError_t launch_batch_kind(const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool virt,
                              hipStream_t s) {
-    if (half)
+    if (virt)
         hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, KIND, true>), dim3(blocks), dim3(64 << (TB - 11)), 0, s, args,
                            first, count);
     else
@@ -685,13 +686,13 @@ hipError_t launch_tb(int kind, const SweepArgs& a, hipStream_t s) {
 
 template <int TB, typename CT>
 hipError_t launch_batch_ct(int kind, const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks,
-                           bool half, hipStream_t s) {
+                           bool virt, hipStream_t s) {
     switch (kind) {
-        case SK_FIRST: return launch_batch_kind<TB, CT, SK_FIRST>(args, first, count, blocks, half, s);
-        case SK_MIDDLE: return launch_batch_kind<TB, CT, SK_MIDDLE>(args, first, count, blocks, half, s);
-        case SK_BOUNDARY: return launch_batch_kind<TB, CT, SK_BOUNDARY>(args, first, count, blocks, half, s);
-        case SK_FINAL: return launch_batch_kind<TB, CT, SK_FINAL>(args, first, count, blocks, half, s);
-        case SK_P0: return launch_batch_kind<TB, CT, SK_P0>(args, first, count, blocks, half, s);
+        case SK_FIRST: return launch_batch_kind<TB, CT, SK_FIRST>(args, first, count, blocks, virt, s);
+        case SK_MIDDLE: return launch_batch_kind<TB, CT, SK_MIDDLE>(args, first, count, blocks, virt, s);
+        case SK_BOUNDARY: return launch_batch_kind<TB, CT, SK_BOUNDARY>(args, first, count, blocks, virt, s);
+        case SK_FINAL: return launch_batch_kind<TB, CT, SK_FINAL>(args, first, count, blocks, virt, s);
+        case SK_P0: return launch_batch_kind<TB, CT, SK_P0>(args, first, count, blocks, virt, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -714,34 +715,39 @@ hipError_t launch_sweep(int tb, int dtype, int kind, const SweepArgs& a, hipStre
 
 template <int TB>
 hipError_t launch_batch_tb(int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                           uint32_t blocks, hipStream_t s, bool half) {
-    return dtype == 1 ? launch_batch_ct<TB, uint8_t>(kind, args, first, count, blocks, half, s)
-                      : launch_batch_ct<TB, uint16_t>(kind, args, first, count, blocks, half, s);
+                           uint32_t blocks, hipStream_t s, bool virt) {
+    return dtype == 1 ? launch_batch_ct<TB, uint8_t>(kind, args, first, count, blocks, virt, s)
+                      : launch_batch_ct<TB, uint16_t>(kind, args, first, count, blocks, virt, s);
 }
 
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool half) {
+                              uint32_t blocks, hipStream_t s, bool virt) {
     switch (tb) {
-        case 12: return launch_batch_tb<12>(dtype, kind, args, first, count, blocks, s, half);
-        case 13: return launch_batch_tb<13>(dtype, kind, args, first, count, blocks, s, half);
-        case 14: return launch_batch_tb<14>(dtype, kind, args, first, count, blocks, s, half);
+        case 12: return launch_batch_tb<12>(dtype, kind, args, first, count, blocks, s, virt);
+        case 13: return launch_batch_tb<13>(dtype, kind, args, first, count, blocks, s, virt);
+        case 14: return launch_batch_tb<14>(dtype, kind, args, first, count, blocks, s, virt);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s) {
+template <typename CT>
+hipError_t launch_ckpt_ct(const SweepArgs& a, hipStream_t s) {
     constexpr int TB = kAdjointTileBits;
-    if (a.half || !a.ckpt || a.nw < 0) return hipErrorInvalidValue;
     const dim3 grid(1u << a.nw), block(64 << (TB - 11));
     const bool l1 = sweep_l1_mode<TB, SK_BOUNDARY>(a) == 1;
-    if (dtype == 1) {
-        if (l1) hipLaunchKernelGGL((sweep_kernel<TB, uint8_t, SK_BOUNDARY, false, true, 1>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((sweep_kernel<TB, uint8_t, SK_BOUNDARY, false, true, 2>), grid, block, 0, s, a);
+    if (a.half && a.vbit >= 0) {
+        if (l1) hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, true, true, 1>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, true, true, 2>), grid, block, 0, s, a);
     } else {
-        if (l1) hipLaunchKernelGGL((sweep_kernel<TB, uint16_t, SK_BOUNDARY, false, true, 1>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((sweep_kernel<TB, uint16_t, SK_BOUNDARY, false, true, 2>), grid, block, 0, s, a);
+        if (l1) hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, false, true, 1>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, false, true, 2>), grid, block, 0, s, a);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s) {
+    if (!a.ckpt || a.nw < 0) return hipErrorInvalidValue;
+    return dtype == 1 ? launch_ckpt_ct<uint8_t>(a, s) : launch_ckpt_ct<uint16_t>(a, s);
 }
 
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s) {
@@ -778,6 +784,11 @@ hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count,
 
 hipError_t launch_final_reduce(const double* partials, int64_t blocks, double* out, hipStream_t s) {
     hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(1024), 0, s, partials, blocks, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, double* out, int count, hipStream_t s) {
+    hipLaunchKernelGGL(final_reduce_rows_kernel, dim3((uint32_t)count), dim3(1024), 0, s, partials, blocks, out);
     return hipGetLastError();
 }
 

@@ -143,7 +143,23 @@ __device__ __forceinline__ constexpr uint32_t phys(uint32_t e) { return e + 2u *
 template <int TB>
 constexpr uint32_t lds_elems() { return phys((1u << TB) - 1u) + 1u; }
 
-template <int TB, int LAYOUT>
+// VIRT tiles (half states): the elements with the top tile bit set are the
+// mirrored ones. In memory, registers and LDS they keep their storage order,
+// in which such an element's other tile bits read complemented; a butterfly on
+// any other bit pairs the same elements either way. Only layout L2, which mixes
+// the top bit and holds it in a slot, takes them by their true position:
+// slots with the bit set address the complemented place, again a per-thread
+// base plus a constant per slot.
+template <int TB>
+struct VirtL2 {
+    static constexpr uint32_t top = 1u << (TB - 1);
+    static constexpr uint32_t slots = Lay<TB>::s2(31) & ~top;                      // slot bits but the top one
+    static constexpr uint32_t threads = ((1u << TB) - 1u) & ~Lay<TB>::s2(31);  // lane and wave bits
+    __device__ static __forceinline__ uint32_t thread_part(uint32_t t2) { return top | (threads ^ t2); }
+    __device__ static __forceinline__ constexpr uint32_t slot_part(uint32_t se) { return slots ^ (se & ~top); }
+};
+
+template <int TB, int LAYOUT, bool VIRT = false>
 __device__ __forceinline__ void to_lds(float2* lds, const float2 (&v)[32], uint32_t lane, uint32_t wave) {
     using L = Lay<TB>;
     if (LAYOUT == 0) {
@@ -156,13 +172,18 @@ __device__ __forceinline__ void to_lds(float2* lds, const float2 (&v)[32], uint3
 #pragma unroll
         for (int j = 0; j < 32; ++j) p[phys(L::s1(j))] = v[j];
     } else {
+        using V = VirtL2<TB>;
         float2* const p = lds + phys(L::t2(lane, wave));
+        float2* const pc = VIRT ? lds + phys(V::thread_part(L::t2(lane, wave))) : p;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) p[phys(L::s2(j))] = v[j];
+        for (int j = 0; j < 32; ++j) {
+            if (VIRT && (L::s2(j) & V::top)) pc[phys(V::slot_part(L::s2(j)))] = v[j];
+            else p[phys(L::s2(j))] = v[j];
+        }
     }
 }
 
-template <int TB, int LAYOUT>
+template <int TB, int LAYOUT, bool VIRT = false>
 __device__ __forceinline__ void from_lds(const float2* lds, float2 (&v)[32], uint32_t lane, uint32_t wave) {
     using L = Lay<TB>;
     if (LAYOUT == 0) {
@@ -178,9 +199,12 @@ __device__ __forceinline__ void from_lds(const float2* lds, float2 (&v)[32], uin
 #pragma unroll
         for (int j = 0; j < 32; ++j) v[j] = p[phys(L::s1(j))];
     } else {
+        using V = VirtL2<TB>;
         const float2* const p = lds + phys(L::t2(lane, wave));
+        const float2* const pc = VIRT ? lds + phys(V::thread_part(L::t2(lane, wave))) : p;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) v[j] = p[phys(L::s2(j))];
+        for (int j = 0; j < 32; ++j)
+            v[j] = VIRT && (L::s2(j) & V::top) ? pc[phys(V::slot_part(L::s2(j)))] : p[phys(L::s2(j))];
     }
 }
 
@@ -230,7 +254,7 @@ __device__ __forceinline__ void set_part(float2& a, float x) {
 }
 
 // Component C (0 real, 1 imaginary) of the tile in layout LAYOUT to LDS.
-template <int TB, int LAYOUT, int C>
+template <int TB, int LAYOUT, int C, bool VIRT = false>
 __device__ __forceinline__ void to_plane(float* lds, const float2 (&v)[32], uint32_t lane, uint32_t wave) {
     using L = Lay<TB>;
     if (LAYOUT == 0) {
@@ -242,13 +266,18 @@ __device__ __forceinline__ void to_plane(float* lds, const float2 (&v)[32], uint
 #pragma unroll
         for (int j = 0; j < 32; ++j) p[physf<TB>(L::s1(j))] = part<C>(v[j]);
     } else {
+        using V = VirtL2<TB>;
         float* const p = lds + physf<TB>(L::t2(lane, wave));
+        float* const pc = VIRT ? lds + physf<TB>(V::thread_part(L::t2(lane, wave))) : p;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) p[physf<TB>(L::s2(j))] = part<C>(v[j]);
+        for (int j = 0; j < 32; ++j) {
+            if (VIRT && (L::s2(j) & V::top)) pc[physf<TB>(V::slot_part(L::s2(j)))] = part<C>(v[j]);
+            else p[physf<TB>(L::s2(j))] = part<C>(v[j]);
+        }
     }
 }
 
-template <int TB, int LAYOUT, int C>
+template <int TB, int LAYOUT, int C, bool VIRT = false>
 __device__ __forceinline__ void from_plane(const float* lds, float2 (&v)[32], uint32_t lane, uint32_t wave) {
     using L = Lay<TB>;
     if (LAYOUT == 0) {
@@ -260,9 +289,13 @@ __device__ __forceinline__ void from_plane(const float* lds, float2 (&v)[32], ui
 #pragma unroll
         for (int j = 0; j < 32; ++j) set_part<C>(v[j], p[physf<TB>(L::s1(j))]);
     } else {
+        using V = VirtL2<TB>;
         const float* const p = lds + physf<TB>(L::t2(lane, wave));
+        const float* const pc = VIRT ? lds + physf<TB>(V::thread_part(L::t2(lane, wave))) : p;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) set_part<C>(v[j], p[physf<TB>(L::s2(j))]);
+        for (int j = 0; j < 32; ++j)
+            set_part<C>(v[j], VIRT && (L::s2(j) & V::top) ? pc[physf<TB>(V::slot_part(L::s2(j)))]
+                                                          : p[physf<TB>(L::s2(j))]);
     }
 }
 
@@ -270,18 +303,18 @@ __device__ __forceinline__ void from_plane(const float* lds, float2 (&v)[32], ui
 // layouts differ in the wave index, so waves exchange data (workgroup
 // barriers); otherwise each wave stays inside its own quarter. The caller
 // orders this against earlier LDS reads of the buffer by other waves.
-template <int TB, int A, int B, bool CROSS>
+template <int TB, int A, int B, bool CROSS, bool VIRT = false>
 __device__ __forceinline__ void relayout(float* lds, float2 (&v)[32], uint32_t lane, uint32_t wave) {
-    to_plane<TB, A, 0>(lds, v, lane, wave);
+    to_plane<TB, A, 0, VIRT>(lds, v, lane, wave);
     if (CROSS) __syncthreads();
     else wave_lds_sync();
-    from_plane<TB, B, 0>(lds, v, lane, wave);
+    from_plane<TB, B, 0, VIRT>(lds, v, lane, wave);
     if (CROSS) __syncthreads();
     else wave_lds_sync();
-    to_plane<TB, A, 1>(lds, v, lane, wave);
+    to_plane<TB, A, 1, VIRT>(lds, v, lane, wave);
     if (CROSS) __syncthreads();
     else wave_lds_sync();
-    from_plane<TB, B, 1>(lds, v, lane, wave);
+    from_plane<TB, B, 1, VIRT>(lds, v, lane, wave);
 }
 
 }  // namespace tile

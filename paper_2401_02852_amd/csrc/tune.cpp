@@ -86,7 +86,7 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
     if (int rc = check_tune_target(n, cost_dtype, 1)) return rc;
     if (reps < 1 || reps > 1000) return fail(QNAE_EINVAL, "reps=%d outside [1, 1000]", reps);
     if (!out) return fail(QNAE_EINVAL, "null output pointer");
-    if (int rc = enter(ctx)) return rc;
+    if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     *out = qnae_tune{0, 0, 0, 0, 0.0};
     if (n <= kResidentMaxN) return QNAE_OK;
     hipStream_t s = (hipStream_t)stream;
@@ -98,9 +98,8 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
     const int p = 4, p_lo = 2, m = 63, lut_len = m + 1;
     const double gammas[p] = {0.4, 0.7, 0.5, 0.3}, betas[p] = {0.3, 0.2, 0.25, 0.15};
     HIP_TRY(ctx->h_luts.reserve(sizeof(float2) * p * lut_len));
-    HIP_TRY(ctx->h_forms.reserve(sizeof(MixForm) * p));
     float2* tables = (float2*)ctx->h_luts.ptr;
-    MixForm* forms = (MixForm*)ctx->h_forms.ptr;
+    MixForm forms[p];
     const std::complex<double> final_scale = build_tables(n, m, gammas, betas, p, tables, forms);
     HIP_TRY(ctx->luts.reserve(sizeof(float2) * p * lut_len));
     HIP_TRY(hipMemcpyAsync(ctx->luts.ptr, tables, sizeof(float2) * p * lut_len, hipMemcpyHostToDevice, s));

@@ -53,19 +53,21 @@ def short_name(name: str) -> str:
     name = re.sub(r"qnae::\(anonymous namespace\)::", "", name)
     # (a sixth argument, whether the tiles pass through layout L1, is not
     # shown: both variants of a kind move the same bytes and are summed)
-    m = re.match(r"void sweep_kernel<(\d+), ([a-z ]+), (\d)(?:, (true|false))?(?:, (true|false))?(?:, \d)?>", name)
+    m = re.match(r"void sweep_kernel<(\d+), ([a-z ]+), (\d)(?:, (true|false|\d))?(?:, (true|false))?(?:, \d)?>", name)
     if m:
-        half = ",half" if m.group(4) == "true" else ""
+        half = ",half" if m.group(4) in ("true", "1") else ""
         ckpt = "_ckpt" if m.group(5) == "true" else ""
         return (f"sweep_kernel<TB={m.group(1)},{m.group(2).replace('unsigned ', 'u')}{half}> "
                 f"{KIND_NAMES[m.group(3)]}{ckpt}")
-    m = re.match(r"void adjoint_kernel<([a-z ]+), (\d)(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?>", name)
+    m = re.match(r"void adjoint_kernel<([a-z ]+), (\d)(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?>",
+                 name)
     if m:
         kind = {"0": "middle", "1": "boundary", "2": "end"}[m.group(2)]
         weigh = "_weigh" if m.group(3) == "true" else ""
         stream = ",stream" if m.group(4) == "true" else ""
         q1 = ",q1" if m.group(5) == "true" else ""
-        return f"adjoint_kernel<{m.group(1).replace('unsigned ', 'u')}{stream}{q1}> adjoint_{kind}{weigh}"
+        half = ",half" if m.group(6) == "true" else ""
+        return f"adjoint_kernel<{m.group(1).replace('unsigned ', 'u')}{stream}{q1}{half}> adjoint_{kind}{weigh}"
     return name.split("(")[0].replace("void ", "")
 
 
