@@ -152,14 +152,14 @@ struct BatchPlan {
     struct Job {
         bool resident = false;
         int T = 1;
-        size_t lut_at = 0, form_at = 0;    // element offsets into the table / form areas
+        size_t lut_at = 0, form_at = 0;    // element offsets into the tables: phase tables, forms
         size_t state_at = 0, part_at = 0;  // element offsets into batch states / partials
         uint32_t tiles = 0;
         SweepPlan plan;
     };
     struct Launch {
-        int kind, dtype, step, tb;
-        bool virt;
+        SweepBucket as;
+        int step;
         std::vector<int> members;
         size_t args_at, first_at;
         uint32_t blocks;
@@ -167,14 +167,14 @@ struct BatchPlan {
     };
     uint64_t key = 0;
     std::vector<Ident> ident;
-    void *blob = nullptr, *states = nullptr, *parts = nullptr, *results = nullptr;  // buffers the arguments point into
+    void *blob = nullptr, *tabs = nullptr, *states = nullptr, *parts = nullptr, *results = nullptr;  // buffers the arguments point into
     std::vector<Job> jobs;
     std::vector<Launch> launches;
     std::vector<int> res_members[2], sweep_members;
-    size_t lut_elems = 0, form_elems = 0, state_elems = 0, part_elems = 0;
-    size_t lut_at = 0, form_at = 0, fixed_at = 0, res_at[2] = {0, 0};
+    size_t state_elems = 0, part_elems = 0;
+    size_t res_at[2] = {0, 0};
     size_t red_part_at = 0, red_blocks_at = 0, red_out_at = 0, size = 0;
-    std::vector<unsigned char> fixed;  // host image of the blob from fixed_at on (angle fields filled per call)
+    std::vector<unsigned char> fixed;  // host image of the blob (angle fields filled per call)
     hipGraphExec_t exec = nullptr;
     uint64_t exec_reverse = 0;  // the final-state reversals the captured sequence holds
     ~BatchPlan() {
@@ -193,7 +193,8 @@ using BatchPlan = qnae_host::BatchPlan;
 uint64_t fnv(uint64_t h, uint64_t v) { return (h ^ v) * 1099511628211ull; }
 
 // The plan of a new batch shape; reserves the context's batch buffers.
-int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, BatchPlan& P) {
+int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, const std::vector<size_t>& lut_at,
+                    BatchPlan& P) {
     P.jobs.resize(count);
     int maxp = 1;
     for (int i = 0; i < count; ++i) maxp = std::max(maxp, inst[i].p);
@@ -205,10 +206,8 @@ int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, BatchPl
         BatchPlan::Job& J = P.jobs[i];
         J.resident = q.n <= kResidentMaxN;
         J.T = q.p > 0 ? q.p : 1;
-        J.lut_at = P.lut_elems;
-        P.lut_elems += (size_t)J.T * (q.m + 1);
-        J.form_at = P.form_elems;
-        P.form_elems += (size_t)J.T;
+        J.lut_at = lut_at[i];
+        J.form_at = lut_at[i] + (size_t)J.T * (q.m + 1);
         const int stored = q.n - (q.half ? 1 : 0);
         J.tiles = J.resident ? 0u : 1u << (stored - id.tb);
         J.part_at = P.part_elems;
@@ -219,26 +218,22 @@ int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, BatchPl
             plan_sweeps(J.plan, q.n, q.m, q.p, q.cost_dtype, id.tb, id.low, id.page, id.split, q.state_dev != nullptr,
                         no_forms.data(), std::complex<double>(1.0, 0.0));
             J.plan.half = q.half != 0;
+            J.plan.expand = q.half == 2 && q.state_dev != nullptr;
             steps = std::max(steps, (int)J.plan.ops.size());
         }
     }
     Blob B;
-    P.lut_at = B.take(sizeof(float2) * P.lut_elems);
-    P.form_at = B.take(sizeof(MixForm) * P.form_elems);
-    P.fixed_at = B.take(0);
-    // Sweep launches: step s, bucket (kind, cost type, virtual bit, tile bits).
+    // Sweep launches: step s, one per bucket.
     for (int st = 0; st < steps; ++st) {
-        std::map<std::tuple<int, int, bool, int>, size_t> bucket;
+        std::map<SweepBucket, size_t> bucket;
         for (int i = 0; i < count; ++i) {
             const BatchPlan::Job& J = P.jobs[i];
             if (J.resident || st >= (int)J.plan.ops.size()) continue;
-            const Op& op = J.plan.ops[st];
-            const auto key = std::make_tuple(op.kind, inst[i].cost_dtype, op_virtual(J.plan, op), P.ident[i].tb);
+            const SweepBucket key = op_bucket(J.plan, J.plan.ops[st]);
             auto it = bucket.find(key);
             if (it == bucket.end()) {
                 it = bucket.emplace(key, P.launches.size()).first;
-                P.launches.push_back({std::get<0>(key), std::get<1>(key), st, std::get<3>(key), std::get<2>(key), {}, 0,
-                                      0, 0u, 0.0});
+                P.launches.push_back({key, st, {}, 0, 0, 0u, 0.0});
             }
             P.launches[it->second].members.push_back(i);
         }
@@ -262,16 +257,17 @@ int make_batch_plan(qnae_ctx* ctx, const qnae_instance* inst, int count, BatchPl
     HIP_TRY(ctx->b_partials.reserve(sizeof(double) * (P.part_elems ? P.part_elems : 1)));
     HIP_TRY(ctx->b_results.reserve(sizeof(double) * 3 * count));
     P.blob = ctx->b_blob.ptr;
+    P.tabs = ctx->b_tabs.ptr;
     P.states = ctx->b_states.ptr;
     P.parts = ctx->b_partials.ptr;
     P.results = ctx->b_results.ptr;
 
     // Host image of the argument area: everything but the angle fields.
-    P.fixed.assign(P.size - P.fixed_at, 0);
-    unsigned char* h = P.fixed.data() - P.fixed_at;  // blob offsets index it directly
-    char* d = (char*)P.blob;
-    const float2* d_luts = (const float2*)(d + P.lut_at);
-    const MixForm* d_forms = (const MixForm*)(d + P.form_at);
+    P.fixed.assign(P.size, 0);
+    unsigned char* h = P.fixed.data();
+    const float2* d_luts = (const float2*)P.tabs;
+    const MixForm* d_forms = (const MixForm*)P.tabs;  // a form fills one table entry
+    static_assert(sizeof(MixForm) == sizeof(float2), "a mixer form fills one table entry");
     double* d_parts = (double*)P.parts;
     double* d_results = (double*)ctx->b_results.ptr;
     auto psi_of = [&](int i) -> float2* {
@@ -339,6 +335,40 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
 
+    // ---- flip-symmetric diagonals run on half the state; the tables are built
+    // and uploaded while the check runs (behind a cost build, say) --------------
+    std::vector<int> half(count);
+    for (int i = 0; i < count; ++i) half[i] = inst[i].half ? 1 : 0;
+    FlipBatch flips;
+    if (int rc = flip_batch_begin(ctx, inst, count, half, s, &flips)) return rc;
+    // Instance i's tables: T rows of m + 1 entries, then p forms.
+    std::vector<size_t> lut_at(count);
+    size_t tab_elems = 0;
+    for (int i = 0; i < count; ++i) {
+        lut_at[i] = tab_elems;
+        const size_t T = inst[i].p > 0 ? inst[i].p : 1;
+        tab_elems += T * (size_t)(inst[i].m + 1) + T;
+    }
+    HIP_TRY(ctx->h_btabs.reserve(sizeof(float2) * tab_elems));
+    HIP_TRY(ctx->b_tabs.reserve(sizeof(float2) * tab_elems));
+    float2* const tables = (float2*)ctx->h_btabs.ptr;
+    auto forms_of = [&](int i) -> MixForm* {
+        return (MixForm*)(tables + lut_at[i] + (size_t)(inst[i].p > 0 ? inst[i].p : 1) * (size_t)(inst[i].m + 1));
+    };
+    std::vector<std::complex<double>> scale(count);
+    constexpr int kChunk = 16;  // instances per host task
+    parallel_for(ctx, (count + kChunk - 1) / kChunk, tab_elems, [&](int c) {
+        for (int i = c * kChunk; i < std::min(count, (c + 1) * kChunk); ++i) {
+            const qnae_instance& q = inst[i];
+            scale[i] = build_tables(q.n, q.m, q.gammas, q.betas, q.p, tables + lut_at[i], forms_of(i));
+        }
+    });
+    HIP_TRY(hipMemcpyAsync(ctx->b_tabs.ptr, tables, sizeof(float2) * tab_elems, hipMemcpyHostToDevice, s));
+    if (int rc = flip_batch_end(ctx, flips, half, s)) return rc;
+    std::vector<qnae_instance> routed(inst, inst + count);  // half: 2 where the kept state is whole
+    for (int i = 0; i < count; ++i) routed[i].half = half[i];
+    inst = routed.data();
+
     // ---- the batch's shape: a plan seen before, or a new one ----------------
     std::vector<BatchPlan::Ident> ident(count);
     uint64_t key = 1469598103934665603ull;
@@ -356,7 +386,7 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     auto& cache = ctx->batch_plans;
     for (size_t c = 0; c < cache.size(); ++c) {
         BatchPlan* e = cache[c].get();
-        if (e->key == key && e->blob == ctx->b_blob.ptr && e->states == ctx->b_states.ptr &&
+        if (e->key == key && e->blob == ctx->b_blob.ptr && e->tabs == ctx->b_tabs.ptr && e->states == ctx->b_states.ptr &&
             e->parts == ctx->b_partials.ptr && e->results == ctx->b_results.ptr && e->ident == ident) {
             P = e;
             std::rotate(cache.begin() + c, cache.begin() + c + 1, cache.end());  // most recent last
@@ -367,34 +397,25 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
         std::unique_ptr<BatchPlan, BatchPlanFree> fresh(new BatchPlan());
         fresh->key = key;
         fresh->ident = std::move(ident);
-        if (int rc = make_batch_plan(ctx, inst, count, *fresh)) return rc;
+        if (int rc = make_batch_plan(ctx, inst, count, lut_at, *fresh)) return rc;
         if (cache.size() >= 8) cache.erase(cache.begin());
         cache.push_back(std::move(fresh));
         P = cache.back().get();
     }
 
-    // ---- per call: tables, forms and the angle fields of the arguments --------
+    // ---- per call: the angle fields of the arguments --------------------------
     HIP_TRY(ctx->h_blob.reserve(P->size));
     HIP_TRY(ctx->h_results.reserve(sizeof(double) * 3 * count));
     char* h = (char*)ctx->h_blob.ptr;
-    float2* tables = (float2*)(h + P->lut_at);
-    MixForm* forms = (MixForm*)(h + P->form_at);
-    std::vector<std::complex<double>> scale(count);
-    constexpr int kChunk = 16;  // instances per host task
-    parallel_for(ctx, (count + kChunk - 1) / kChunk, P->lut_elems, [&](int c) {
-        for (int i = c * kChunk; i < std::min(count, (c + 1) * kChunk); ++i) {
-            const qnae_instance& q = inst[i];
-            BatchPlan::Job& J = P->jobs[i];
-            scale[i] = build_tables(q.n, q.m, q.gammas, q.betas, q.p, tables + J.lut_at, forms + J.form_at);
-            if (!J.resident) {
-                SweepPlan& S = J.plan;
-                S.forms.assign(forms + J.form_at, forms + J.form_at + q.p);
-                for (int l = 0; l < q.p; ++l) S.flips_before[l + 1] = S.flips_before[l] ^ S.forms[l].flip;
-                S.final_scale = scale[i];
-            }
-        }
-    });
-    std::memcpy(h + P->fixed_at, P->fixed.data(), P->fixed.size());
+    for (int i : P->sweep_members) {
+        const qnae_instance& q = inst[i];
+        SweepPlan& S = P->jobs[i].plan;
+        const MixForm* const forms = forms_of(i);
+        S.forms.assign(forms, forms + q.p);
+        for (int l = 0; l < q.p; ++l) S.flips_before[l + 1] = S.flips_before[l] ^ S.forms[l].flip;
+        S.final_scale = scale[i];
+    }
+    std::memcpy(h, P->fixed.data(), P->fixed.size());
     for (const BatchPlan::Launch& L : P->launches) {
         SweepArgs* args = (SweepArgs*)(h + L.args_at);
         for (size_t q = 0; q < L.members.size(); ++q) {
@@ -438,9 +459,9 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
         }
         for (const BatchPlan::Launch& L : P->launches) {
             HIP_TRY(run(K_BATCH_SWEEP, L.bytes, [&] {
-                return qnae::launch_sweep_batch(L.tb, L.dtype, L.kind, (const SweepArgs*)(d + L.args_at),
+                return qnae::launch_sweep_batch(L.as.tb, L.as.dtype, L.as.kind, (const SweepArgs*)(d + L.args_at),
                                                 (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, st,
-                                                L.virt);
+                                                L.as.virt, L.as.l1);
             }));
         }
         for (int i : P->sweep_members) {

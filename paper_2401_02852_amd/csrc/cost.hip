@@ -180,39 +180,76 @@ __device__ __forceinline__ uint32_t flip_word(uint32_t w, bool u16) {
 }
 
 constexpr int kProThreads = 256, kProUnroll = 4;
-template <bool U16>
-__global__ __launch_bounds__(kProThreads) void prologue_kernel(const PrologueArgs a) {
-    const uint64_t id = (uint64_t)blockIdx.x * kProThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kProThreads;
-    for (uint64_t i = id; i < a.copies; i += stride) a.dst[i] = a.src[i];
-    if (!a.cost) return;
-    // a.quads 16-byte pieces: piece i faces a.quads - 1 - i
-    const uint64_t half = a.quads / 2;
+
+// Does a piece that thread `id` of `stride` looks at differ from its mirror
+// image? found(): has another workgroup found one (asked when there is more
+// to read)?
+template <bool U16, typename F>
+__device__ __forceinline__ bool flip_differs(const uint4* cost, uint64_t quads, uint64_t id, uint64_t stride,
+                                             F&& found) {
+    const uint64_t half = quads / 2;  // piece i faces quads - 1 - i
     uint32_t diff = 0u;
     for (uint64_t i = id; i < half; i += kProUnroll * stride) {
         uint4 x[kProUnroll], y[kProUnroll];
 #pragma unroll
         for (int u = 0; u < kProUnroll; ++u) {
             const uint64_t j = i + u * stride < half ? i + u * stride : i;
-            x[u] = a.cost[j];
-            y[u] = a.cost[a.quads - 1 - j];
+            x[u] = cost[j];
+            y[u] = cost[quads - 1 - j];
         }
 #pragma unroll
         for (int u = 0; u < kProUnroll; ++u)
             diff |= (x[u].x ^ flip_word(y[u].w, U16)) | (x[u].y ^ flip_word(y[u].z, U16)) |
                     (x[u].z ^ flip_word(y[u].y, U16)) | (x[u].w ^ flip_word(y[u].x, U16));
-        // more to read, and no workgroup has found a difference?
-        if (diff != 0u || (i + kProUnroll * stride < half &&
-                           __hip_atomic_load(a.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != 0u))
-            break;
+        if (diff != 0u || (i + kProUnroll * stride < half && found())) break;
     }
+    return diff != 0u;
+}
+
+template <bool U16>
+__global__ __launch_bounds__(kProThreads) void prologue_kernel(const PrologueArgs a) {
+    const uint64_t id = (uint64_t)blockIdx.x * kProThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kProThreads;
+    for (uint64_t i = id; i < a.copies; i += stride) a.dst[i] = a.src[i];
+    if (!a.cost) return;
+    const bool diff = flip_differs<U16>(a.cost, a.quads, id, stride, [&] {
+        return __hip_atomic_load(a.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != 0u;
+    });
     // One counter: workgroups done, and 2^16 for each that found a difference.
-    const uint32_t mine = __syncthreads_or(diff != 0u) ? 0x10001u : 1u;
+    const uint32_t mine = __syncthreads_or(diff) ? 0x10001u : 1u;
     if (threadIdx.x == 0) {
         const uint32_t v = mine + __hip_atomic_fetch_add(a.word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((v & 0xffffu) == gridDim.x) {
             __hip_atomic_store(a.word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(a.answer, 2u * a.ticket + (v >> 16 ? 1u : 0u), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
+// Job blockIdx.y, its pieces over the blocks of a row. The last workgroup of
+// all writes the ticket, after every flag. Ended workgroups are counted per
+// job first: thousands of additions to one word took 100 us.
+__global__ __launch_bounds__(kProThreads) void flip_batch_kernel(FlipJob* jobs, uint32_t* flags, uint32_t* word,
+                                                                 uint32_t ticket, uint32_t* answer) {
+    const FlipJob j = jobs[blockIdx.y];
+    const uint64_t id = (uint64_t)blockIdx.x * kProThreads + threadIdx.x, stride = (uint64_t)gridDim.x * kProThreads;
+    auto none = [] { return false; };
+    const bool diff = j.u16 ? flip_differs<true>(j.cost, j.quads, id, stride, none)
+                            : flip_differs<false>(j.cost, j.quads, id, stride, none);
+    const bool any = __syncthreads_or(diff) != 0;
+    if (threadIdx.x == 0) {
+        if (any) {
+            __hip_atomic_store(&flags[blockIdx.y], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __threadfence_system();
+        }
+        const uint32_t w =
+            1u + __hip_atomic_fetch_add(&jobs[blockIdx.y].done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (w != gridDim.x) return;
+        const uint32_t v = 1u + __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v == gridDim.y) {
+            __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence_system();
+            __hip_atomic_store(answer, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -250,6 +287,16 @@ hipError_t launch_prologue(const PrologueArgs& a, int dtype, hipStream_t s) {
     const dim3 grid((uint32_t)(want < 1024 ? want : 1024)), block(kProThreads);
     if (dtype == 1) hipLaunchKernelGGL(prologue_kernel<false>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(prologue_kernel<true>, grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint32_t* flags, uint32_t* word,
+                             uint32_t ticket, uint32_t* answer, hipStream_t s) {
+    if (count < 1 || count > 65535 || max_quads < 2) return hipErrorInvalidValue;
+    constexpr uint32_t kPer = kProThreads * kProUnroll;
+    const uint32_t want = (max_quads / 2 + kPer - 1) / kPer;
+    hipLaunchKernelGGL(flip_batch_kernel, dim3(want < 64 ? want : 64, (uint32_t)count), dim3(kProThreads), 0, s, jobs,
+                       flags, word, ticket, answer);
     return hipGetLastError();
 }
 

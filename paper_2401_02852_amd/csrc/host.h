@@ -16,6 +16,7 @@
 #include <string>
 #include <thread>
 #include <utility>
+#include <tuple>
 #include <vector>
 
 #include "../../include/qnae.h"
@@ -143,10 +144,10 @@ struct qnae_ctx {
     qnae_host::DevBuf state, partials, luts, clauses, small;  // small: zeros counter + 3 result doubles
     qnae_host::HostBuf h_luts, h_clauses, h_small;
     // batched path: uploaded tables and work lists, states, partial sums, results
-    qnae_host::DevBuf b_blob, b_states, b_partials, b_results;
+    qnae_host::DevBuf b_blob, b_tabs, b_states, b_partials, b_results;
     // gradient: checkpoints + adjoint state, tables, partial sums
     qnae_host::DevBuf g_states, g_blob, g_partials;
-    qnae_host::HostBuf h_blob, h_results;
+    qnae_host::HostBuf h_blob, h_btabs, h_results;
     hipEvent_t staging_done = nullptr;  // last async copy out of pinned staging
     // plans of recent batch shapes, with their captured launch sequences (most recent last)
     bool use_graphs = true;
@@ -165,6 +166,8 @@ struct qnae_ctx {
     qnae_host::DevBuf s_dev;
     qnae_host::HostBuf h_sample;
     uint32_t flip_ticket = 0;           // flip checks launched so far
+    qnae_host::DevBuf f_jobs;           // batched flip checks: jobs; pinned: answer, flags, jobs
+    qnae_host::HostBuf h_flip;
     int tile_bits = 13;                 // tile size of the plain sweeps (log2 amplitudes)
     int min_low_run = 4;                // minimum contiguous low run (log2 amplitudes)
     int page_bit = 18;                  // first index bit above a 2 MiB page of amplitudes
@@ -202,6 +205,18 @@ constexpr int kFlipEarlyMaxN = 24;
 int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void* cost, int dtype, int n,
              hipStream_t s);
 int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric);
+// The same for the instances of a batch: the tiled ones with half[i] = 0 are
+// checked, when their states together hold kFlipBatchAmps amplitudes or more
+// (smaller batches are bound by launches, not by bytes). end sets half[i] = 2
+// (half state, whole final state) where the diagonal is symmetric.
+constexpr uint64_t kFlipBatchAmps = 1ull << 22;
+struct FlipBatch {
+    std::vector<int> jobs;  // instances being checked
+    uint32_t ticket = 0;
+};
+int flip_batch_begin(qnae_ctx* ctx, const qnae_instance* inst, int count, const std::vector<int>& half, hipStream_t s,
+                     FlipBatch* f);
+int flip_batch_end(qnae_ctx* ctx, const FlipBatch& f, std::vector<int>& half, hipStream_t s);
 // fn(i) for i in [0, count), spread over the context's host threads when the
 // work is large enough to pay for the hand-off (`items` units of it).
 void parallel_for(qnae_ctx* ctx, int count, size_t items, const std::function<void(int)>& fn);
@@ -367,6 +382,21 @@ void sweep_args_angles(const SweepPlan& P, const Op& op, qnae::SweepArgs* a);
 // Does the op's group hold the virtual bit of a half-state plan (bit n-1)?
 inline bool op_virtual(const SweepPlan& P, const Op& op) {
     return P.half && P.groups[op.group].pos[P.TB - 1] == P.n - 1;
+}
+// Which sweeps of different plans share a launch: kind, cost type, virtual
+// bit, layout L1 and tile bits (fields compare in that order).
+struct SweepBucket {
+    int kind, dtype;
+    bool virt;
+    int l1, tb;
+    bool operator<(const SweepBucket& o) const {
+        return std::tie(kind, dtype, virt, l1, tb) < std::tie(o.kind, o.dtype, o.virt, o.l1, o.tb);
+    }
+};
+inline SweepBucket op_bucket(const SweepPlan& P, const Op& op) {
+    const uint32_t mask = P.groups[op.group].mask;
+    return {op.kind, P.dtype, op_virtual(P, op),
+            qnae::sweep_l1(P.TB, op.kind, op.pre_layer >= 0 ? mask : 0u, op.post_layer >= 0 ? mask : 0u), P.TB};
 }
 // Algorithmic bytes of one op and its profiling kind.
 double op_bytes(const SweepPlan& P, const Op& op);

@@ -59,6 +59,19 @@ struct PrologueArgs {
 };
 hipError_t launch_prologue(const PrologueArgs& a, int dtype, hipStream_t s);
 
+// The same check of many diagonals: flags[i] (pinned, zero before) is set to 1
+// when job i's is not symmetric, then the ticket is written to *answer
+// (pinned). word as above.
+struct FlipJob {
+    const uint4* cost;
+    uint32_t quads;  // 16-byte pieces of the diagonal, >= 2
+    uint32_t u16;
+    uint32_t done;  // workgroups of this job that have ended; 0 before
+    uint32_t pad[3];
+};
+hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint32_t* flags, uint32_t* word,
+                             uint32_t ticket, uint32_t* answer, hipStream_t s);
+
 // ---------------------------------------------------------------------------
 // State sweeps
 // ---------------------------------------------------------------------------
@@ -131,9 +144,13 @@ hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s);
 // first[i] .. first[i+1]-1 (first has count+1 entries, first[count] =
 // blocks), one per tile of its own geometry; args[i].partials receives 3
 // doubles per tile for readout kinds. Every instance uses tiles of tb bits
-// (12, 13 or 14). virt: every instance's group holds the virtual bit (args[i].vbit >= 0), or none does.
+// (12, 13 or 14). virt: every instance's group holds the virtual bit
+// (args[i].vbit >= 0), or none does. l1: sweep_l1 of every instance.
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool virt = false);
+                              uint32_t blocks, hipStream_t s, bool virt, int l1);
+// Does a launch of this kind over a group with these mix masks pass its tiles
+// through register layout L1? 1 yes, 2 no; 0: the kernel decides per tile.
+int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask);
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
 
 // Whole circuit for n <= 14 in one workgroup (state resident in LDS).

@@ -251,23 +251,20 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     size_t rounds = most;
     if (round_bytes > 0) rounds = std::min(rounds, std::max<size_t>(1, (size_t)(tick_bytes / round_bytes)));
     struct Launch {
-        int kind, dtype;
-        bool virt;
-        int tb;
         std::vector<Request*> members;
         size_t args_at, first_at;
         uint32_t blocks;
     };
-    std::vector<std::map<std::tuple<int, int, bool, int>, Launch>> sweeps(rounds);
+    std::vector<std::map<SweepBucket, Launch>> sweeps(rounds);
     std::vector<Request*> finishing;
     for (Request* r : large) {
         for (size_t k = 0; k < rounds && r->next_op + k < r->plan.ops.size(); ++k) {
             const Op& op = r->plan.ops[r->next_op + k];
-            Launch& L = sweeps[k][std::make_tuple(op.kind, r->dtype, op_virtual(r->plan, op), r->shape.tile_bits)];
-            L.kind = op.kind;
-            L.dtype = r->dtype;
-            L.virt = op_virtual(r->plan, op);
-            L.tb = r->shape.tile_bits;
+            // requests are at different sweeps of their plans: the kernel looks
+            // at layout L1 per tile rather than split the few there are
+            SweepBucket as = op_bucket(r->plan, op);
+            as.l1 = 0;
+            Launch& L = sweeps[k][as];
             L.members.push_back(r);
         }
         if (r->next_op + rounds >= r->plan.ops.size()) finishing.push_back(r);
@@ -384,9 +381,10 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     for (size_t k = 0; k < rounds; ++k)
         for (auto& kv : sweeps[k]) {
             const Launch& L = kv.second;
-            HIP_TRY(qnae::launch_sweep_batch(L.tb, L.dtype, L.kind, (const SweepArgs*)(d + L.args_at),
+            const SweepBucket& as = kv.first;
+            HIP_TRY(qnae::launch_sweep_batch(as.tb, as.dtype, as.kind, (const SweepArgs*)(d + L.args_at),
                                              (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, s,
-                                             L.virt));
+                                             as.virt, as.l1));
             ++launches;
         }
     if (!finishing.empty()) {

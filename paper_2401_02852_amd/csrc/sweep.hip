@@ -415,14 +415,15 @@ __global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu
     sweep_tile<TB, CT, KIND, VIRT, CKPT, L1M>(a, blockIdx.x, a.partials + 3 * (size_t)blockIdx.x);
 }
 
-// L1M of a single-state launch: 1 when a mask the kind mixes has bits that
+// L1M of a launch: 1 when a mask the kind mixes has bits that
 // only layout L1 holds, else 2.
 template <int TB, int KIND>
-int sweep_l1_mode(const SweepArgs& a) {
+int sweep_l1_mode(uint32_t pre_mask, uint32_t post_mask) {
     using L = Lay<TB>;
+    if (KIND == SK_P0) return 2;
     const bool pre = KIND == SK_MIDDLE || KIND == SK_BOUNDARY || KIND == SK_FINAL;
     const bool post = KIND == SK_FIRST || KIND == SK_BOUNDARY;
-    const bool l1 = (pre && L::sm1(a.pre_mask) != 0u) || (post && L::sm1(a.post_mask) != 0u);
+    const bool l1 = (pre && L::sm1(pre_mask) != 0u) || (post && L::sm1(post_mask) != 0u);
     return l1 ? 1 : 2;
 }
 
@@ -439,13 +440,13 @@ __device__ __forceinline__ int batch_item(const uint32_t* first, int count, uint
 
 // One sweep step over many states at once (ragged): instance i owns blocks
 // first[i] .. first[i+1]-1, one per tile, with its own arguments.
-template <int TB, typename CT, int KIND, bool VIRT>
+template <int TB, typename CT, int KIND, bool VIRT, int L1M>
 __global__ __launch_bounds__(64 << (TB - 11)) __attribute__((amdgpu_waves_per_eu(sweep_waves(TB, KIND)))) void sweep_batch_kernel(const SweepArgs* args, const uint32_t* first,
                                                                       int count) {
     const int i = batch_item(first, count, blockIdx.x);
     const SweepArgs a = args[i];
     const uint32_t t = blockIdx.x - first[i];
-    sweep_tile<TB, CT, KIND, VIRT>(a, t, a.partials + 3 * (size_t)t);
+    sweep_tile<TB, CT, KIND, VIRT, false, L1M>(a, t, a.partials + 3 * (size_t)t);
 }
 
 // psi[x] <-> psi[N - 1 - x]: undoes an X on every qubit (N >= 4).
@@ -652,23 +653,31 @@ void launch_kind_l1(const SweepArgs& a, hipStream_t s) {
 // (1.81 and 1.62 ms against 1.93 and 1.75 ms: the first kind fits four
 // workgroups per CU without the branch instead of three, and that is
 // slower for this write-only kind).
+constexpr bool l1_per_tile(int tb, int kind) { return tb == 13 && (kind == SK_FIRST || kind == SK_FINAL); }
+
 template <int TB, typename CT, int KIND>
 hipError_t launch_kind(const SweepArgs& a, hipStream_t s) {
-    if (TB == 13 && (KIND == SK_FIRST || KIND == SK_FINAL)) launch_kind_l1<TB, CT, KIND, 0>(a, s);
-    else if (KIND == SK_P0 || sweep_l1_mode<TB, KIND>(a) == 2) launch_kind_l1<TB, CT, KIND, 2>(a, s);
+    if constexpr (l1_per_tile(TB, KIND)) launch_kind_l1<TB, CT, KIND, 0>(a, s);
+    else if (sweep_l1_mode<TB, KIND>(a.pre_mask, a.post_mask) == 2) launch_kind_l1<TB, CT, KIND, 2>(a, s);
     else launch_kind_l1<TB, CT, KIND, 1>(a, s);
     return hipGetLastError();
 }
 
+template <int TB, typename CT, int KIND, int L1M>
+void launch_batch_l1(const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool virt,
+                     hipStream_t s) {
+    const dim3 grid(blocks), block(64 << (TB - 11));
+    if (virt) hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, KIND, true, L1M>), grid, block, 0, s, args, first, count);
+    else hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, KIND, false, L1M>), grid, block, 0, s, args, first, count);
+}
+
 template <int TB, typename CT, int KIND>
 hipError_t launch_batch_kind(const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool virt,
-                             hipStream_t s) {
-    if (virt)
-        hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, KIND, true>), dim3(blocks), dim3(64 << (TB - 11)), 0, s, args,
-                           first, count);
-    else
-        hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, KIND, false>), dim3(blocks), dim3(64 << (TB - 11)), 0, s, args,
-                           first, count);
+                             int l1, hipStream_t s) {
+    if (l1 == 0) launch_batch_l1<TB, CT, KIND, 0>(args, first, count, blocks, virt, s);
+    else if (l1_per_tile(TB, KIND)) return hipErrorInvalidValue;
+    else if (l1 == 2) launch_batch_l1<TB, CT, KIND, 2>(args, first, count, blocks, virt, s);
+    else launch_batch_l1<TB, CT, KIND, 1>(args, first, count, blocks, virt, s);
     return hipGetLastError();
 }
 
@@ -686,13 +695,13 @@ hipError_t launch_tb(int kind, const SweepArgs& a, hipStream_t s) {
 
 template <int TB, typename CT>
 hipError_t launch_batch_ct(int kind, const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks,
-                           bool virt, hipStream_t s) {
+                           bool virt, int l1, hipStream_t s) {
     switch (kind) {
-        case SK_FIRST: return launch_batch_kind<TB, CT, SK_FIRST>(args, first, count, blocks, virt, s);
-        case SK_MIDDLE: return launch_batch_kind<TB, CT, SK_MIDDLE>(args, first, count, blocks, virt, s);
-        case SK_BOUNDARY: return launch_batch_kind<TB, CT, SK_BOUNDARY>(args, first, count, blocks, virt, s);
-        case SK_FINAL: return launch_batch_kind<TB, CT, SK_FINAL>(args, first, count, blocks, virt, s);
-        case SK_P0: return launch_batch_kind<TB, CT, SK_P0>(args, first, count, blocks, virt, s);
+        case SK_FIRST: return launch_batch_kind<TB, CT, SK_FIRST>(args, first, count, blocks, virt, l1, s);
+        case SK_MIDDLE: return launch_batch_kind<TB, CT, SK_MIDDLE>(args, first, count, blocks, virt, l1, s);
+        case SK_BOUNDARY: return launch_batch_kind<TB, CT, SK_BOUNDARY>(args, first, count, blocks, virt, l1, s);
+        case SK_FINAL: return launch_batch_kind<TB, CT, SK_FINAL>(args, first, count, blocks, virt, l1, s);
+        case SK_P0: return launch_batch_kind<TB, CT, SK_P0>(args, first, count, blocks, virt, l1, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -715,17 +724,35 @@ hipError_t launch_sweep(int tb, int dtype, int kind, const SweepArgs& a, hipStre
 
 template <int TB>
 hipError_t launch_batch_tb(int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                           uint32_t blocks, hipStream_t s, bool virt) {
-    return dtype == 1 ? launch_batch_ct<TB, uint8_t>(kind, args, first, count, blocks, virt, s)
-                      : launch_batch_ct<TB, uint16_t>(kind, args, first, count, blocks, virt, s);
+                           uint32_t blocks, hipStream_t s, bool virt, int l1) {
+    return dtype == 1 ? launch_batch_ct<TB, uint8_t>(kind, args, first, count, blocks, virt, l1, s)
+                      : launch_batch_ct<TB, uint16_t>(kind, args, first, count, blocks, virt, l1, s);
+}
+
+template <int TB>
+int sweep_l1_tb(int kind, uint32_t pre_mask, uint32_t post_mask) {
+    if (l1_per_tile(TB, kind)) return 0;
+    switch (kind) {
+        case SK_FIRST: return sweep_l1_mode<TB, SK_FIRST>(pre_mask, post_mask);
+        case SK_MIDDLE: return sweep_l1_mode<TB, SK_MIDDLE>(pre_mask, post_mask);
+        case SK_BOUNDARY: return sweep_l1_mode<TB, SK_BOUNDARY>(pre_mask, post_mask);
+        case SK_FINAL: return sweep_l1_mode<TB, SK_FINAL>(pre_mask, post_mask);
+        default: return 2;
+    }
+}
+
+int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask) {
+    return tb == 12   ? sweep_l1_tb<12>(kind, pre_mask, post_mask)
+           : tb == 13 ? sweep_l1_tb<13>(kind, pre_mask, post_mask)
+                      : sweep_l1_tb<14>(kind, pre_mask, post_mask);
 }
 
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool virt) {
+                              uint32_t blocks, hipStream_t s, bool virt, int l1) {
     switch (tb) {
-        case 12: return launch_batch_tb<12>(dtype, kind, args, first, count, blocks, s, virt);
-        case 13: return launch_batch_tb<13>(dtype, kind, args, first, count, blocks, s, virt);
-        case 14: return launch_batch_tb<14>(dtype, kind, args, first, count, blocks, s, virt);
+        case 12: return launch_batch_tb<12>(dtype, kind, args, first, count, blocks, s, virt, l1);
+        case 13: return launch_batch_tb<13>(dtype, kind, args, first, count, blocks, s, virt, l1);
+        case 14: return launch_batch_tb<14>(dtype, kind, args, first, count, blocks, s, virt, l1);
         default: return hipErrorInvalidValue;
     }
 }
@@ -734,7 +761,7 @@ template <typename CT>
 hipError_t launch_ckpt_ct(const SweepArgs& a, hipStream_t s) {
     constexpr int TB = kAdjointTileBits;
     const dim3 grid(1u << a.nw), block(64 << (TB - 11));
-    const bool l1 = sweep_l1_mode<TB, SK_BOUNDARY>(a) == 1;
+    const bool l1 = sweep_l1_mode<TB, SK_BOUNDARY>(a.pre_mask, a.post_mask) == 1;
     if (a.half && a.vbit >= 0) {
         if (l1) hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, true, true, 1>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((sweep_kernel<TB, CT, SK_BOUNDARY, true, true, 2>), grid, block, 0, s, a);

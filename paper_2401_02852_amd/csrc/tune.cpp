@@ -136,6 +136,7 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
         SweepPlan P;
         plan_sweeps(P, n, m, layers, cost_dtype, t.tile_bits, t.low_run_bits, t.page_bit, t.split, false, forms,
                     final_scale);
+        P.half = n >= kFlipMinN;  // as a run on this (flip-symmetric) diagonal
         hipError_t e = run(P, t.tile_bits);  // warm-up
         if (e || (e = hipEventRecord(ev[0], s))) return e;
         for (int r = 0; r < reps && !e; ++r) e = run(P, t.tile_bits);
