@@ -50,10 +50,15 @@ int qnae_build_cost_diagonal_batched(qnae_ctx* ctx, const qnae_cost_job* jobs, i
     Blob B;
     const size_t rec_at = B.take(sizeof(ClauseRec) * (total_recs ? total_recs : 1));
     const size_t zero_at = B.take(sizeof(unsigned long long) * count);
-    std::vector<int> groups[4];  // (dtype, wide)
-    for (int i = 0; i < count; ++i) groups[(jobs[i].cost_dtype == QNAE_U16 ? 2 : 0) + (jobs[i].n > 32 ? 1 : 0)].push_back(i);
-    size_t args_at[4], first_at[4];
-    for (int g = 0; g < 4; ++g) {
+    std::vector<int> groups[2];  // by cost type
+    uint64_t total[2] = {0, 0};  // states
+    for (int i = 0; i < count; ++i) {
+        const int g = jobs[i].cost_dtype == QNAE_U16 ? 1 : 0;
+        groups[g].push_back(i);
+        total[g] += 1ull << (jobs[i].n - (jobs[i].half ? 1 : 0));
+    }
+    size_t args_at[2], first_at[2];
+    for (int g = 0; g < 2; ++g) {
         args_at[g] = B.take(sizeof(qnae::CostArgs) * groups[g].size());
         first_at[g] = B.take(sizeof(uint32_t) * (groups[g].size() + 1));
     }
@@ -64,7 +69,7 @@ int qnae_build_cost_diagonal_batched(qnae_ctx* ctx, const qnae_cost_job* jobs, i
     ClauseRec* recs = (ClauseRec*)(h + rec_at);
     // each job's records start at the sum of the clause counts before it
     std::vector<size_t> rec_off(count);
-    std::vector<int> nrec(count), nlow(count);
+    std::vector<int> nrec(count);
     size_t at = 0;
     for (int i = 0; i < count; ++i) {
         rec_off[i] = at;
@@ -73,29 +78,26 @@ int qnae_build_cost_diagonal_batched(qnae_ctx* ctx, const qnae_cost_job* jobs, i
     constexpr int kChunk = 16;  // jobs per host task
     parallel_for(ctx, (count + kChunk - 1) / kChunk, total_recs, [&](int c) {
         for (int i = c * kChunk; i < std::min(count, (c + 1) * kChunk); ++i)
-            nrec[i] = make_clause_records(jobs[i].clauses, jobs[i].m, jobs[i].k, recs + rec_off[i], jobs[i].predicate,
-                                          &nlow[i]);
+            nrec[i] = make_clause_records(jobs[i].clauses, jobs[i].m, jobs[i].k, recs + rec_off[i], jobs[i].predicate);
     });
     std::memset(h + zero_at, 0, sizeof(unsigned long long) * count);
     unsigned long long* zeros_dev = (unsigned long long*)(d + zero_at);
-    uint32_t blocks[4] = {0, 0, 0, 0};
-    int maxc[4] = {0, 0, 0, 0};
-    double bytes[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int g = 0; g < 4; ++g) {
+    uint32_t blocks[2] = {0, 0};
+    int maxc[2] = {0, 0};
+    double bytes[2] = {0.0, 0.0};
+    for (int g = 0; g < 2; ++g) {
         qnae::CostArgs* args = (qnae::CostArgs*)(h + args_at[g]);
         uint32_t* first = (uint32_t*)(h + first_at[g]);
         for (size_t q = 0; q < groups[g].size(); ++q) {
             const int i = groups[g][q];
             args[q].clauses = (const ClauseRec*)(d + rec_at) + rec_off[i];
             args[q].num_clauses = nrec[i];
-            args[q].num_low = nlow[i];
             const int states = jobs[i].n - (jobs[i].half ? 1 : 0);
             args[q].n = states;
             args[q].cost = jobs[i].cost_dev;
             args[q].zeros = zeros_dev + i;
             first[q] = blocks[g];
-            const uint64_t threads = states >= 5 ? (1ull << (states - 5)) : 1ull;
-            const uint64_t nb = (threads + 255) / 256;
+            const uint64_t nb = qnae::cost_blocks(states, qnae::cost_words(total[g]));
             if (blocks[g] + nb > 0x7fffffffull) return fail(QNAE_EINVAL, "batch too large for one grid");
             blocks[g] += (uint32_t)nb;
             maxc[g] = std::max(maxc[g], nrec[i]);
@@ -104,12 +106,12 @@ int qnae_build_cost_diagonal_batched(qnae_ctx* ctx, const qnae_cost_job* jobs, i
         first[groups[g].size()] = blocks[g];
     }
     HIP_TRY(hipMemcpyAsync(d, h, B.size, hipMemcpyHostToDevice, s));
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < 2; ++g) {
         if (groups[g].empty()) continue;
         HIP_TRY(timed(ctx, K_BATCH_COST, bytes[g], s, [&] {
             return qnae::launch_cost_batch((const qnae::CostArgs*)(d + args_at[g]), (const uint32_t*)(d + first_at[g]),
-                                           (int)groups[g].size(), blocks[g], g >= 2 ? QNAE_U16 : QNAE_U8, maxc[g],
-                                           (g & 1) != 0, s);
+                                           (int)groups[g].size(), blocks[g], g ? QNAE_U16 : QNAE_U8, maxc[g],
+                                           qnae::cost_words(total[g]), s);
         }));
     }
     HIP_TRY(hipEventRecord(ctx->cost_staging_done, s));

@@ -1,145 +1,288 @@
 // Cost diagonal kernel: C(x) = number of NAE-violated clauses, for every basis
 // state x (Section 3.2, eq. knaesatobj; Appendix A.2, eq. demorgannae).
 //
-// Bit-sliced: each thread owns an aligned run of 32 consecutive states. For one
-// clause, its violation pattern over the run is a 32-bit word: the part of the
-// clause on variables >= 5 is constant over the run (one compare against the
-// thread's index), and the part on variables 0..4 is a per-clause table built
-// on the host. The per-state counters are kept as NP bit-planes (a vertical
-// counter); clauses go in eight at a time through a carry-save adder tree, so
-// one clause costs about 9 integer operations per 32 states (clauses on
-// variables >= 5 only are constant over the run and are counted as one
-// integer instead). At the end the planes are transposed into bytes (uint8)
-// or half-words (uint16) and written with 16-byte stores.
+// Bit-sliced: a thread counts W runs of 32 consecutive states, a wave 64 W runs:
+// state bits 0..4 in a run, 5..10 the lane, 11.. the thread's run, the rest
+// the wave. Counters are NP bit planes per run (vertical counters).
+//
+// What bounds it is integer ALU work, so clauses are cut down to what a wave
+// can see before any of its lanes counts: 64 clauses at a time, a lane per
+// clause, the literals on the wave's own bits decide whether the clause can be
+// violated there at all (with h of them 2^(1-h) can). Survivors go to two
+// lists in LDS: clauses with a variable below 5 carry a 32-state violation
+// pattern per polarity; the others are constant over a run and only count.
+// Clauses that are constant over the whole wave are counted by the ballot. One
+// pass over the first list then costs about 5 operations per clause and run
+// (2 to form the pattern, 2.5 in a carry-save adder tree, and the lane
+// compare, shared by the W runs), over the second about 1.5.
+// Measured against every lane testing every clause with scalar loads: see
+// launch_cost.
+#include <type_traits>
+
 #include "internal.h"
+#include "tile.h"
 
 namespace qnae {
 namespace {
 
-// Thread `tid` of one diagonal: states [32 tid, 32 tid + 32).
-template <int NP, bool WIDE, bool U16>
-__device__ __forceinline__ void cost_chunk(const CostArgs& a, uint64_t tid) {
-    const uint64_t nthreads = a.n >= 5 ? (1ull << (a.n - 5)) : 1ull;
-    uint32_t zeros = 0;
-    if (tid < nthreads) {
-        const uint64_t xbase = tid << 5;
-        const uint32_t xlo = (uint32_t)xbase, xhi = (uint32_t)(xbase >> 32);
-        uint32_t plane[NP];
+constexpr int kCostThreads = 256, kCostWaves = kCostThreads / 64;
+constexpr int kCostChunk = 192;  // clauses filtered into the lists at a time: counts of a run fit a byte
+
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
+}
+
+// Position of state s of a run in the planes: bit 8 (s & 3) + (s >> 2), so that
+// transposing 8x8 bit blocks leaves four consecutive states in each word. The
+// index bits rotate by two: swaps of index bits (0,2), (1,3), (2,4), (3,4).
+template <int I, int J>
+__device__ __forceinline__ uint32_t swap_index_bits(uint32_t x) {
+    constexpr uint32_t set[5] = {0xAAAAAAAAu, 0xCCCCCCCCu, 0xF0F0F0F0u, 0xFF00FF00u, 0xFFFF0000u};
+    constexpr uint32_t m = set[I] & ~set[J];  // bit I set, bit J clear
+    constexpr int d = (1 << J) - (1 << I);
+    const uint32_t t = ((x >> d) ^ x) & m;
+    return x ^ t ^ (t << d);
+}
+__device__ __forceinline__ uint32_t to_planes(uint32_t x) {
+    return swap_index_bits<3, 4>(swap_index_bits<2, 4>(swap_index_bits<1, 3>(swap_index_bits<0, 2>(x))));
+}
+
+// 8x8 transposes of the bit blocks of eight planes: byte q of word r becomes
+// the counter of state 4 r + q.
+__device__ __forceinline__ void transpose8(uint32_t (&p)[8]) {
+    auto step = [&](int d, uint32_t m) {
 #pragma unroll
-        for (int b = 0; b < NP; ++b) plane[b] = 0u;
-        // Violation word of clause i over the 32 states.
-        auto viol = [&](int i) -> uint32_t {
-            const ClauseRec r = a.clauses[i];
-            const uint32_t hlo = (xlo ^ r.pat_lo) & r.mask_hi_lo;
-            bool none, all;
-            if (WIDE) {
-                const uint32_t hhi = (xhi ^ r.pat_hi) & r.mask_hi_hi;
-                none = (hlo | hhi) == 0u;
-                all = (hlo == r.mask_hi_lo) && (hhi == r.mask_hi_hi);
-            } else {
-                none = hlo == 0u;
-                all = hlo == r.mask_hi_lo;
-            }
-            return (none ? r.zero_tab : 0u) | (all ? r.full_tab : 0u);
-        };
-        // Adds carry * 2^b0 to the counter (ripple through the planes above).
-        auto add_at = [&](int b0, uint32_t carry) {
-#pragma unroll
-            for (int b = 0; b < NP; ++b) {
-                if (b < b0) continue;
-                const uint32_t t = plane[b] & carry;
-                plane[b] ^= carry;
-                carry = t;
-            }
-        };
-        // Full adder per bit: x + p + q = x' + 2 carry.
-        auto csa = [](uint32_t& x, uint32_t p, uint32_t q) -> uint32_t {
-            const uint32_t t = x ^ p;
-            const uint32_t carry = (t & q) | (~t & x);
-            x = t ^ q;
-            return carry;
-        };
-        // Eight clauses at a time through a carry-save tree (7 full adders
-        // into the planes of weight 1, 2 and 4, one ripple from weight 8):
-        // the counter value after the block is exactly the sum it had plus
-        // the eight violation bits, per state.
-        int i = 0;
-        for (; i + 8 <= a.num_low; i += 8) {
-            const uint32_t c2a = csa(plane[0], viol(i), viol(i + 1));
-            const uint32_t c2b = csa(plane[0], viol(i + 2), viol(i + 3));
-            const uint32_t c2c = csa(plane[0], viol(i + 4), viol(i + 5));
-            const uint32_t c2d = csa(plane[0], viol(i + 6), viol(i + 7));
-            const uint32_t c4a = csa(plane[1], c2a, c2b);
-            const uint32_t c4b = csa(plane[1], c2c, c2d);
-            add_at(3, csa(plane[2], c4a, c4b));
+        for (int i = 0; i < 8; ++i) {
+            if (i & d) continue;
+            const uint32_t a = p[i], b = p[i | d];
+            p[i] = (a & m) | ((b << d) & ~m);
+            p[i | d] = ((a >> d) & m) | (b & ~m);
         }
-        for (; i < a.num_low; ++i) add_at(0, viol(i));
-        // The other clauses only have variables >= 5: each is violated on all
-        // 32 states of the run or on none, so they are counted as one integer
-        // (about 5 operations per clause instead of 9) and the count is added
-        // to every state's counter once, as a ripple-carry over the planes.
-        uint32_t cnt = 0u;
-        for (; i < a.num_clauses; ++i) cnt += viol(i) & 1u;
+    };
+    step(4, 0x0f0f0f0fu);
+    step(2, 0x33333333u);
+    step(1, 0x55555555u);
+}
+
+// Vertical counters of one run.
+template <int NP>
+struct Counter {
+    uint32_t p[NP];
+    // + carry 2^b0 (ripple)
+    __device__ __forceinline__ void add_at(int b0, uint32_t carry) {
+#pragma unroll
+        for (int b = 0; b < NP; ++b) {
+            if (b < b0) continue;
+            const uint32_t t = p[b] & carry;
+            p[b] ^= carry;
+            carry = t;
+        }
+    }
+    // + x + y at plane b; returns the carry out (weight 2^(b+1))
+    __device__ __forceinline__ uint32_t csa(int b, uint32_t x, uint32_t y) {
+        const uint32_t carry = maj3(p[b], x, y);
+        p[b] = xor3(p[b], x, y);
+        return carry;
+    }
+    __device__ __forceinline__ void add4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+        const uint32_t x = csa(0, a, b), y = csa(0, c, d);
+        add_at(2, csa(1, x, y));
+    }
+    // + eight patterns; returns the carry of weight 8
+    __device__ __forceinline__ uint32_t add8(const uint32_t (&v)[8]) {
+        const uint32_t a = csa(0, v[0], v[1]), b = csa(0, v[2], v[3]), c = csa(0, v[4], v[5]), d = csa(0, v[6], v[7]);
+        const uint32_t e = csa(1, a, b), f = csa(1, c, d);
+        return csa(2, e, f);
+    }
+    // + n to every state
+    __device__ __forceinline__ void add_all(uint32_t n) {
         uint32_t carry = 0u;
 #pragma unroll
         for (int b = 0; b < NP; ++b) {
-            const uint32_t cb = 0u - ((cnt >> b) & 1u);
-            const uint32_t t = plane[b] ^ cb;
-            const uint32_t nc = (plane[b] & cb) | (t & carry);
-            plane[b] = t ^ carry;
-            carry = nc;
+            const uint32_t bit = 0u - ((n >> b) & 1u);
+            const uint32_t c = maj3(p[b], bit, carry);
+            p[b] = xor3(p[b], bit, carry);
+            carry = c;
         }
-        const uint32_t valid = a.n >= 5 ? 0xffffffffu : ((1u << (1u << a.n)) - 1u);
-        uint32_t any = 0u;
-#pragma unroll
-        for (int b = 0; b < NP; ++b) any |= plane[b];
-        zeros = (uint32_t)__popc(~any & valid);
+    }
+};
 
-        if (!U16) {
-            // 32 bytes: byte j = sum_b bit j of plane b, shifted to bit b.
-            uint32_t word[8];
+// Wave `wv` of one diagonal: states [wv 2048 W, (wv + 1) 2048 W).
+template <int NP, bool U16, int W>
+__device__ __forceinline__ void cost_wave(const CostArgs& a, uint64_t wv) {
+    static_assert(W == 1 || W == 4, "a thread counts one or four runs");
+    constexpr int LB = W == 4 ? 13 : 11;  // state bits within a wave
+    // Entries (pattern where every literal is false, where every one is true, their
+    // signs on bits 5..10 and run masks, variables on bits 5..10): the first list
+    // from the front, in multiples of four, the second from the back.
+    __shared__ uint4 lists[kCostWaves][kCostChunk + 4];
+    __shared__ uint32_t blk;
+    uint32_t zeros = 0;
+    const uint32_t lane = threadIdx.x & 63u;
+    uint4* const list = lists[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
+    const uint64_t x0 = wv << LB;
+    if (a.n >= LB ? (wv >> (a.n - LB)) == 0ull : wv == 0ull) {
+        const uint32_t xlo = (uint32_t)x0, xhi = (uint32_t)(x0 >> 32);
+        Counter<NP> cnt[W];
+        uint32_t runs[W];  // clauses counted as integers, per run
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                uint32_t wv = 0u;
+        for (int w = 0; w < W; ++w) {
+            runs[w] = 0u;
 #pragma unroll
-                for (int b = 0; b < NP; ++b) {
-                    const uint32_t nib = (plane[b] >> (4 * q)) & 0xfu;
-                    wv |= ((nib * 0x00204081u) & 0x01010101u) << b;
+            for (int b = 0; b < NP; ++b) cnt[w].p[b] = 0u;
+        }
+        uint32_t whole = 0u;  // clauses violated on the whole wave
+        for (int c0 = 0; c0 < a.num_clauses; c0 += kCostChunk) {
+            const int c1 = min(a.num_clauses, c0 + kCostChunk);
+            uint32_t nfront = 0u, nback = 0u;
+            for (int c = c0; c < c1; c += 64) {
+                uint32_t zt = 0u, ft = 0u, signs = 0u, vars = 0u;
+                bool low = false, fixed = false;  // a variable below 5; none below the wave's bits
+                if (c + (int)lane < c1) {
+                    const ClauseRec r = a.clauses[c + lane];
+                    const uint32_t mlo = r.mask_hi_lo & ~((1u << LB) - 1u);
+                    const uint32_t dlo = (xlo ^ r.pat_lo) & mlo, dhi = (xhi ^ r.pat_hi) & r.mask_hi_hi;
+                    const uint32_t in = (r.mask_hi_lo >> 5) & ((1u << (LB - 5)) - 1u), sg = r.pat_lo >> 5;
+                    if ((dlo | dhi) == 0u) zt = r.zero_tab;
+                    if (dlo == mlo && dhi == r.mask_hi_hi) ft = r.full_tab;
+                    low = r.zero_tab != ~0u;
+                    vars = in & 63u;
+                    uint32_t nw = 1u, aw = 1u;  // runs on whose own bits every literal is false, true
+                    if (W == 4) {
+                        nw = aw = 0u;
+#pragma unroll
+                        for (uint32_t w = 0; w < 4; ++w) {
+                            const uint32_t d = (w ^ (sg >> 6)) & (in >> 6);
+                            nw |= d == 0u ? 1u << w : 0u;
+                            aw |= d == (in >> 6) ? 1u << w : 0u;
+                        }
+                    }
+                    signs = (sg & 63u) | (nw << 16) | (aw << 20);
+                    if (low) {
+                        zt = to_planes(zt);
+                        ft = to_planes(ft);
+                    } else {  // constant over a run: a byte per run
+                        zt = zt ? (nw * 0x00204081u) & 0x01010101u : 0u;
+                        ft = ft ? (aw * 0x00204081u) & 0x01010101u : 0u;
+                        fixed = in == 0u;
+                    }
                 }
-                word[q] = wv;
+                const bool alive = (zt | ft) != 0u;
+                whole += (uint32_t)__popcll(__ballot(alive && fixed));
+                const bool tof = alive && low, tob = alive && !low && !fixed;
+                const uint64_t bf = __ballot(tof), bb = __ballot(tob);
+                const uint64_t below = (1ull << lane) - 1ull;
+                const uint4 e = make_uint4(zt, ft, signs, vars);
+                if (tof) list[nfront + (uint32_t)__popcll(bf & below)] = e;
+                if (tob) list[kCostChunk + 3u - nback - (uint32_t)__popcll(bb & below)] = e;
+                nfront += (uint32_t)__popcll(bf);
+                nback += (uint32_t)__popcll(bb);
             }
-            uint8_t* out = (uint8_t*)a.cost + xbase;
-            if (a.n >= 5) {
-                ((uint4*)out)[0] = make_uint4(word[0], word[1], word[2], word[3]);
-                ((uint4*)out)[1] = make_uint4(word[4], word[5], word[6], word[7]);
-            } else {
-                for (uint32_t j = 0; j < (1u << a.n); ++j) out[j] = (uint8_t)(word[j >> 2] >> (8 * (j & 3)));
-            }
-        } else {
-            // 64 bytes: half-word j = sum_b bit j of plane b, shifted to bit b.
-            uint32_t word[16];
+            // entries that never match fill the first list to a multiple of four
+            if (lane < (4u - (nfront & 3u) & 3u)) list[nfront + lane] = make_uint4(0u, 0u, 0u, 0u);
+            tile::wave_lds_sync();
+            const uint32_t steps = (nfront + 3u) & ~3u;
+            // Patterns of entry i over the thread's runs.
+            auto viol = [&](uint32_t i, uint32_t(&v)[W]) {
+                const uint4 e = list[i];
+                const uint32_t d = __builtin_amdgcn_bitop3_b32(lane, e.z, e.w, 0x28);  // (lane ^ z) & w
+                const uint32_t z = d == 0u ? e.x : 0u, f = d == e.w ? e.y : 0u;
+                if (W == 1) {
+                    v[0] = z | f;
+                } else {
+                    const int s = __builtin_amdgcn_readfirstlane((int)e.z);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                uint32_t wv = 0u;
-#pragma unroll
-                for (int b = 0; b < NP; ++b) {
-                    const uint32_t pair = (plane[b] >> (2 * q)) & 3u;
-                    wv |= ((pair * 0x8001u) & 0x10001u) << b;
+                    for (int w = 0; w < W; ++w) {
+                        const uint32_t sn = (uint32_t)((s << (15 - w)) >> 31), sa = (uint32_t)((s << (11 - w)) >> 31);
+                        v[w] = (z & sn) | (f & sa);
+                    }
                 }
-                word[q] = wv;
-            }
-            uint16_t* out = (uint16_t*)a.cost + xbase;
-            if (a.n >= 5) {
+            };
+            auto eight = [&](uint32_t i, uint32_t(&carry)[W]) {
+                uint32_t v[W][8];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    ((uint4*)out)[q] = make_uint4(word[4 * q], word[4 * q + 1], word[4 * q + 2], word[4 * q + 3]);
+                for (int k = 0; k < 8; ++k) {
+                    uint32_t t[W];
+                    viol(i + k, t);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) v[w][k] = t[w];
+                }
+#pragma unroll
+                for (int w = 0; w < W; ++w) carry[w] = cnt[w].add8(v[w]);
+            };
+            uint32_t i = 0;
+            for (; i + 16u <= steps; i += 16u) {
+                uint32_t x[W], y[W];
+                eight(i, x);
+                eight(i + 8u, y);
+#pragma unroll
+                for (int w = 0; w < W; ++w) cnt[w].add_at(4, cnt[w].csa(3, x[w], y[w]));
+            }
+            for (; i < steps; i += 4u) {
+                uint32_t v[4][W];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) viol(i + k, v[k]);
+#pragma unroll
+                for (int w = 0; w < W; ++w) cnt[w].add4(v[0][w], v[1][w], v[2][w], v[3][w]);
+            }
+            uint32_t bytes = 0u;
+            for (uint32_t k = 0; k < nback; ++k) {
+                const uint4 e = list[kCostChunk + 3u - k];
+                const uint32_t d = __builtin_amdgcn_bitop3_b32(lane, e.z, e.w, 0x28);
+                bytes += (d == 0u ? e.x : 0u) + (d == e.w ? e.y : 0u);
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w) runs[w] += (bytes >> (8 * w)) & 0xffu;
+            tile::wave_lds_sync();  // the lists are read before the next chunk's entries go in
+        }
+        const uint32_t valid = a.n >= 5 ? 0xffffffffu : to_planes((1u << (1u << a.n)) - 1u);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint64_t x = x0 | (uint64_t)w << 11 | (uint64_t)lane << 5;
+            if (x >> a.n) continue;  // (n below the wave's bits)
+            cnt[w].add_all(whole + runs[w]);
+            uint32_t any = 0u;
+#pragma unroll
+            for (int b = 0; b < NP; ++b) any |= cnt[w].p[b];
+            zeros += (uint32_t)__popc(~any & valid);
+            uint32_t lo[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) lo[b] = b < NP ? cnt[w].p[b] : 0u;
+            transpose8(lo);
+            if (!U16) {
+                uint8_t* const out = (uint8_t*)a.cost + x;
+                if (a.n >= 5) {
+                    ((uint4*)out)[0] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+                    ((uint4*)out)[1] = make_uint4(lo[4], lo[5], lo[6], lo[7]);
+                } else {
+                    for (uint32_t j = 0; j < (1u << a.n); ++j) out[j] = (uint8_t)(lo[j >> 2] >> (8 * (j & 3)));
+                }
             } else {
-                for (uint32_t j = 0; j < (1u << a.n); ++j) out[j] = (uint16_t)(word[j >> 1] >> (16 * (j & 1)));
+                uint32_t hi[8];
+#pragma unroll
+                for (int b = 0; b < 8; ++b) hi[b] = b + 8 < NP ? cnt[w].p[b + 8] : 0u;
+                transpose8(hi);
+                uint32_t word[16];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    word[2 * r] = __builtin_amdgcn_perm(hi[r], lo[r], 0x05010400u);
+                    word[2 * r + 1] = __builtin_amdgcn_perm(hi[r], lo[r], 0x07030602u);
+                }
+                uint16_t* const out = (uint16_t*)a.cost + x;
+                if (a.n >= 5) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        ((uint4*)out)[q] = make_uint4(word[4 * q], word[4 * q + 1], word[4 * q + 2], word[4 * q + 3]);
+                } else {
+                    for (uint32_t j = 0; j < (1u << a.n); ++j) out[j] = (uint16_t)(word[j >> 1] >> (16 * (j & 1)));
+                }
             }
         }
     }
     if (a.zeros) {
-        __shared__ uint32_t blk;
         if (threadIdx.x == 0) blk = 0u;
         __syncthreads();
         // wave-level sum first, then one LDS atomic per wave
@@ -151,14 +294,16 @@ __device__ __forceinline__ void cost_chunk(const CostArgs& a, uint64_t tid) {
     }
 }
 
-template <int NP, bool WIDE, bool U16>
-__global__ __launch_bounds__(256) void cost_kernel(const CostArgs a) {
-    cost_chunk<NP, WIDE, U16>(a, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x);
+template <int NP, bool U16, int W>
+__global__ __launch_bounds__(kCostThreads) void cost_kernel(const CostArgs a) {
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    cost_wave<NP, U16, W>(a, (uint64_t)blockIdx.x * kCostWaves + wave);
 }
 
 // Many diagonals at once: instance i owns blocks first[i] .. first[i+1]-1.
-template <int NP, bool WIDE, bool U16>
-__global__ __launch_bounds__(256) void cost_batch_kernel(const CostArgs* args, const uint32_t* first, int count) {
+template <int NP, bool U16, int W>
+__global__ __launch_bounds__(kCostThreads) void cost_batch_kernel(const CostArgs* args, const uint32_t* first,
+                                                                  int count) {
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -166,7 +311,8 @@ __global__ __launch_bounds__(256) void cost_batch_kernel(const CostArgs* args, c
         else hi = mid - 1;
     }
     const CostArgs a = args[lo];
-    cost_chunk<NP, WIDE, U16>(a, (uint64_t)(blockIdx.x - first[lo]) * blockDim.x + threadIdx.x);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    cost_wave<NP, U16, W>(a, (uint64_t)(blockIdx.x - first[lo]) * kCostWaves + wave);
 }
 
 // What precedes a run in one launch: its tables from pinned host memory to the
@@ -254,28 +400,38 @@ __global__ __launch_bounds__(kProThreads) void flip_batch_kernel(FlipJob* jobs, 
     }
 }
 
-template <int NP, bool U16>
-hipError_t launch_np(const CostArgs& a, bool wide, hipStream_t s) {
-    const uint64_t nthreads = a.n >= 5 ? (1ull << (a.n - 5)) : 1ull;
-    const uint64_t blocks = (nthreads + 255) / 256;
-    if (wide)
-        hipLaunchKernelGGL((cost_kernel<NP, true, U16>), dim3((uint32_t)blocks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((cost_kernel<NP, false, U16>), dim3((uint32_t)blocks), dim3(256), 0, s, a);
+template <int NP, bool U16, int W>
+hipError_t launch_np(const CostArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((cost_kernel<NP, U16, W>), dim3(cost_blocks(a.n, W)), dim3(kCostThreads), 0, s, a);
     return hipGetLastError();
+}
+template <int NP, bool U16, int W>
+hipError_t launch_batch_np(const CostArgs* args, const uint32_t* first, int count, uint32_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL((cost_batch_kernel<NP, U16, W>), dim3(blocks), dim3(kCostThreads), 0, s, args, first, count);
+    return hipGetLastError();
+}
+
+// Calls f.run<NP, U16, W>() with enough planes for counts up to `clauses`.
+template <typename F>
+hipError_t cost_dispatch(int dtype, int clauses, int words, F&& f) {
+    const int need = 32 - __builtin_clz((unsigned)clauses | 1u);
+    auto by_words = [&](auto np, auto u16) {
+        return words == 4 ? f(np, u16, std::integral_constant<int, 4>{}) : f(np, u16, std::integral_constant<int, 1>{});
+    };
+    if (dtype == 1) {
+        if (need <= 6) return by_words(std::integral_constant<int, 6>{}, std::false_type{});
+        return by_words(std::integral_constant<int, 8>{}, std::false_type{});
+    }
+    if (need <= 12) return by_words(std::integral_constant<int, 12>{}, std::true_type{});
+    return by_words(std::integral_constant<int, 16>{}, std::true_type{});
 }
 
 }  // namespace
 
-hipError_t launch_cost(const CostArgs& a, int dtype, bool wide, hipStream_t s) {
-    // Enough planes to count up to the number of (normalised) clauses.
-    const int need = 32 - __builtin_clz((unsigned)a.num_clauses | 1u);
-    if (dtype == 1) {
-        if (need <= 6) return launch_np<6, false>(a, wide, s);
-        return launch_np<8, false>(a, wide, s);
-    }
-    if (need <= 12) return launch_np<12, true>(a, wide, s);
-    return launch_np<16, true>(a, wide, s);
+hipError_t launch_cost(const CostArgs& a, int dtype, hipStream_t s) {
+    return cost_dispatch(dtype, a.num_clauses, cost_words(1ull << a.n), [&](auto np, auto u16, auto w) {
+        return launch_np<np.value, u16.value, w.value>(a, s);
+    });
 }
 
 hipError_t launch_prologue(const PrologueArgs& a, int dtype, hipStream_t s) {
@@ -301,19 +457,10 @@ hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint3
 }
 
 hipError_t launch_cost_batch(const CostArgs* args, const uint32_t* first, int count, uint32_t blocks, int dtype,
-                             int max_clauses, bool wide, hipStream_t s) {
-    const int need = 32 - __builtin_clz((unsigned)max_clauses | 1u);
-    if (dtype == 1) {
-        if (wide) hipLaunchKernelGGL((cost_batch_kernel<8, true, false>), dim3(blocks), dim3(256), 0, s, args, first, count);
-        else hipLaunchKernelGGL((cost_batch_kernel<8, false, false>), dim3(blocks), dim3(256), 0, s, args, first, count);
-    } else if (need <= 12) {
-        if (wide) hipLaunchKernelGGL((cost_batch_kernel<12, true, true>), dim3(blocks), dim3(256), 0, s, args, first, count);
-        else hipLaunchKernelGGL((cost_batch_kernel<12, false, true>), dim3(blocks), dim3(256), 0, s, args, first, count);
-    } else {
-        if (wide) hipLaunchKernelGGL((cost_batch_kernel<16, true, true>), dim3(blocks), dim3(256), 0, s, args, first, count);
-        else hipLaunchKernelGGL((cost_batch_kernel<16, false, true>), dim3(blocks), dim3(256), 0, s, args, first, count);
-    }
-    return hipGetLastError();
+                             int max_clauses, int words, hipStream_t s) {
+    return cost_dispatch(dtype, max_clauses, words, [&](auto np, auto u16, auto w) {
+        return launch_batch_np<np.value, u16.value, w.value>(args, first, count, blocks, s);
+    });
 }
 
 }  // namespace qnae

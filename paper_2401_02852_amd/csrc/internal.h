@@ -27,20 +27,26 @@ struct ClauseRec {
 struct CostArgs {
     const ClauseRec* clauses;
     int32_t num_clauses;
-    int32_t num_low;            // records 0 .. num_low-1 have a variable below 5; the rest only higher ones
     int32_t n;
     void* cost;                 // uint8 or uint16 [2^n]
     unsigned long long* zeros;  // optional counter of states with cost 0
 };
 
-// C(x) for x < 2^a.n. wide: clause variables reach index 32 or above
-// (64-bit pattern compares), required when any variable is >= 32.
-hipError_t launch_cost(const CostArgs& a, int dtype, bool wide, hipStream_t s);
-// Many diagonals of one cost type: instance i owns 256-thread blocks
-// first[i] .. first[i+1]-1 (32 states per thread). max_clauses bounds every
-// instance's clause count; wide when some instance has n > 32.
+// C(x) for x < 2^a.n.
+hipError_t launch_cost(const CostArgs& a, int dtype, hipStream_t s);
+// Runs of 32 states a thread counts, for this many states in one launch: four
+// share the work per clause, once that leaves enough waves to fill the chip.
+inline int cost_words(uint64_t states) { return states >= (1ull << 24) ? 4 : 1; }
+// 256-thread blocks of a diagonal of 2^n states.
+inline uint32_t cost_blocks(int n, int words) {
+    const int bits = words == 4 ? 15 : 13;  // states of a block
+    return n > bits ? 1u << (n - bits) : 1u;
+}
+// Many diagonals of one cost type: instance i owns blocks first[i] ..
+// first[i+1]-1, cost_blocks(n, words) of them. max_clauses bounds every
+// instance's clause count.
 hipError_t launch_cost_batch(const CostArgs* args, const uint32_t* first, int count, uint32_t blocks, int dtype,
-                             int max_clauses, bool wide, hipStream_t s);
+                             int max_clauses, int words, hipStream_t s);
 
 // Launch ahead of a run: copies `copies` 16-byte pieces from src (pinned host
 // memory) to dst and, with a cost (of `quads` >= 2 16-byte pieces), checks the

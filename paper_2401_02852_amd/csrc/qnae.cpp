@@ -111,8 +111,7 @@ int build_cost(qnae_ctx* ctx, const int32_t* clauses, int32_t m, int32_t n, int3
 
     HIP_TRY(ctx->h_clauses.reserve(sizeof(ClauseRec) * (size_t)(m > 0 ? m : 1)));
     ClauseRec* recs = (ClauseRec*)ctx->h_clauses.ptr;
-    int nlow = 0;
-    const int nrec = make_clause_records(clauses, m, k, recs, predicate, &nlow);
+    const int nrec = make_clause_records(clauses, m, k, recs, predicate);
     HIP_TRY(ctx->clauses.reserve(sizeof(ClauseRec) * (size_t)(nrec > 0 ? nrec : 1)));
     if (nrec > 0)
         HIP_TRY(hipMemcpyAsync(ctx->clauses.ptr, recs, sizeof(ClauseRec) * nrec, hipMemcpyHostToDevice, s));
@@ -122,12 +121,11 @@ int build_cost(qnae_ctx* ctx, const int32_t* clauses, int32_t m, int32_t n, int3
     qnae::CostArgs a;
     a.clauses = (const ClauseRec*)ctx->clauses.ptr;
     a.num_clauses = nrec;
-    a.num_low = nlow;
     a.n = states;
     a.cost = cost_dev;
     a.zeros = num_solutions ? zeros : nullptr;
     const double cost_bytes = (double)(cost_dtype == QNAE_U8 ? 1 : 2) * std::ldexp(1.0, states);
-    HIP_TRY(timed(ctx, K_COST, cost_bytes, s, [&] { return qnae::launch_cost(a, cost_dtype, n > 32, s); }));
+    HIP_TRY(timed(ctx, K_COST, cost_bytes, s, [&] { return qnae::launch_cost(a, cost_dtype, s); }));
     HIP_TRY(hipEventRecord(ctx->cost_staging_done, s));
     if (num_solutions) {
         HIP_TRY(hipMemcpyAsync(ctx->h_small.ptr, zeros, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));

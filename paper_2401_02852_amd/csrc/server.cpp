@@ -199,7 +199,7 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     struct New {
         Request* r;
         size_t rec_at, tab_at;
-        int nrec, nlow = 0;
+        int nrec;
         std::vector<ClauseRec> recs;
         std::vector<float2> tabs;
         std::vector<MixForm> forms;
@@ -210,7 +210,7 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
         New& w = nw[i];
         w.r = &r;
         w.recs.resize((size_t)std::max(r.m, 1));
-        w.nrec = make_clause_records(r.clauses.data(), r.m, r.k, w.recs.data(), QNAE_PRED_NAE, &w.nlow);
+        w.nrec = make_clause_records(r.clauses.data(), r.m, r.k, w.recs.data(), QNAE_PRED_NAE);
         w.rec_at = B.take(sizeof(ClauseRec) * (size_t)std::max(w.nrec, 1));
         const int T = r.p > 0 ? r.p : 1;
         w.tabs.resize((size_t)T * (r.m + 1));
@@ -297,23 +297,21 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     }
     uint32_t cblocks[2] = {0, 0};
     int cmax[2] = {0, 0};
-    bool cwide[2] = {false, false};  // some clause variable at index 32 or above
+    uint64_t ctotal[2] = {0, 0};  // states
     for (int g = 0; g < 2; ++g) {
+        for (const New* w : cgroups[g]) ctotal[g] += 1ull << (w->r->n - (w->r->half ? 1 : 0));
         qnae::CostArgs* args = (qnae::CostArgs*)(h + cargs_at[g]);
         uint32_t* first = (uint32_t*)(h + cfirst_at[g]);
         for (size_t q = 0; q < cgroups[g].size(); ++q) {
             const New& w = *cgroups[g][q];
             args[q].clauses = (const ClauseRec*)(d + w.rec_at);
             args[q].num_clauses = w.nrec;
-            args[q].num_low = w.nlow;
             const int states = w.r->n - (w.r->half ? 1 : 0);  // half: the lower half of the diagonal
             args[q].n = states;
             args[q].cost = pool + w.r->cost_off;
             args[q].zeros = nullptr;
             first[q] = cblocks[g];
-            cwide[g] = cwide[g] || w.r->n > 32;
-            const uint64_t threads = states >= 5 ? (1ull << (states - 5)) : 1ull;
-            cblocks[g] += (uint32_t)((threads + 255) / 256);
+            cblocks[g] += qnae::cost_blocks(states, qnae::cost_words(ctotal[g]));
             cmax[g] = std::max(cmax[g], w.nrec);
         }
         first[cgroups[g].size()] = cblocks[g];
@@ -369,7 +367,8 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     for (int g = 0; g < 2; ++g) {
         if (cgroups[g].empty()) continue;
         HIP_TRY(qnae::launch_cost_batch((const qnae::CostArgs*)(d + cargs_at[g]), (const uint32_t*)(d + cfirst_at[g]),
-                                        (int)cgroups[g].size(), cblocks[g], g ? QNAE_U16 : QNAE_U8, cmax[g], cwide[g], s));
+                                        (int)cgroups[g].size(), cblocks[g], g ? QNAE_U16 : QNAE_U8, cmax[g],
+                                        qnae::cost_words(ctotal[g]), s));
         ++launches;
     }
     for (int g = 0; g < 2; ++g) {
