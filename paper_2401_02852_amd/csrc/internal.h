@@ -264,13 +264,17 @@ hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, doub
 
 constexpr int kSampleTileBits = 12;
 constexpr int kSampleChunks = 1024;  // tile-prefix chunks
-// Draw `count` outcomes of psi (2^n complex64) for the given uniforms in
-// [0, 1): mass (ceil(2^n / 4096) doubles), pref (one more) and chunk
-// (kSampleChunks doubles) are scratch. out[q] = ~0 marks a zero state.
-// out_cost, if not null, receives C at each outcome (or -1 without a cost
-// diagonal).
-hipError_t launch_sample(const float2* psi, int n, const void* cost, int cost_dtype, const double* uniforms,
-                         int count, double* mass, double* pref, double* chunk, uint64_t* out, int32_t* out_cost,
-                         hipStream_t s);
+constexpr int kSampleSegs = 16;      // segments of a tile
+// Prefix sums of psi (2^n complex64) at tile, chunk and segment level: mass
+// (ceil(2^n / 4096) doubles), pref (one more), seg (kSampleSegs per tile) and
+// chunk (kSampleChunks doubles).
+hipError_t launch_sample_prefix(const float2* psi, int n, double* mass, double* pref, double* seg, double* chunk,
+                                hipStream_t s);
+// `count` outcomes for the given uniforms in [0, 1) from those. out[q] = ~0
+// marks a zero state. out_cost, if not null, receives C at each outcome (or -1
+// without a cost diagonal).
+hipError_t launch_sample_draws(const float2* psi, int n, const void* cost, int cost_dtype, const double* uniforms,
+                               int count, const double* mass, const double* pref, const double* seg, uint64_t* out,
+                               int32_t* out_cost, hipStream_t s);
 
 }  // namespace qnae

@@ -19,7 +19,9 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
     if (count > 0 && (!uniforms || !samples)) return fail(QNAE_EINVAL, "null uniforms or samples");
     if (cost_dev && cost_dtype != QNAE_U8 && cost_dtype != QNAE_U16)
         return fail(QNAE_EINVAL, "cost_dtype=%d is not QNAE_U8/QNAE_U16", cost_dtype);
-    for (int q = 0; q < count; ++q)
+    int bad = 0;  // (no exit from the loop, so that it is vectorised)
+    for (int q = 0; q < count; ++q) bad |= !(uniforms[q] >= 0.0 && uniforms[q] < 1.0);
+    for (int q = 0; bad && q < count; ++q)
         if (!(uniforms[q] >= 0.0 && uniforms[q] < 1.0))
             return fail(QNAE_EINVAL, "uniforms[%d]=%g outside [0, 1)", q, uniforms[q]);
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
@@ -29,6 +31,7 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
     const size_t mass_at = B.take(sizeof(double) * T);
     const size_t pref_at = B.take(sizeof(double) * (T + 1));
     const size_t chunk_at = B.take(sizeof(double) * qnae::kSampleChunks);
+    const size_t seg_at = B.take(sizeof(double) * T * qnae::kSampleSegs);
     const size_t u_at = B.take(sizeof(double) * (size_t)count);
     const size_t out_at = B.take(sizeof(uint64_t) * (size_t)count);
     const size_t cost_at = B.take(sizeof(int32_t) * (size_t)count);
@@ -36,15 +39,18 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
     HIP_TRY(ctx->h_sample.reserve(B.size - u_at));
     char* d = (char*)ctx->s_dev.ptr;
     char* h = (char*)ctx->h_sample.ptr;  // mirrors the blob from u_at on
+    // the uniforms are staged while the prefix pass runs
+    const float2* const psi = (const float2*)state_dev;
+    double *const mass = (double*)(d + mass_at), *const pref = (double*)(d + pref_at), *const seg = (double*)(d + seg_at);
+    HIP_TRY(qnae::launch_sample_prefix(psi, n, mass, pref, seg, (double*)(d + chunk_at), s));
     if (count > 0) {
         std::memcpy(h, uniforms, sizeof(double) * (size_t)count);
         HIP_TRY(hipMemcpyAsync(d + u_at, h, sizeof(double) * (size_t)count, hipMemcpyHostToDevice, s));
-    }
-    HIP_TRY(qnae::launch_sample((const float2*)state_dev, n, cost_dev, cost_dtype, (const double*)(d + u_at), count,
-                                (double*)(d + mass_at), (double*)(d + pref_at), (double*)(d + chunk_at), (uint64_t*)(d + out_at),
-                                sample_costs ? (int32_t*)(d + cost_at) : nullptr, s));
-    if (count > 0)
+        HIP_TRY(qnae::launch_sample_draws(psi, n, cost_dev, cost_dtype, (const double*)(d + u_at), count, mass, pref,
+                                          seg, (uint64_t*)(d + out_at),
+                                          sample_costs ? (int32_t*)(d + cost_at) : nullptr, s));
         HIP_TRY(hipMemcpyAsync(h + (out_at - u_at), d + out_at, B.size - out_at, hipMemcpyDeviceToHost, s));
+    }
     HIP_TRY(hipStreamSynchronize(s));
     if (count == 0) return QNAE_OK;
     const uint64_t* o = (const uint64_t*)(h + (out_at - u_at));

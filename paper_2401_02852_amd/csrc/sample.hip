@@ -6,19 +6,25 @@
 // order: the outcome for a uniform u is the smallest x whose cumulative mass
 // exceeds u times the total. The cumulative distribution is never stored per
 // amplitude; it is kept at three levels of prefix sums from zero:
-//   chunk level  C[i]: sequential sums of chunk masses (one thread);
+//   chunk level  C[i]: sums of chunk masses, sequential within groups of 32
+//                chunks and over the groups;
 //   tile level   P[t] = C[i] + (sequential sum of the tile masses before t in
 //                its chunk), tiles of 4096 consecutive amplitudes;
-//   inside a tile: per-thread sums of 16 consecutive probabilities, their
-//                block-wide exclusive scan, then a walk over the 16.
+//   segments     S[k]: where each 256 amplitudes start in their tile (sums of
+//                16 consecutive probabilities, their block-wide exclusive scan).
 // The first two are nondecreasing by construction (sequential sums of
 // nonnegative terms, and FP64 addition of a fixed offset is monotone). The
 // in-tile scan is a shuffle tree whose rounding may differ from a sequential
-// sum, so a draw takes the highest thread with mass whose start is at or below
-// its remainder and, if rounding carries the remainder past that thread's
-// walk, the thread's last nonzero probability. A draw finds its tile by binary
-// search over P, then its thread, then its amplitude. Probabilities are FP32
-// |psi|^2, sums FP64.
+// sum, so a draw takes the highest segment with mass whose start is at or below
+// its remainder, in it the highest lane of four amplitudes likewise and, if
+// rounding carries the remainder past that lane's walk, the lane's last nonzero
+// probability. Probabilities are FP32 |psi|^2, sums FP64.
+//
+// A draw is one wave: a 64-way search over P (three or four loads in a row
+// instead of a binary search's 14 to 22), the 16 starts of the tile (one cache
+// line, written by the pass that sums the tiles, 0.4% more bytes there), and one
+// segment of 2 KiB. Rescanning the whole 32 KiB tile per draw had made 100 000
+// draws at n = 26 move 3.2 GB: 420 us.
 #include "internal.h"
 
 namespace qnae {
@@ -32,7 +38,6 @@ constexpr int kPer = kTile / 256;            // per thread, consecutive
 __device__ __forceinline__ uint32_t pad(uint32_t e) { return e + (e >> 4); }
 
 struct TileScan {
-    double mine;   // this thread's 16 probabilities summed in order
     double excl;   // sum of the lower threads' sums (block-wide exclusive scan)
     double total;  // sum of the four wave totals in wave order
 };
@@ -78,18 +83,21 @@ __device__ TileScan tile_scan(const float2* __restrict__ psi, uint64_t N, uint64
     double woff = 0.0;
     for (uint32_t w = 0; w < wave; ++w) woff += wsum[w];
     TileScan r;
-    r.mine = s;
     r.excl = woff + (lane ? prev : 0.0);
     r.total = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
     return r;
 }
 
+// Tile masses, and the segment starts of every tile.
+constexpr int kSeg = 256, kSegs = kTile / kSeg;  // amplitudes of a segment, segments of a tile
 __global__ __launch_bounds__(256) void tile_mass_kernel(const float2* __restrict__ psi, uint64_t N,
-                                                         double* __restrict__ mass) {
+                                                         double* __restrict__ mass, double* __restrict__ seg) {
     __shared__ float prob[kTile + kTile / 16];
     __shared__ double wsum[4];
     const TileScan r = tile_scan(psi, N, blockIdx.x, prob, wsum);
     if (threadIdx.x == 0) mass[blockIdx.x] = r.total;
+    constexpr uint32_t kThreadsPer = kSeg / kPer;
+    if (threadIdx.x % kThreadsPer == 0) seg[(uint64_t)blockIdx.x * kSegs + threadIdx.x / kThreadsPer] = r.excl;
 }
 
 // The tile level in three launches. Thread i of the first owns tiles
@@ -126,144 +134,158 @@ __global__ __launch_bounds__(64) void chunk_run_kernel(const double* __restrict_
     chunk_total[i] = run;
 }
 
-// The chunk level: C[0] = 0 and C[i+1] = C[i] + total[i] in chunk order, in
-// place over the totals, for the `used` = T / chunk chunks that hold tiles
-// (the others hold none and add nothing), and P[T] = C[used]. One wave stages
-// the totals in LDS; one thread adds them in order.
-__global__ __launch_bounds__(64) void chunk_offset_kernel(double* __restrict__ chunk_total, double* __restrict__ pref,
-                                                          uint32_t T, uint32_t used) {
-    __shared__ double c[kSampleChunks];
-    const uint32_t lane = threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < kSampleChunks / 64; ++j) c[lane + 64u * j] = chunk_total[lane + 64u * j];
+// The chunk and tile levels together: P[t] = C[t / chunk] + (prefix within the
+// chunk), one tile per thread, and P[T] = the total. Every workgroup forms C
+// for itself, 32 groups of 32 chunks: prefixes within the groups, 32 threads
+// at once, then over the groups (two chains of 32 additions; one thread over
+// all 1024 took 13 us and a launch of its own).
+constexpr int kGroup = 32;
+static_assert(kSampleChunks == kGroup * kGroup, "groups of chunks");
+__global__ __launch_bounds__(256) void chunk_add_kernel(double* __restrict__ pref,
+                                                        const double* __restrict__ chunk_total, uint32_t T,
+                                                        uint32_t chunk_bits) {
+    __shared__ double c[kSampleChunks + kGroup];  // one pad slot per group
+    __shared__ double g[kGroup + 1];
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i = tid; i < kSampleChunks; i += 256u) c[i + i / kGroup] = chunk_total[i];
     __syncthreads();
-    if (lane == 0) {
+    if (tid < kGroup) {
         double acc = 0.0;
-        uint32_t q = 0;
-        for (; q + kRun <= used; q += kRun) {
-            double v[kRun];
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) v[j] = c[q + j];
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) {
-                const double tj = v[j];
-                v[j] = acc;
-                acc += tj;
-            }
-#pragma unroll
-            for (int j = 0; j < kRun; ++j) c[q + j] = v[j];
+        for (int j = 0; j < kGroup; ++j) {
+            const uint32_t at = tid * (kGroup + 1) + j;
+            const double v = c[at];
+            c[at] = acc;
+            acc += v;
         }
-        for (; q < used; ++q) {
-            const double tq = c[q];
-            c[q] = acc;
-            acc += tq;
-        }
-        pref[T] = acc;
+        g[tid + 1] = acc;
     }
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kSampleChunks / 64; ++j) chunk_total[lane + 64u * j] = c[lane + 64u * j];
+    if (tid == 0) {
+        double acc = 0.0;
+        g[0] = 0.0;
+        for (int j = 1; j <= kGroup; ++j) {
+            acc += g[j];
+            g[j] = acc;
+        }
+    }
+    __syncthreads();
+    const uint32_t t = blockIdx.x * 256u + tid;
+    if (t < T) {
+        const uint32_t i = t >> chunk_bits;
+        pref[t] = (g[i / kGroup] + c[i + i / kGroup]) + pref[t];
+    }
+    if (t == 0) pref[T] = g[kGroup];
 }
 
-// P[t] = C[t / chunk] + (prefix within the chunk), one tile per thread.
-__global__ __launch_bounds__(256) void chunk_add_kernel(double* __restrict__ pref, const double* __restrict__ C,
-                                                        uint32_t T, uint32_t chunk_bits) {
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    if (t < T) pref[t] = C[t >> chunk_bits] + pref[t];
-}
-
-// One workgroup per draw.
+// One wave per draw, four to a workgroup.
 template <typename CT>
 __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ psi, uint64_t N,
                                                      const double* __restrict__ mass, const double* __restrict__ pref,
-                                                     uint32_t T, const double* __restrict__ uniforms,
+                                                     const double* __restrict__ seg, uint32_t T,
+                                                     const double* __restrict__ uniforms, uint32_t count,
                                                      const CT* __restrict__ cost, uint64_t* __restrict__ out,
                                                      int32_t* __restrict__ out_cost) {
-    __shared__ float prob[kTile + kTile / 16];
-    __shared__ double wsum[4];
-    __shared__ uint32_t s_tile;
-    __shared__ double s_r;
-    __shared__ uint32_t s_best[4];
-    const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t q =
+        blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (q >= count) return;
     const double total = pref[T];
     if (!(total > 0.0)) {  // zero state: reported to the host as an error
-        if (tid == 0) out[q] = ~0ull;
+        if (lane == 0) out[q] = ~0ull;
         return;
     }
-    if (tid == 0) {
-        const double target = uniforms[q] * total;
-        uint32_t lo = 0, hi = T - 1;  // largest t with P[t] <= target (P[0] = 0)
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo + 1) / 2;
-            if (pref[mid] <= target) lo = mid;
-            else hi = mid - 1;
-        }
-        while (lo > 0 && !(mass[lo] > 0.0)) --lo;  // only past the last nonzero tile
-        s_tile = lo;
-        s_r = target - pref[lo];
+    const double target = uniforms[q] * total;
+    // largest t with P[t] <= target (P[0] = 0): 64 places of the range at a time
+    uint32_t lo = 0, size = T;
+    while (size > 1) {
+        const uint32_t step = (size + 63u) / 64u;
+        const uint32_t t = lo + lane * step;
+        const uint64_t le = __ballot(lane * step < size && pref[min(t, T - 1u)] <= target);
+        const uint32_t k = (uint32_t)__popcll(le) - 1u;  // P is nondecreasing; place 0 is always at or below
+        size = min(step, size - k * step);
+        lo += k * step;
     }
-    __syncthreads();
-    const uint32_t tile = s_tile;
-    const double r = s_r;
-    const TileScan sc = tile_scan(psi, N, tile, prob, wsum);
-    // the highest thread with mass whose range starts at or below r
-    const bool ok = sc.mine > 0.0 && sc.excl <= r;
-    const uint64_t bal = __ballot(ok);
-    if (lane == 0) s_best[wave] = bal ? (wave << 6) + 63u - (uint32_t)__builtin_clzll(bal) : 0xffffffffu;
-    __syncthreads();
-    uint32_t best = 0xffffffffu;
-    for (int w = 3; w >= 0; --w)
-        if (s_best[w] != 0xffffffffu) {
-            best = s_best[w];
-            break;
+    while (lo > 0 && !(mass[lo] > 0.0)) --lo;  // only past the last nonzero tile
+    const double r = target - pref[lo];
+    // the highest segment of the tile that starts at or below r and has mass
+    const double start = seg[(uint64_t)lo * kSegs + (lane & (kSegs - 1))];
+    int k = 63 - __builtin_clzll(__ballot(lane < kSegs && start <= r));
+    for (;; --k) {
+        const double s0 = __shfl(start, k);
+        const uint64_t base = (uint64_t)lo * kTile + (uint64_t)k * kSeg + 4u * lane;
+        float p[4] = {0.f, 0.f, 0.f, 0.f};
+        if (base + 2 <= N) {  // (N is even; small states end inside the segment)
+            const float4 a = *(const float4*)(psi + base);
+            p[0] = fmaf(a.x, a.x, a.y * a.y);
+            p[1] = fmaf(a.z, a.z, a.w * a.w);
         }
-    if (tid != best) return;
-    double acc = sc.excl;
-    int pick = -1, last = -1;
-    for (int j = 0; j < kPer; ++j) {
-        const float p = prob[pad(kPer * tid + j)];
-        acc += (double)p;
-        if (p > 0.f) {
-            last = j;
-            if (acc > r) {
-                pick = j;
-                break;
+        if (base + 4 <= N) {
+            const float4 b = *(const float4*)(psi + base + 2);
+            p[2] = fmaf(b.x, b.x, b.y * b.y);
+            p[3] = fmaf(b.z, b.z, b.w * b.w);
+        }
+        const double mine = (((double)p[0] + (double)p[1]) + (double)p[2]) + (double)p[3];
+        double incl = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+            const double t = __shfl_up(incl, off);
+            if (lane >= (uint32_t)off) incl += t;
+        }
+        const double prev = __shfl_up(incl, 1);
+        const double excl = s0 + (lane ? prev : 0.0);
+        const uint64_t ok = __ballot(mine > 0.0 && excl <= r);
+        if (ok == 0ull && k > 0) continue;
+        if (ok != 0ull && lane == 63u - (uint32_t)__builtin_clzll(ok)) {
+            double acc = excl;
+            int pick = -1, last = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc += (double)p[j];
+                if (p[j] > 0.f && pick < 0) {
+                    last = j;
+                    if (acc > r) pick = j;
+                }
             }
+            const uint64_t x = base + (uint64_t)(pick < 0 ? last : pick);  // rounding put r past this lane's walk
+            out[q] = x;
+            if (out_cost) out_cost[q] = cost ? (int32_t)cost[x] : -1;
         }
+        break;
     }
-    if (pick < 0) pick = last;  // rounding put r past this thread's walk
-    const uint64_t x = (uint64_t)tile * kTile + (uint64_t)kPer * tid + (uint64_t)pick;
-    out[q] = x;
-    if (out_cost) out_cost[q] = cost ? (int32_t)cost[x] : -1;
 }
 
 }  // namespace
 
-hipError_t launch_sample(const float2* psi, int n, const void* cost, int cost_dtype, const double* uniforms,
-                         int count, double* mass, double* pref, double* chunk_scratch, uint64_t* out, int32_t* out_cost,
-                         hipStream_t s) {
+hipError_t launch_sample_prefix(const float2* psi, int n, double* mass, double* pref, double* seg,
+                                double* chunk_scratch, hipStream_t s) {
     const uint64_t N = 1ull << n;
     const uint32_t T = (uint32_t)((N + kTile - 1) / kTile);
-    hipLaunchKernelGGL(tile_mass_kernel, dim3(T), dim3(256), 0, s, psi, N, mass);
+    hipLaunchKernelGGL(tile_mass_kernel, dim3(T), dim3(256), 0, s, psi, N, mass, seg);
     if (hipError_t e = hipGetLastError()) return e;
     static_assert(kSampleChunks % 64 == 0 && kSampleChunks % kRun == 0, "chunk launch shape");
+    static_assert(kSegs == kSampleSegs, "room for the segment starts");
     const uint32_t chunk = (T + kSampleChunks - 1) / kSampleChunks;  // T is a power of two
     const uint32_t chunk_bits = (uint32_t)__builtin_ctz(chunk);
     hipLaunchKernelGGL(chunk_run_kernel, dim3(kSampleChunks / 64), dim3(64), 0, s, mass, pref, chunk_scratch, T,
                        chunk);
     if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(chunk_offset_kernel, dim3(1), dim3(64), 0, s, chunk_scratch, pref, T, T / chunk);
-    if (hipError_t e = hipGetLastError()) return e;
     hipLaunchKernelGGL(chunk_add_kernel, dim3((T + 255) / 256), dim3(256), 0, s, pref,
                        (const double*)chunk_scratch, T, chunk_bits);
-    if (hipError_t e = hipGetLastError()) return e;
-    if (count == 0) return hipSuccess;
+    return hipGetLastError();
+}
+
+hipError_t launch_sample_draws(const float2* psi, int n, const void* cost, int cost_dtype, const double* uniforms,
+                               int count, const double* mass, const double* pref, const double* seg, uint64_t* out,
+                               int32_t* out_cost, hipStream_t s) {
+    const uint64_t N = 1ull << n;
+    const uint32_t T = (uint32_t)((N + kTile - 1) / kTile);
+    if (count <= 0) return hipSuccess;
+    const dim3 grid(((uint32_t)count + 3u) / 4u), block(256);
     if (cost_dtype == 2)
-        hipLaunchKernelGGL(sample_kernel<uint16_t>, dim3((uint32_t)count), dim3(256), 0, s, psi, N, mass, pref, T,
-                           uniforms, (const uint16_t*)cost, out, out_cost);
+        hipLaunchKernelGGL(sample_kernel<uint16_t>, grid, block, 0, s, psi, N, mass, pref, seg, T, uniforms,
+                           (uint32_t)count, (const uint16_t*)cost, out, out_cost);
     else
-        hipLaunchKernelGGL(sample_kernel<uint8_t>, dim3((uint32_t)count), dim3(256), 0, s, psi, N, mass, pref, T,
-                           uniforms, (const uint8_t*)cost, out, out_cost);
+        hipLaunchKernelGGL(sample_kernel<uint8_t>, grid, block, 0, s, psi, N, mass, pref, seg, T, uniforms,
+                           (uint32_t)count, (const uint8_t*)cost, out, out_cost);
     return hipGetLastError();
 }
 
