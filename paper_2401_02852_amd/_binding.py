@@ -706,27 +706,28 @@ def qaoa_grad_batched(costs, ns, ms, gammas, betas, *, w_psucc: float = 1.0, w_e
     if not (len(ns) == len(ms) == len(gammas) == len(betas) == count):
         raise ValueError("argument lists differ in length")
     ctx = ctx or default_context()
+    G, goff, gcnt = _packed_angles(gammas, "gammas")
+    B, boff, bcnt = _packed_angles(betas, "betas")
+    bad = np.nonzero(gcnt != bcnt)[0]
+    if bad.size:
+        raise ValueError(f"instance {int(bad[0])}: gammas and betas must be 1-D of equal length")
+    nv = np.asarray(ns, dtype=np.int64).reshape(count)
+    if np.any(nv < 1) or np.any(nv > 34):
+        i = int(np.nonzero((nv < 1) | (nv > 34))[0][0])
+        raise ValueError(f"instance {i}: n={int(nv[i])} outside [1, 34]")
+    cost_ptr, codes = _device_buffers(costs, "costs", ctx, _cost_types(), np.left_shift(np.int64(1), nv))
+    dg, db = np.zeros(G.shape[0]), np.zeros(B.shape[0])
     jobs = (_CGradJob * count)()
-    keep, dgs, dbs = [], [], []
-    for i in range(count):
-        g = np.ascontiguousarray(np.atleast_1d(np.asarray(gammas[i], dtype=np.float64)))
-        b = np.ascontiguousarray(np.atleast_1d(np.asarray(betas[i], dtype=np.float64)))
-        if g.shape != b.shape or g.ndim != 1:
-            raise ValueError(f"instance {i}: gammas and betas must be 1-D of equal length")
-        if not 1 <= int(ns[i]) <= 34:
-            raise ValueError(f"instance {i}: n={int(ns[i])} outside [1, 34]")
-        cptr = _device_buffer(costs[i], f"costs[{i}]", ctx, _cost_types(), 1 << int(ns[i]))
-        p = g.shape[0]
-        dg, db = np.zeros(p), np.zeros(p)
-        keep += [g, b]
-        dgs.append(dg)
-        dbs.append(db)
-        jobs[i].cost_dev = cptr
-        jobs[i].cost_dtype = _cost_code(costs[i])
-        jobs[i].n, jobs[i].m, jobs[i].p = int(ns[i]), int(ms[i]), p
-        if p:
-            jobs[i].gammas, jobs[i].betas = g.ctypes.data_as(_F64P), b.ctypes.data_as(_F64P)
-            jobs[i].dgammas, jobs[i].dbetas = dg.ctypes.data_as(_F64P), db.ctypes.data_as(_F64P)
+    v = _np_view(jobs, _CGradJob)
+    v["cost_dev"] = cost_ptr
+    v["cost_dtype"] = codes
+    v["n"] = nv
+    v["m"] = np.asarray(ms, dtype=np.int64).reshape(count)
+    v["p"] = gcnt
+    for field, buf, off in (("gammas", G, goff), ("betas", B, boff), ("dgammas", dg, goff), ("dbetas", db, boff)):
+        v[field] = np.where(gcnt > 0, np.uint64(buf.ctypes.data) + np.uint64(8) * off, np.uint64(0))
+    ends = np.cumsum(gcnt)[:-1]
+    dgs, dbs = (np.split(x[:int(gcnt.sum())], ends) if count else [] for x in (dg, db))
     res = (_CResult * max(count, 1))()
     _check(load_library().qnae_qaoa_grad_batched(ctx.handle, jobs, count, float(w_psucc), float(w_energy),
                                                  int(checkpoint_every), res, _stream(stream)))

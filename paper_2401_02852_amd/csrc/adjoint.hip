@@ -519,28 +519,67 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
 // the LDS latency.
 constexpr int kResidentGradThreads = 1024;
 
-// Pairs (x, x | 2^j) of bit j over the resident states: first Im<l|X_j|p>
-// (when l != null) then a' = c a - i s b on every state given.
-__device__ __forceinline__ float resident_bit(float2* l, float2* p, uint32_t N, int j, float c, float s) {
+// LDS slot of element x: one pad slot per 16, so that threads that hold runs
+// of four or eight elements fall in different banks.
+__device__ __forceinline__ uint32_t gslot(uint32_t x) { return x + (x >> 4); }
+
+// NB consecutive bits from g0 of the resident states at once: a task holds the
+// 2^NB elements of one coset of p (and of l), and for each bit first sums
+// Im<l|X_j|p> (REV), then applies a' = c a - i s b. Three bits a pass touch
+// LDS a third as often as one, and need a third of the barriers.
+template <int NB, bool REV>
+__device__ __forceinline__ float resident_pass(float2* l, float2* p, uint32_t N, int g0, float c, float s) {
+    constexpr int K = 1 << NB;
     float acc = 0.f;
-    const uint32_t bit = 1u << j;
-    for (uint32_t task = threadIdx.x; task < N / 2; task += kResidentGradThreads) {
-        const uint32_t x = ((task >> j) << (j + 1)) | (task & (bit - 1u));
-        const uint32_t y = x | bit;
-        const float2 pa = p[x], pb = p[y];
-        if (l) {
-            const float2 la = l[x], lb = l[y];
-            acc = fmaf(la.x, pb.y, acc);
-            acc = fmaf(-la.y, pb.x, acc);
-            acc = fmaf(lb.x, pa.y, acc);
-            acc = fmaf(-lb.y, pa.x, acc);
-            l[x] = make_float2(fmaf(c, la.x, s * lb.y), fmaf(c, la.y, -s * lb.x));
-            l[y] = make_float2(fmaf(c, lb.x, s * la.y), fmaf(c, lb.y, -s * la.x));
+    for (uint32_t task = threadIdx.x; task < (N >> NB); task += kResidentGradThreads) {
+        const uint32_t b = ((task >> g0) << (g0 + NB)) | (task & ((1u << g0) - 1u));
+        float2 pv[K], lv[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t at = gslot(b | ((uint32_t)i << g0));
+            pv[i] = p[at];
+            if (REV) lv[i] = l[at];
         }
-        p[x] = make_float2(fmaf(c, pa.x, s * pb.y), fmaf(c, pa.y, -s * pb.x));
-        p[y] = make_float2(fmaf(c, pb.x, s * pa.y), fmaf(c, pb.y, -s * pa.x));
+        auto rotate = [&](float2& x, float2& y) {
+            const float2 u = x, w = y;
+            x = make_float2(fmaf(c, u.x, s * w.y), fmaf(c, u.y, -s * w.x));
+            y = make_float2(fmaf(c, w.x, s * u.y), fmaf(c, w.y, -s * u.x));
+        };
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                if (i & (1 << q)) continue;
+                const int k = i | (1 << q);
+                if (REV) {
+                    acc = fmaf(lv[i].x, pv[k].y, acc);
+                    acc = fmaf(-lv[i].y, pv[k].x, acc);
+                    acc = fmaf(lv[k].x, pv[i].y, acc);
+                    acc = fmaf(-lv[k].y, pv[i].x, acc);
+                    rotate(lv[i], lv[k]);
+                }
+                rotate(pv[i], pv[k]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t at = gslot(b | ((uint32_t)i << g0));
+            p[at] = pv[i];
+            if (REV) l[at] = lv[i];
+        }
     }
     __syncthreads();
+    return acc;
+}
+
+// Every bit of a layer's mixer.
+template <bool REV>
+__device__ __forceinline__ float resident_layer(float2* l, float2* p, uint32_t N, int n, float c, float s) {
+    float acc = 0.f;
+    int g = 0;
+    for (; g + 3 <= n; g += 3) acc += resident_pass<3, REV>(l, p, N, g, c, s);
+    if (n - g == 2) acc += resident_pass<2, REV>(l, p, N, g, c, s);
+    else if (n - g == 1) acc += resident_pass<1, REV>(l, p, N, g, c, s);
     return acc;
 }
 
@@ -557,8 +596,8 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 
 template <typename CT>
 __device__ __forceinline__ void resident_grad_body(const ResidentGradArgs& a) {
-    __shared__ float2 ls[1 << 13];
-    __shared__ float2 ps[1 << 13];
+    __shared__ float2 ls[(1 << 13) + (1 << 9)];
+    __shared__ float2 ps[(1 << 13) + (1 << 9)];
     __shared__ double red[kResidentGradThreads / 64];
     constexpr uint32_t NT = kResidentGradThreads;
     const int n = a.n;
@@ -572,30 +611,30 @@ __device__ __forceinline__ void resident_grad_body(const ResidentGradArgs& a) {
         const float2* lut = a.luts + (size_t)l * a.lut_len;
         for (uint32_t x = tid; x < N; x += NT) {
             const float2 e = lut[min((uint32_t)cost[x], last)];
-            ps[x] = l == 0 ? make_float2(amp * e.x, amp * e.y) : cmul(ps[x], e);
+            ps[gslot(x)] = l == 0 ? make_float2(amp * e.x, amp * e.y) : cmul(ps[gslot(x)], e);
         }
         __syncthreads();
         const float2 cs = a.cs[l];
-        for (int j = 0; j < n; ++j) resident_bit(nullptr, ps, N, j, cs.x, cs.y);
+        resident_layer<false>(nullptr, ps, N, n, cs.x, cs.y);
         if ((l + 1) % a.every == 0 && l + 1 < a.p) {
             float2* ck = a.ckpt + (size_t)((l + 1) / a.every - 1) * N;
-            for (uint32_t x = tid; x < N; x += NT) ck[x] = ps[x];
+            for (uint32_t x = tid; x < N; x += NT) ck[x] = ps[gslot(x)];
         }
     }
     if (a.p == 0)
-        for (uint32_t x = tid; x < N; x += NT) ps[x] = make_float2(amp, 0.f);
+        for (uint32_t x = tid; x < N; x += NT) ps[gslot(x)] = make_float2(amp, 0.f);
     __syncthreads();
     // readout and lam = W psi
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     for (uint32_t x = tid; x < N; x += NT) {
-        const float2 v = ps[x];
+        const float2 v = ps[gslot(x)];
         const uint32_t c = cost[x];
         const float pr = fmaf(v.x, v.x, v.y * v.y);
         s2 += pr;
         s1 += (double)c * pr;
         s0 += c == 0u ? pr : 0.0;
         const float w = (float)a.w_energy * (float)c + (c == 0u ? (float)a.w_psucc : 0.f);
-        ls[x] = make_float2(w * v.x, w * v.y);
+        ls[gslot(x)] = make_float2(w * v.x, w * v.y);
     }
     s0 = block_sum(s0, red);
     s1 = block_sum(s1, red);
@@ -609,18 +648,17 @@ __device__ __forceinline__ void resident_grad_body(const ResidentGradArgs& a) {
     // reverse
     for (int l = a.p - 1; l >= 0; --l) {
         const float2 cs = a.cs[l];
-        float accb = 0.f;
-        for (int j = 0; j < n; ++j) accb += resident_bit(ls, ps, N, j, cs.x, -cs.y);
+        const float accb = resident_layer<true>(ls, ps, N, n, cs.x, -cs.y);
         const float2* lut = a.luts + (size_t)l * a.lut_len;
         float accg = 0.f;
         for (uint32_t x = tid; x < N; x += NT) {
             const uint32_t c = cost[x];
-            const float2 lv = ls[x], pv = ps[x];
+            const float2 lv = ls[gslot(x)], pv = ps[gslot(x)];
             accg = fmaf((float)c, fmaf(lv.x, pv.y, -lv.y * pv.x), accg);
             const float2 e = lut[min(c, last)];
             const float2 ec = make_float2(e.x, -e.y);
-            ls[x] = cmul(lv, ec);
-            ps[x] = cmul(pv, ec);
+            ls[gslot(x)] = cmul(lv, ec);
+            ps[gslot(x)] = cmul(pv, ec);
         }
         const double db = block_sum((double)accb, red);
         const double dg = block_sum((double)accg, red);
@@ -630,18 +668,13 @@ __device__ __forceinline__ void resident_grad_body(const ResidentGradArgs& a) {
         }
         if (l % a.every == 0 && l > 0) {
             const float2* ck = a.ckpt + (size_t)(l / a.every - 1) * N;
-            for (uint32_t x = tid; x < N; x += NT) ps[x] = ck[x];
+            for (uint32_t x = tid; x < N; x += NT) ps[gslot(x)] = ck[x];
         }
         __syncthreads();
     }
 }
 
-template <typename CT>
-__global__ __launch_bounds__(kResidentGradThreads) void resident_grad_kernel(const ResidentGradArgs a) {
-    resident_grad_body<CT>(a);
-}
-
-// Many small gradients, one workgroup each.
+// One workgroup per gradient.
 template <typename CT>
 __global__ __launch_bounds__(kResidentGradThreads) void resident_grad_batch_kernel(const ResidentGradArgs* args) {
     const ResidentGradArgs a = args[blockIdx.x];
@@ -704,14 +737,6 @@ hipError_t launch_resident_grad_batch(int dtype, const ResidentGradArgs* args, i
     else
         hipLaunchKernelGGL(resident_grad_batch_kernel<uint16_t>, dim3((uint32_t)count), dim3(kResidentGradThreads), 0, s,
                            args);
-    return hipGetLastError();
-}
-
-hipError_t launch_resident_grad(int dtype, const ResidentGradArgs& a, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL(resident_grad_kernel<uint8_t>, dim3(1), dim3(kResidentGradThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(resident_grad_kernel<uint16_t>, dim3(1), dim3(kResidentGradThreads), 0, s, a);
     return hipGetLastError();
 }
 

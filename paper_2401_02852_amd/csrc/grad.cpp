@@ -22,6 +22,102 @@ using namespace qnae_host;
 using qnae::MixForm;
 using qnae::SweepArgs;
 
+namespace {
+
+// The gradients of the jobs `pick` (n <= 13), one launch per cost type. Uploaded:
+// a record per phase table row, the (cos, sin) of the mixers and the kernel
+// arguments; the tables are built on the device, the results come back
+// through pinned memory that the kernels write.
+int resident_grads(qnae_ctx* ctx, const qnae_grad_job* jobs, const std::vector<int>& pick, double w_psucc,
+                   double w_energy, int every, qnae_result* out, hipStream_t s) {
+    Blob B, C, T;  // uploaded; checkpoints; tables
+    size_t rows = 0;
+    int max_m = 0;
+    std::vector<int> group[2];
+    for (int i : pick) {
+        rows += (size_t)jobs[i].p;
+        max_m = std::max(max_m, jobs[i].m);
+        group[jobs[i].cost_dtype == QNAE_U16 ? 1 : 0].push_back(i);
+    }
+    const size_t row_at = B.take(sizeof(qnae::PhaseRow) * rows);
+    const size_t cs_at = B.take(sizeof(float2) * rows);
+    size_t args_at[2];
+    for (int g = 0; g < 2; ++g) args_at[g] = B.take(sizeof(qnae::ResidentGradArgs) * group[g].size());
+    B.take(16);
+    const size_t out_at = B.take(sizeof(double) * (3 * pick.size() + 2 * rows));  // pinned only
+    for (int i : pick) {
+        const int nck = jobs[i].p > 1 ? (jobs[i].p - 1) / every : 0;
+        C.take(sizeof(float2) * ((size_t)1 << jobs[i].n) * (size_t)std::max(nck, 1));
+        T.take(sizeof(float2) * (size_t)std::max(jobs[i].p, 1) * (size_t)(jobs[i].m + 1));
+    }
+    HIP_TRY(ctx->h_blob.reserve(B.size));
+    HIP_TRY(ctx->g_blob.reserve(B.size));
+    HIP_TRY(ctx->g_states.reserve(C.size));
+    HIP_TRY(ctx->g_tables.reserve(T.size));
+    char* const h = (char*)ctx->h_blob.ptr;
+    char* const d = (char*)ctx->g_blob.ptr;
+    qnae::PhaseRow* const hr = (qnae::PhaseRow*)(h + row_at);
+    float2* const hc = (float2*)(h + cs_at);
+    double* const ho = (double*)(h + out_at);
+    Blob ck, tab;
+    size_t row = 0, at[2] = {0, 0}, res = 0;
+    for (int i : pick) {
+        const qnae_grad_job& j = jobs[i];
+        const int nck = j.p > 1 ? (j.p - 1) / every : 0;
+        const size_t N = (size_t)1 << j.n, ck_at = ck.take(sizeof(float2) * N * (size_t)std::max(nck, 1));
+        const size_t tab_at = tab.take(sizeof(float2) * (size_t)std::max(j.p, 1) * (size_t)(j.m + 1));
+        float2* const tables = (float2*)((char*)ctx->g_tables.ptr + tab_at);
+        const int g = j.cost_dtype == QNAE_U16 ? 1 : 0;
+        qnae::ResidentGradArgs& a = ((qnae::ResidentGradArgs*)(h + args_at[g]))[at[g]++];
+        a.cost = j.cost_dev;
+        a.luts = tables;
+        a.cs = (const float2*)(d + cs_at) + row;
+        a.ckpt = (float2*)((char*)ctx->g_states.ptr + ck_at);
+        a.out = ho + res;
+        a.w_psucc = w_psucc;
+        a.w_energy = w_energy;
+        a.n = j.n;
+        a.p = j.p;
+        a.lut_len = j.m + 1;
+        a.every = every;
+        res += 3 + 2 * (size_t)j.p;
+        for (int l = 0; l < j.p; ++l, ++row) {
+            hr[row] = {j.gammas[l], 1.0, 0.0, -1.0, tables + (size_t)l * (size_t)(j.m + 1), j.m, 0};
+            hc[row] = make_float2((float)std::cos(j.betas[l]), (float)std::sin(j.betas[l]));
+        }
+    }
+    if (int rc = prologue(ctx, d, h, args_at[1] + sizeof(qnae::ResidentGradArgs) * group[1].size(), nullptr, QNAE_U8, 0,
+                          s))
+        return rc;
+    HIP_TRY(qnae::launch_phase_rows((const qnae::PhaseRow*)(d + row_at), (int)rows, max_m, s));
+    for (int g = 0; g < 2; ++g) {
+        if (group[g].empty()) continue;
+        double bytes = 0.0;
+        for (int i : group[g]) bytes += std::ldexp(3.0 * jobs[i].p, jobs[i].n);
+        HIP_TRY(timed(ctx, K_RESIDENT, bytes, s, [&] {
+            return qnae::launch_resident_grad_batch(g ? QNAE_U16 : QNAE_U8,
+                                                    (const qnae::ResidentGradArgs*)(d + args_at[g]),
+                                                    (int)group[g].size(), s);
+        }));
+    }
+    HIP_TRY(hipStreamSynchronize(s));
+    const double* r = ho;
+    for (int i : pick) {
+        const qnae_grad_job& j = jobs[i];
+        out[i].p_success = r[0];
+        out[i].expected_cost = r[1];
+        out[i].norm = r[2];
+        for (int l = 0; l < j.p; ++l) {
+            j.dgammas[l] = r[3 + l];
+            j.dbetas[l] = r[3 + j.p + l];
+        }
+        r += 3 + 2 * (size_t)j.p;
+    }
+    return QNAE_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int32_t n, int32_t m,
@@ -39,50 +135,8 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     const int lut_len = m + 1;
 
     if (n <= 13) {
-        const size_t N = (size_t)1 << n;
-        // tables: forward phases exp(-i gamma c) (unit), (cos b, sin b)
-        Blob B;
-        const size_t lut_at = B.take(sizeof(float2) * (size_t)(p > 0 ? p : 1) * lut_len);
-        const size_t cs_at = B.take(sizeof(float2) * (size_t)(p > 0 ? p : 1));
-        const size_t out_at = B.take(sizeof(double) * (3 + 2 * (size_t)p));
-        HIP_TRY(ctx->h_blob.reserve(B.size));
-        HIP_TRY(ctx->g_blob.reserve(B.size));
-        char* h = (char*)ctx->h_blob.ptr;
-        char* d = (char*)ctx->g_blob.ptr;
-        float2* lut = (float2*)(h + lut_at);
-        float2* cs = (float2*)(h + cs_at);
-        for (int l = 0; l < p; ++l) {
-            phase_row(gammas[l], m, 1.0, -1, lut + (size_t)l * lut_len);
-            cs[l] = make_float2((float)std::cos(betas[l]), (float)std::sin(betas[l]));
-        }
-        const int nck = p > 1 ? (p - 1) / every : 0;
-        HIP_TRY(ctx->g_states.reserve(sizeof(float2) * N * (size_t)(nck > 0 ? nck : 1)));
-        HIP_TRY(hipMemcpyAsync(d, h, out_at, hipMemcpyHostToDevice, s));
-        qnae::ResidentGradArgs a;
-        a.cost = cost_dev;
-        a.luts = (const float2*)(d + lut_at);
-        a.cs = (const float2*)(d + cs_at);
-        a.ckpt = (float2*)ctx->g_states.ptr;
-        a.out = (double*)(d + out_at);
-        a.w_psucc = w_psucc;
-        a.w_energy = w_energy;
-        a.n = n;
-        a.p = p;
-        a.lut_len = lut_len;
-        a.every = every;
-        HIP_TRY(timed(ctx, K_RESIDENT, std::ldexp(3.0 * p, n), s, [&] { return qnae::launch_resident_grad(cost_dtype, a, s); }));
-        HIP_TRY(hipMemcpyAsync(h + out_at, d + out_at, sizeof(double) * (3 + 2 * (size_t)p), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipEventRecord(ctx->staging_done, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        const double* r = (const double*)(h + out_at);
-        out->p_success = r[0];
-        out->expected_cost = r[1];
-        out->norm = r[2];
-        for (int l = 0; l < p; ++l) {
-            dgammas[l] = r[3 + l];
-            dbetas[l] = r[3 + p + l];
-        }
-        return QNAE_OK;
+        const qnae_grad_job job{cost_dev, cost_dtype, n, m, p, gammas, betas, dgammas, dbetas};
+        return resident_grads(ctx, &job, {0}, w_psucc, w_energy, every, out, s);
     }
 
     // ---- tiled path ----------------------------------------------------------
@@ -327,96 +381,11 @@ int qnae_qaoa_grad_batched(qnae_ctx* ctx, const qnae_grad_job* jobs, int32_t cou
     const int every = checkpoint_every > 0 ? checkpoint_every : 4;
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
-    // Small jobs: per job its tables and outputs in one blob, checkpoints in
-    // one device buffer, one launch per cost type.
-    Blob B, C;
-    std::vector<size_t> lut_at(count), cs_at(count), out_at(count), ck_at(count);
-    std::vector<int> small[2];
-    for (int i = 0; i < count; ++i) {
-        const qnae_grad_job& j = jobs[i];
-        if (j.n > 13) continue;
-        const int T = j.p > 0 ? j.p : 1;
-        lut_at[i] = B.take(sizeof(float2) * (size_t)T * (j.m + 1));
-        cs_at[i] = B.take(sizeof(float2) * (size_t)T);
-        out_at[i] = B.take(sizeof(double) * (3 + 2 * (size_t)j.p));
-        const int nck = j.p > 1 ? (j.p - 1) / every : 0;
-        ck_at[i] = C.take(sizeof(float2) * ((size_t)1 << j.n) * (size_t)(nck > 0 ? nck : 1));
-        small[j.cost_dtype == QNAE_U16 ? 1 : 0].push_back(i);
-    }
-    size_t args_at[2];
-    for (int g = 0; g < 2; ++g) args_at[g] = B.take(sizeof(qnae::ResidentGradArgs) * small[g].size());
-    if (!small[0].empty() || !small[1].empty()) {
-        HIP_TRY(ctx->h_blob.reserve(B.size));
-        HIP_TRY(ctx->g_blob.reserve(B.size));
-        HIP_TRY(ctx->g_states.reserve(C.size));
-        char* h = (char*)ctx->h_blob.ptr;
-        char* d = (char*)ctx->g_blob.ptr;
-        // Tables and arguments job by job, chunks of jobs over the context's
-        // host threads (each job writes only its own rows and argument slot).
-        std::vector<std::pair<int, int>> work;  // (cost type, position in its launch)
-        size_t entries = 0;
-        for (int g = 0; g < 2; ++g)
-            for (size_t q = 0; q < small[g].size(); ++q) {
-                work.emplace_back(g, (int)q);
-                entries += (size_t)jobs[small[g][q]].p * (size_t)(jobs[small[g][q]].m + 1);
-            }
-        constexpr int kChunk = 16;
-        parallel_for(ctx, ((int)work.size() + kChunk - 1) / kChunk, entries, [&](int chunk) {
-            const int w_end = std::min((int)work.size(), (chunk + 1) * kChunk);
-            for (int w = chunk * kChunk; w < w_end; ++w) {
-                const int g = work[w].first;
-                const size_t q = (size_t)work[w].second;
-                qnae::ResidentGradArgs* args = (qnae::ResidentGradArgs*)(h + args_at[g]);
-                const int i = small[g][q];
-                const qnae_grad_job& j = jobs[i];
-                const int lut_len = j.m + 1;
-                float2* lut = (float2*)(h + lut_at[i]);
-                float2* cs = (float2*)(h + cs_at[i]);
-                for (int l = 0; l < j.p; ++l) {
-                    phase_row(j.gammas[l], j.m, 1.0, -1, lut + (size_t)l * lut_len);
-                    cs[l] = make_float2((float)std::cos(j.betas[l]), (float)std::sin(j.betas[l]));
-                }
-                qnae::ResidentGradArgs& a = args[q];
-                a.cost = j.cost_dev;
-                a.luts = (const float2*)(d + lut_at[i]);
-                a.cs = (const float2*)(d + cs_at[i]);
-                a.ckpt = (float2*)((char*)ctx->g_states.ptr + ck_at[i]);
-                a.out = (double*)(d + out_at[i]);
-                a.w_psucc = w_psucc;
-                a.w_energy = w_energy;
-                a.n = j.n;
-                a.p = j.p;
-                a.lut_len = lut_len;
-                a.every = every;
-            }
-        });
-        HIP_TRY(hipMemcpyAsync(d, h, B.size, hipMemcpyHostToDevice, s));
-        for (int g = 0; g < 2; ++g) {
-            if (small[g].empty()) continue;
-            double bytes = 0.0;
-            for (int i : small[g]) bytes += std::ldexp(3.0 * jobs[i].p, jobs[i].n);
-            HIP_TRY(timed(ctx, K_RESIDENT, bytes, s, [&] {
-                return qnae::launch_resident_grad_batch(g ? QNAE_U16 : QNAE_U8,
-                                                         (const qnae::ResidentGradArgs*)(d + args_at[g]),
-                                                         (int)small[g].size(), s);
-            }));
-        }
-        HIP_TRY(hipMemcpyAsync(h, d, args_at[0], hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipEventRecord(ctx->staging_done, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        for (int g = 0; g < 2; ++g)
-            for (int i : small[g]) {
-                const qnae_grad_job& j = jobs[i];
-                const double* r = (const double*)(h + out_at[i]);
-                out[i].p_success = r[0];
-                out[i].expected_cost = r[1];
-                out[i].norm = r[2];
-                for (int l = 0; l < j.p; ++l) {
-                    j.dgammas[l] = r[3 + l];
-                    j.dbetas[l] = r[3 + j.p + l];
-                }
-            }
-    }
+    std::vector<int> small;
+    for (int i = 0; i < count; ++i)
+        if (jobs[i].n <= 13) small.push_back(i);
+    if (!small.empty())
+        if (int rc = resident_grads(ctx, jobs, small, w_psucc, w_energy, every, out, s)) return rc;
     // Large jobs: the tiled adjoint, one after another.
     for (int i = 0; i < count; ++i) {
         const qnae_grad_job& j = jobs[i];

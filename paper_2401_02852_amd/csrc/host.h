@@ -146,7 +146,7 @@ struct qnae_ctx {
     // batched path: uploaded tables and work lists, states, partial sums, results
     qnae_host::DevBuf b_blob, b_tabs, b_states, b_partials, b_results;
     // gradient: checkpoints + adjoint state, tables, partial sums
-    qnae_host::DevBuf g_states, g_blob, g_partials;
+    qnae_host::DevBuf g_states, g_blob, g_partials, g_tables;
     qnae_host::HostBuf h_blob, h_btabs, h_results;
     hipEvent_t staging_done = nullptr;  // last async copy out of pinned staging
     // plans of recent batch shapes, with their captured launch sequences (most recent last)

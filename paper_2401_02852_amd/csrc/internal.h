@@ -78,6 +78,14 @@ struct FlipJob {
 hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint32_t* flags, uint32_t* word,
                              uint32_t ticket, uint32_t* answer, hipStream_t s);
 
+// A phase table row: out[c] = (re + i im) exp(sign i g c), c = 0 .. m.
+struct PhaseRow {
+    double g, re, im, sign;
+    float2* out;
+    int32_t m, pad;
+};
+hipError_t launch_phase_rows(const PhaseRow* rows, int count, int max_m, hipStream_t s);
+
 // ---------------------------------------------------------------------------
 // State sweeps
 // ---------------------------------------------------------------------------
@@ -240,11 +248,10 @@ struct ResidentGradArgs {
     const float2* luts;    // p forward tables exp(-i gamma_l c)
     const float2* cs;      // p (cos beta_l, sin beta_l)
     float2* ckpt;          // (p - 1) / every states of 2^n
-    double* out;           // 3 readout sums, then dgamma[p], then dbeta[p]
+    double* out;           // pinned host memory: 3 readout sums, then dgamma[p], then dbeta[p]
     double w_psucc, w_energy;
     int32_t n, p, lut_len, every;
 };
-hipError_t launch_resident_grad(int dtype, const ResidentGradArgs& a, hipStream_t s);
 // One workgroup per entry of args (count entries, all of one cost type).
 hipError_t launch_resident_grad_batch(int dtype, const ResidentGradArgs* args, int count, hipStream_t s);
 hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, hipStream_t s);

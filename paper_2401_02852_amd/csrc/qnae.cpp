@@ -61,7 +61,7 @@ int qnae_destroy(qnae_ctx* ctx) try {
     for (DevBuf* b : {&ctx->state, &ctx->partials, &ctx->luts, &ctx->clauses, &ctx->small, &ctx->b_blob,
                       &ctx->b_tabs, &ctx->c_blob,
                       &ctx->b_states, &ctx->b_partials, &ctx->b_results, &ctx->g_states, &ctx->g_blob,
-                      &ctx->g_partials, &ctx->tune_cost, &ctx->s_dev, &ctx->f_jobs})
+                      &ctx->g_partials, &ctx->tune_cost, &ctx->s_dev, &ctx->f_jobs, &ctx->g_tables})
         b->release();
     for (HostBuf* b : {&ctx->h_luts, &ctx->h_clauses, &ctx->h_small, &ctx->h_blob, &ctx->h_results,
                        &ctx->h_sample, &ctx->na_host, &ctx->h_cblob, &ctx->h_flip, &ctx->h_btabs})
