@@ -384,7 +384,7 @@ inline bool op_virtual(const SweepPlan& P, const Op& op) {
     return P.half && P.groups[op.group].pos[P.TB - 1] == P.n - 1;
 }
 // Which sweeps of different plans share a launch: kind, cost type, virtual
-// bit, layout L1 and tile bits (fields compare in that order).
+// bit, layouts 2 and 3 and tile bits (fields compare in that order).
 struct SweepBucket {
     int kind, dtype;
     bool virt;

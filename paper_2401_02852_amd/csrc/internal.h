@@ -163,7 +163,8 @@ hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s);
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
                               uint32_t blocks, hipStream_t s, bool virt, int l1);
 // Does a launch of this kind over a group with these mix masks pass its tiles
-// through register layout L1? 1 yes, 2 no; 0: the kernel decides per tile.
+// through register layouts 2 and 3? 1 yes, 2 no. (A launch that holds one that does
+// passes every tile through it.)
 int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask);
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
 

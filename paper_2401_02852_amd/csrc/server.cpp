@@ -260,11 +260,7 @@ int qnae_server::tick(std::vector<Request*>& admitted) try {
     for (Request* r : large) {
         for (size_t k = 0; k < rounds && r->next_op + k < r->plan.ops.size(); ++k) {
             const Op& op = r->plan.ops[r->next_op + k];
-            // requests are at different sweeps of their plans: the kernel looks
-            // at layout L1 per tile rather than split the few there are
-            SweepBucket as = op_bucket(r->plan, op);
-            as.l1 = 0;
-            Launch& L = sweeps[k][as];
+            Launch& L = sweeps[k][op_bucket(r->plan, op)];
             L.members.push_back(r);
         }
         if (r->next_op + rounds >= r->plan.ops.size()) finishing.push_back(r);

@@ -28,7 +28,7 @@ import sys
 from collections import OrderedDict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/sweep.hip", "csrc/tile.h", "csrc/cost.hip"]
+KERNEL_SOURCES = ["csrc/sweep.hip", "csrc/sweep14.hip", "csrc/sweep_common.h", "csrc/tile.h", "csrc/cost.hip"]
 ADJOINT_SOURCES = ["csrc/adjoint.hip", "csrc/tile.h"]
 
 KIND_NAMES = {"0": "sweep_first", "1": "sweep_middle", "2": "sweep_boundary", "3": "sweep_final", "4": "sweep_p0"}
@@ -51,13 +51,17 @@ def _hash_lines():
 
 def short_name(name: str) -> str:
     name = re.sub(r"qnae::\(anonymous namespace\)::", "", name)
-    # (a sixth argument, whether the tiles pass through layout L1, is not
-    # shown: both variants of a kind move the same bytes and are summed)
-    m = re.match(r"void sweep_kernel<(\d+), ([a-z ]+), (\d)(?:, (true|false|\d))?(?:, (true|false))?(?:, \d)?>", name)
+    # (arguments past the fifth choose register layouts and transposes and are
+    # not shown: those variants of a kind move the same bytes and are summed)
+    m = re.match(r"void sweep_kernel<(\d+), ([a-z ]+), (\d)(?:, (true|false))?(?:, (true|false))?(?:, (?:\d|true|false))*>",
+                 name)
+    if not m:  # 14-bit tiles: cost type, kind, half, layout choice
+        m = re.match(r"void (sweep14)_kernel<([a-z ]+), (\d), (true|false), (?:true|false)>()", name)
     if m:
-        half = ",half" if m.group(4) in ("true", "1") else ""
+        tb = "14" if m.group(1) == "sweep14" else m.group(1)
+        half = ",half" if m.group(4) == "true" else ""
         ckpt = "_ckpt" if m.group(5) == "true" else ""
-        return (f"sweep_kernel<TB={m.group(1)},{m.group(2).replace('unsigned ', 'u')}{half}> "
+        return (f"sweep_kernel<TB={tb},{m.group(2).replace('unsigned ', 'u')}{half}> "
                 f"{KIND_NAMES[m.group(3)]}{ckpt}")
     m = re.match(r"void adjoint_kernel<([a-z ]+), (\d)(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?(?:, (true|false))?>",
                  name)
