@@ -273,14 +273,16 @@ hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, doub
 constexpr int kSampleTileBits = 12;
 constexpr int kSampleChunks = 1024;  // tile-prefix chunks
 constexpr int kSampleSegs = 16;      // segments of a tile
-// Prefix sums of psi (2^n complex64) at tile, chunk and segment level: mass
-// (ceil(2^n / 4096) doubles), pref (one more), seg (kSampleSegs per tile) and
-// chunk (kSampleChunks doubles).
-hipError_t launch_sample_prefix(const float2* psi, int n, double* mass, double* pref, double* seg, double* chunk,
-                                hipStream_t s);
-// `count` outcomes for the given uniforms in [0, 1) from those. out[q] = ~0
-// marks a zero state. out_cost, if not null, receives C at each outcome (or -1
-// without a cost diagonal).
+// Tile masses of psi (2^n complex64; ceil(2^n / 4096) doubles) and segment starts
+// (kSampleSegs per tile).
+hipError_t launch_sample_masses(const float2* psi, int n, double* mass, double* seg, hipStream_t s);
+// Their prefix sums: pref (one more than mass), chunk (kSampleChunks doubles of
+// scratch); also copies `count` uniforms from pinned u_host to u_dev.
+hipError_t launch_sample_prefix(int n, const double* mass, double* pref, double* chunk, const double* u_host,
+                                double* u_dev, int count, hipStream_t s);
+// `count` outcomes for the given uniforms in [0, 1) from those, to pinned host
+// memory. out[q] = ~0 marks a zero state. out_cost, if not null, receives C at
+// each outcome (or -1 without a cost diagonal).
 hipError_t launch_sample_draws(const float2* psi, int n, const void* cost, int cost_dtype, const double* uniforms,
                                int count, const double* mass, const double* pref, const double* seg, uint64_t* out,
                                int32_t* out_cost, hipStream_t s);

@@ -33,30 +33,32 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
     const size_t chunk_at = B.take(sizeof(double) * qnae::kSampleChunks);
     const size_t seg_at = B.take(sizeof(double) * T * qnae::kSampleSegs);
     const size_t u_at = B.take(sizeof(double) * (size_t)count);
-    const size_t out_at = B.take(sizeof(uint64_t) * (size_t)count);
-    const size_t cost_at = B.take(sizeof(int32_t) * (size_t)count);
+    Blob H;  // pinned: the uniforms on their way in, the outcomes and their costs
+    const size_t h_u = H.take(sizeof(double) * (size_t)count);
+    const size_t out_at = H.take(sizeof(uint64_t) * (size_t)count);
+    const size_t cost_at = H.take(sizeof(int32_t) * (size_t)count);
     HIP_TRY(ctx->s_dev.reserve(B.size));
-    HIP_TRY(ctx->h_sample.reserve(B.size - u_at));
+    HIP_TRY(ctx->h_sample.reserve(H.size));
     char* d = (char*)ctx->s_dev.ptr;
-    char* h = (char*)ctx->h_sample.ptr;  // mirrors the blob from u_at on
-    // the uniforms are staged while the prefix pass runs
+    char* h = (char*)ctx->h_sample.ptr;
+    // the uniforms are staged while the state is read; the outcomes are written to
+    // pinned memory, so no copy follows the draws
     const float2* const psi = (const float2*)state_dev;
     double *const mass = (double*)(d + mass_at), *const pref = (double*)(d + pref_at), *const seg = (double*)(d + seg_at);
-    HIP_TRY(qnae::launch_sample_prefix(psi, n, mass, pref, seg, (double*)(d + chunk_at), s));
-    if (count > 0) {
-        std::memcpy(h, uniforms, sizeof(double) * (size_t)count);
-        HIP_TRY(hipMemcpyAsync(d + u_at, h, sizeof(double) * (size_t)count, hipMemcpyHostToDevice, s));
-        HIP_TRY(qnae::launch_sample_draws(psi, n, cost_dev, cost_dtype, (const double*)(d + u_at), count, mass, pref,
-                                          seg, (uint64_t*)(d + out_at),
-                                          sample_costs ? (int32_t*)(d + cost_at) : nullptr, s));
-        HIP_TRY(hipMemcpyAsync(h + (out_at - u_at), d + out_at, B.size - out_at, hipMemcpyDeviceToHost, s));
-    }
+    double* const u = (double*)(d + u_at);
+    HIP_TRY(qnae::launch_sample_masses(psi, n, mass, seg, s));
+    if (count > 0) std::memcpy(h + h_u, uniforms, sizeof(double) * (size_t)count);
+    HIP_TRY(qnae::launch_sample_prefix(n, mass, pref, (double*)(d + chunk_at), (const double*)(h + h_u), u, count, s));
+    if (count > 0)
+        HIP_TRY(qnae::launch_sample_draws(psi, n, cost_dev, cost_dtype, u, count, mass, pref, seg,
+                                          (uint64_t*)(h + out_at),
+                                          sample_costs ? (int32_t*)(h + cost_at) : nullptr, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (count == 0) return QNAE_OK;
-    const uint64_t* o = (const uint64_t*)(h + (out_at - u_at));
+    const uint64_t* o = (const uint64_t*)(h + out_at);
     if (o[0] == ~0ull) return fail(QNAE_EINVAL, "state has zero norm");
     std::memcpy(samples, o, sizeof(uint64_t) * (size_t)count);
-    if (sample_costs) std::memcpy(sample_costs, h + (cost_at - u_at), sizeof(int32_t) * (size_t)count);
+    if (sample_costs) std::memcpy(sample_costs, h + cost_at, sizeof(int32_t) * (size_t)count);
     return QNAE_OK;
 } catch (...) {
     return host_exception();

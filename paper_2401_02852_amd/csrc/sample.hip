@@ -108,8 +108,17 @@ __global__ __launch_bounds__(256) void tile_mass_kernel(const float2* __restrict
 // over 16 workgroups, as each load instruction touches 64 chunks' lines.
 constexpr int kRun = 16;
 
+// Workgroups past those copy the uniforms in from pinned host memory.
 __global__ __launch_bounds__(64) void chunk_run_kernel(const double* __restrict__ mass, double* __restrict__ pref,
-                                                       double* __restrict__ chunk_total, uint32_t T, uint32_t chunk) {
+                                                       double* __restrict__ chunk_total, uint32_t T, uint32_t chunk,
+                                                       const double* __restrict__ u_host, double* __restrict__ u_dev,
+                                                       uint32_t count) {
+    if (blockIdx.x >= kSampleChunks / 64) {
+        const uint32_t stride = (gridDim.x - kSampleChunks / 64) * 64u;
+        for (uint32_t q = (blockIdx.x - kSampleChunks / 64) * 64u + threadIdx.x; q < count; q += stride)
+            u_dev[q] = u_host[q];
+        return;
+    }
     const uint32_t i = blockIdx.x * 64u + threadIdx.x;
     const uint32_t lo = min(T, i * chunk), hi = min(T, lo + chunk);
     double run = 0.0;
@@ -177,7 +186,10 @@ __global__ __launch_bounds__(256) void chunk_add_kernel(double* __restrict__ pre
     if (t == 0) pref[T] = g[kGroup];
 }
 
-// One wave per draw, four to a workgroup.
+// One wave per draw, four to a workgroup. The outcomes go straight to pinned
+// host memory, four in one store: no copy follows the launch (of 100 000 draws
+// with costs from n = 26, 309 us with copies both ways, 259 us without; two
+// draws or four in turn by one wave took as long as one).
 template <typename CT>
 __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ psi, uint64_t N,
                                                      const double* __restrict__ mass, const double* __restrict__ pref,
@@ -185,88 +197,104 @@ __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ 
                                                      const double* __restrict__ uniforms, uint32_t count,
                                                      const CT* __restrict__ cost, uint64_t* __restrict__ out,
                                                      int32_t* __restrict__ out_cost) {
+    __shared__ uint64_t s_out[4];
+    __shared__ int32_t s_cost[4];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t q =
-        blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (q >= count) return;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const double total = pref[T];
-    if (!(total > 0.0)) {  // zero state: reported to the host as an error
-        if (lane == 0) out[q] = ~0ull;
-        return;
-    }
-    const double target = uniforms[q] * total;
-    // largest t with P[t] <= target (P[0] = 0): 64 places of the range at a time
-    uint32_t lo = 0, size = T;
-    while (size > 1) {
-        const uint32_t step = (size + 63u) / 64u;
-        const uint32_t t = lo + lane * step;
-        const uint64_t le = __ballot(lane * step < size && pref[min(t, T - 1u)] <= target);
-        const uint32_t k = (uint32_t)__popcll(le) - 1u;  // P is nondecreasing; place 0 is always at or below
-        size = min(step, size - k * step);
-        lo += k * step;
-    }
-    while (lo > 0 && !(mass[lo] > 0.0)) --lo;  // only past the last nonzero tile
-    const double r = target - pref[lo];
-    // the highest segment of the tile that starts at or below r and has mass
-    const double start = seg[(uint64_t)lo * kSegs + (lane & (kSegs - 1))];
-    int k = 63 - __builtin_clzll(__ballot(lane < kSegs && start <= r));
-    for (;; --k) {
-        const double s0 = __shfl(start, k);
-        const uint64_t base = (uint64_t)lo * kTile + (uint64_t)k * kSeg + 4u * lane;
-        float p[4] = {0.f, 0.f, 0.f, 0.f};
-        if (base + 2 <= N) {  // (N is even; small states end inside the segment)
-            const float4 a = *(const float4*)(psi + base);
-            p[0] = fmaf(a.x, a.x, a.y * a.y);
-            p[1] = fmaf(a.z, a.z, a.w * a.w);
+    const uint32_t q = blockIdx.x * 4u + wave;
+    if (q < count && !(total > 0.0)) {  // zero state: reported to the host as an error
+        if (lane == 0) s_out[wave] = ~0ull;
+    } else if (q < count) {
+        const double target = uniforms[q] * total;
+        // largest t with P[t] <= target (P[0] = 0): 64 places of the range at a time
+        uint32_t lo = 0, size = T;
+        while (size > 1) {
+            const uint32_t step = (size + 63u) / 64u;
+            const uint32_t t = lo + lane * step;
+            const uint64_t le = __ballot(lane * step < size && pref[min(t, T - 1u)] <= target);
+            const uint32_t k = (uint32_t)__popcll(le) - 1u;  // P is nondecreasing; place 0 is always at or below
+            size = min(step, size - k * step);
+            lo += k * step;
         }
-        if (base + 4 <= N) {
-            const float4 b = *(const float4*)(psi + base + 2);
-            p[2] = fmaf(b.x, b.x, b.y * b.y);
-            p[3] = fmaf(b.z, b.z, b.w * b.w);
+        // (the three loads go out together; the loop runs only past the last nonzero tile)
+        double here = mass[lo], before = pref[lo], start = seg[(uint64_t)lo * kSegs + (lane & (kSegs - 1))];
+        while (lo > 0 && !(here > 0.0)) {
+            --lo;
+            here = mass[lo], before = pref[lo], start = seg[(uint64_t)lo * kSegs + (lane & (kSegs - 1))];
         }
-        const double mine = (((double)p[0] + (double)p[1]) + (double)p[2]) + (double)p[3];
-        double incl = mine;
-        for (int off = 1; off < 64; off <<= 1) {
-            const double t = __shfl_up(incl, off);
-            if (lane >= (uint32_t)off) incl += t;
-        }
-        const double prev = __shfl_up(incl, 1);
-        const double excl = s0 + (lane ? prev : 0.0);
-        const uint64_t ok = __ballot(mine > 0.0 && excl <= r);
-        if (ok == 0ull && k > 0) continue;
-        if (ok != 0ull && lane == 63u - (uint32_t)__builtin_clzll(ok)) {
-            double acc = excl;
-            int pick = -1, last = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc += (double)p[j];
-                if (p[j] > 0.f && pick < 0) {
-                    last = j;
-                    if (acc > r) pick = j;
-                }
+        const double r = target - before;
+        // the highest segment of the tile that starts at or below r and has mass
+        int k = 63 - __builtin_clzll(__ballot(lane < kSegs && start <= r));
+        for (;; --k) {
+            const double s0 = __shfl(start, k);
+            const uint64_t base = (uint64_t)lo * kTile + (uint64_t)k * kSeg + 4u * lane;
+            float p[4] = {0.f, 0.f, 0.f, 0.f};
+            if (base + 2 <= N) {  // (N is even; small states end inside the segment)
+                const float4 a = *(const float4*)(psi + base);
+                p[0] = fmaf(a.x, a.x, a.y * a.y);
+                p[1] = fmaf(a.z, a.z, a.w * a.w);
             }
-            const uint64_t x = base + (uint64_t)(pick < 0 ? last : pick);  // rounding put r past this lane's walk
-            out[q] = x;
-            if (out_cost) out_cost[q] = cost ? (int32_t)cost[x] : -1;
+            if (base + 4 <= N) {
+                const float4 b = *(const float4*)(psi + base + 2);
+                p[2] = fmaf(b.x, b.x, b.y * b.y);
+                p[3] = fmaf(b.z, b.z, b.w * b.w);
+            }
+            const double mine = (((double)p[0] + (double)p[1]) + (double)p[2]) + (double)p[3];
+            double incl = mine;
+            for (int off = 1; off < 64; off <<= 1) {
+                const double t = __shfl_up(incl, off);
+                if (lane >= (uint32_t)off) incl += t;
+            }
+            const double prev = __shfl_up(incl, 1);
+            const double excl = s0 + (lane ? prev : 0.0);
+            const uint64_t ok = __ballot(mine > 0.0 && excl <= r);
+            if (ok == 0ull && k > 0) continue;
+            if (ok != 0ull && lane == 63u - (uint32_t)__builtin_clzll(ok)) {
+                double acc = excl;
+                int pick = -1, last = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    acc += (double)p[j];
+                    if (p[j] > 0.f && pick < 0) {
+                        last = j;
+                        if (acc > r) pick = j;
+                    }
+                }
+                const uint64_t x = base + (uint64_t)(pick < 0 ? last : pick);  // rounding put r past this lane's walk
+                s_out[wave] = x;
+                if (out_cost) s_cost[wave] = cost ? (int32_t)cost[x] : -1;
+            }
+            break;
         }
-        break;
+    }
+    __syncthreads();
+    const uint32_t at = blockIdx.x * 4u + threadIdx.x;
+    if (threadIdx.x < 4u && at < count) {
+        out[at] = s_out[threadIdx.x];
+        if (out_cost) out_cost[at] = s_cost[threadIdx.x];
     }
 }
 
 }  // namespace
 
-hipError_t launch_sample_prefix(const float2* psi, int n, double* mass, double* pref, double* seg,
-                                double* chunk_scratch, hipStream_t s) {
+hipError_t launch_sample_masses(const float2* psi, int n, double* mass, double* seg, hipStream_t s) {
+    const uint64_t N = 1ull << n;
+    hipLaunchKernelGGL(tile_mass_kernel, dim3((uint32_t)((N + kTile - 1) / kTile)), dim3(256), 0, s, psi, N, mass, seg);
+    return hipGetLastError();
+}
+
+hipError_t launch_sample_prefix(int n, const double* mass, double* pref, double* chunk_scratch,
+                                const double* u_host, double* u_dev, int count, hipStream_t s) {
     const uint64_t N = 1ull << n;
     const uint32_t T = (uint32_t)((N + kTile - 1) / kTile);
-    hipLaunchKernelGGL(tile_mass_kernel, dim3(T), dim3(256), 0, s, psi, N, mass, seg);
-    if (hipError_t e = hipGetLastError()) return e;
     static_assert(kSampleChunks % 64 == 0 && kSampleChunks % kRun == 0, "chunk launch shape");
     static_assert(kSegs == kSampleSegs, "room for the segment starts");
     const uint32_t chunk = (T + kSampleChunks - 1) / kSampleChunks;  // T is a power of two
     const uint32_t chunk_bits = (uint32_t)__builtin_ctz(chunk);
-    hipLaunchKernelGGL(chunk_run_kernel, dim3(kSampleChunks / 64), dim3(64), 0, s, mass, pref, chunk_scratch, T,
-                       chunk);
+    const uint32_t copiers = ((uint32_t)count + 1023u) / 1024u;
+    hipLaunchKernelGGL(chunk_run_kernel, dim3(kSampleChunks / 64 + (copiers < 512u ? copiers : 512u)), dim3(64), 0, s,
+                       mass, pref, chunk_scratch, T, chunk, u_host, u_dev, (uint32_t)count);
     if (hipError_t e = hipGetLastError()) return e;
     hipLaunchKernelGGL(chunk_add_kernel, dim3((T + 255) / 256), dim3(256), 0, s, pref,
                        (const double*)chunk_scratch, T, chunk_bits);
