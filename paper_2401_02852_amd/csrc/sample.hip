@@ -213,7 +213,8 @@ __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ 
             const uint32_t step = (size + 63u) / 64u;
             const uint32_t t = lo + lane * step;
             const uint64_t le = __ballot(lane * step < size && pref[min(t, T - 1u)] <= target);
-            const uint32_t k = (uint32_t)__popcll(le) - 1u;  // P is nondecreasing; place 0 is always at or below
+            // P is nondecreasing and place 0 at or below, but for a target of 0 * infinity
+            const uint32_t k = (uint32_t)__popcll(le | 1ull) - 1u;
             size = min(step, size - k * step);
             lo += k * step;
         }
@@ -225,7 +226,8 @@ __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ 
         }
         const double r = target - before;
         // the highest segment of the tile that starts at or below r and has mass
-        int k = 63 - __builtin_clzll(__ballot(lane < kSegs && start <= r));
+        // (an infinite total can make r not a number: no test holds, the first place is taken)
+        int k = 63 - __builtin_clzll(__ballot(lane < kSegs && start <= r) | 1ull);
         for (;; --k) {
             const double s0 = __shfl(start, k);
             const uint64_t base = (uint64_t)lo * kTile + (uint64_t)k * kSeg + 4u * lane;
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(256) void sample_kernel(const float2* __restrict__ 
             const double excl = s0 + (lane ? prev : 0.0);
             const uint64_t ok = __ballot(mine > 0.0 && excl <= r);
             if (ok == 0ull && k > 0) continue;
-            if (ok != 0ull && lane == 63u - (uint32_t)__builtin_clzll(ok)) {
+            if (lane == 63u - (uint32_t)__builtin_clzll(ok | 1ull)) {
                 double acc = excl;
                 int pick = -1, last = 0;
 #pragma unroll

@@ -165,3 +165,24 @@ def test_sample_edge_cases(q):
     assert list(got) == [5, 5, 1000, 1000]
     with pytest.raises(q.QNAEError, match="uniforms"):
         q.sample(z, 10, [1.0])
+
+
+@pytest.mark.parametrize("n", [1, 4, 12, 13, 18])
+@pytest.mark.parametrize("at", ["first", "last", "both"])
+def test_sample_of_an_infinite_mass_stays_in_range(q, n, at):
+    """An amplitude whose square overflows leaves no distribution to draw from;
+    every outcome is an index of the state all the same, with its own cost, and a
+    state that holds no number at all is refused like a zero one."""
+    import torch
+    st = torch.zeros(1 << n, dtype=torch.complex64, device="cuda")
+    st += 2.0 ** (-n / 2)
+    for i in {"first": [0], "last": [-1], "both": [0, -1]}[at]:
+        st[i] = 1e30
+    c = torch.arange(1 << n, device="cuda").to(torch.uint8)
+    u = np.concatenate([[0.0], np.random.default_rng(n).random(40), [1.0 - 2.0 ** -53]])
+    got, costs = q.sample(st, n, u, cost=c)
+    assert np.all(got.astype(np.uint64) < np.uint64(1 << n))
+    assert np.array_equal(costs, (got.astype(np.int64) & 255).astype(np.int32))
+    st[0] = float("nan")
+    with pytest.raises(Exception):
+        q.sample(st, n, u, cost=c)
