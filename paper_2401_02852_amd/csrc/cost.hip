@@ -372,9 +372,12 @@ __global__ __launch_bounds__(kProThreads) void prologue_kernel(const PrologueArg
     }
 }
 
-// Job blockIdx.y, its pieces over the blocks of a row. The last workgroup of
-// all writes the ticket, after every flag. Ended workgroups are counted per
-// job first: thousands of additions to one word took 100 us.
+// Job blockIdx.y, its pieces over the blocks of a row; counted as above, a
+// counter per job (thousands of additions to one word took 100 us). The last
+// workgroup of a job writes its flag to the host, the last of all the ticket,
+// after every flag. (A flag written by every workgroup that found a difference,
+// 64 fenced stores to the host a job, cost a batch of 16 3-SAT instances at
+// n = 20 60 us.)
 __global__ __launch_bounds__(kProThreads) void flip_batch_kernel(FlipJob* jobs, uint32_t* flags, uint32_t* word,
                                                                  uint32_t ticket, uint32_t* answer) {
     const FlipJob j = jobs[blockIdx.y];
@@ -382,15 +385,15 @@ __global__ __launch_bounds__(kProThreads) void flip_batch_kernel(FlipJob* jobs, 
     auto none = [] { return false; };
     const bool diff = j.u16 ? flip_differs<true>(j.cost, j.quads, id, stride, none)
                             : flip_differs<false>(j.cost, j.quads, id, stride, none);
-    const bool any = __syncthreads_or(diff) != 0;
+    const uint32_t mine = __syncthreads_or(diff) ? 0x10001u : 1u;
     if (threadIdx.x == 0) {
-        if (any) {
+        const uint32_t w =
+            mine + __hip_atomic_fetch_add(&jobs[blockIdx.y].done, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((w & 0xffffu) != gridDim.x) return;
+        if (w >> 16) {
             __hip_atomic_store(&flags[blockIdx.y], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __threadfence_system();
         }
-        const uint32_t w =
-            1u + __hip_atomic_fetch_add(&jobs[blockIdx.y].done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (w != gridDim.x) return;
         const uint32_t v = 1u + __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (v == gridDim.y) {
             __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

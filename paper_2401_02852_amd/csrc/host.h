@@ -190,13 +190,17 @@ int enter(qnae_ctx* ctx, hipStream_t s);
 // context's fixed pinned staging for it.
 int noalloc_setup(qnae_ctx* ctx);
 // Smallest n whose single runs and gradients are checked for a flip-symmetric
-// cost (and then use half the state).
+// cost (and then use half the state). Below, a sweep of either takes as long: it
+// is bound by its launch and by the depth of a tile (eight layers on the whole
+// and on the half state, us: n = 18 107 and 106, n = 19 110 and 106, n = 20 124 and
+// 111, n = 22 173 and 129, n = 24 896 and 495).
 constexpr int kFlipMinN = 20;
 // Up to this n the first sweep is launched on the whole state before the
 // check's answer is known: it covers the wait (about 10 us), and its lower
 // half is what a half-state run goes on from. Above, a whole first sweep
-// costs more than the wait.
-constexpr int kFlipEarlyMaxN = 24;
+// costs more than the wait (two layers, waiting and not, us: n = 20 53 and 50,
+// n = 21 54 and 52, n = 22 57 and 56, n = 23 98 and 100, n = 24 158 and 167).
+constexpr int kFlipEarlyMaxN = 22;
 // The launch ahead of a run: copies `bytes` (rounded up to 16; both buffers
 // hold that many) of pinned src to dst and, unless cost is null, checks the
 // diagonal; flip_answer waits for the check's answer by watching the pinned
@@ -208,8 +212,11 @@ int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric);
 // The same for the instances of a batch: the tiled ones with half[i] = 0 are
 // checked, when their states together hold kFlipBatchAmps amplitudes or more
 // (smaller batches are bound by launches, not by bytes). end sets half[i] = 2
-// (half state, whole final state) where the diagonal is symmetric.
-constexpr uint64_t kFlipBatchAmps = 1ull << 22;
+// (half state, whole final state) where the diagonal is symmetric. A check that
+// finds no symmetry costs about 15 us; five layers without and with it, us:
+// 2^22 amplitudes (16 of n = 18) NAE 169 and 158, SAT 167 and 182; 2^23 (8 of n = 20)
+// 216 and 159, 218 and 227; 2^24 373 and 251, 369 and 382.
+constexpr uint64_t kFlipBatchAmps = 1ull << 23;
 struct FlipBatch {
     std::vector<int> jobs;  // instances being checked
     uint32_t ticket = 0;

@@ -35,8 +35,11 @@ struct CostArgs {
 // C(x) for x < 2^a.n.
 hipError_t launch_cost(const CostArgs& a, int dtype, hipStream_t s);
 // Runs of 32 states a thread counts, for this many states in one launch: four
-// share the work per clause, once that leaves enough waves to fill the chip.
-inline int cost_words(uint64_t states) { return states >= (1ull << 24) ? 4 : 1; }
+// share the work per clause, once that leaves enough waves to fill the chip
+// (one run and four, us per call: n = 23, k = 3 20.5 and 22.9, k = 5 26.4 and
+// 34.1; n = 24 24.0 and 23.9, 32.6 and 36.3; n = 25 30.8 and 28.3, 44.2 and 45.0;
+// n = 26 43.4 and 37, 67 and 63.5).
+inline int cost_words(uint64_t states) { return states >= (1ull << 25) ? 4 : 1; }
 // 256-thread blocks of a diagonal of 2^n states.
 inline uint32_t cost_blocks(int n, int words) {
     const int bits = words == 4 ? 15 : 13;  // states of a block
@@ -72,7 +75,7 @@ struct FlipJob {
     const uint4* cost;
     uint32_t quads;  // 16-byte pieces of the diagonal, >= 2
     uint32_t u16;
-    uint32_t done;  // workgroups of this job that have ended; 0 before
+    uint32_t done;  // workgroups of this job that have ended, and 2^16 for each that found a difference; 0 before
     uint32_t pad[3];
 };
 hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint32_t* flags, uint32_t* word,

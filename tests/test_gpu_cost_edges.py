@@ -1,6 +1,6 @@
 """Cost diagonals at the edges of the cost kernel's waves and clause lists,
 against the oracle, every entry: sizes around one wave's states (2^11, and
-2^13 from 2^24 states on), clause counts around a list chunk (192) and a multiple of
+2^13 from 2^25 states on), clause counts around a list chunk (192) and a multiple of
 four or sixteen patterns, and clause sets that sit wholly in one list."""
 import numpy as np
 import pytest
@@ -31,7 +31,7 @@ def check(q, cl, n, pred="nae"):
 
 
 @pytest.mark.parametrize("n,m", [(3, 5), (4, 16), (5, 17), (10, 3), (11, 191), (11, 192), (12, 193), (13, 255), (13, 256),
-                                 (14, 385), (17, 60), (23, 40), (24, 33), (24, 260), (25, 9)])
+                                 (14, 385), (17, 60), (23, 40), (24, 33), (24, 260), (25, 9), (25, 260)])
 @pytest.mark.parametrize("pred", ["nae", "sat"])
 def test_waves_and_chunks(q, n, m, pred):
     check(q, inst.instance(n, 3, m, 1000 * n + m), n, pred)
@@ -40,7 +40,7 @@ def test_waves_and_chunks(q, n, m, pred):
 # variables of every clause drawn from one range: the pattern list, the list
 # of clauses constant over a run, those constant over a wave, and high bits only
 @pytest.mark.parametrize("lo,hi", [(0, 5), (5, 11), (11, 13), (13, 24), (0, 24)])
-@pytest.mark.parametrize("n,m", [(24, 200), (24, 1)])
+@pytest.mark.parametrize("n,m", [(24, 200), (24, 1), (25, 200)])
 def test_clauses_of_one_list(q, lo, hi, n, m):
     rng = np.random.default_rng(lo * 100 + hi + m)
     k = min(3, hi - lo)
