@@ -171,7 +171,7 @@ hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args
 int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask);
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
 
-// Whole circuit for n <= 14 in one workgroup (state resident in LDS).
+// Whole circuit for n <= 14 in one workgroup (resident.hip).
 struct ResidentArgs {
     const float2* state_in;  // optional initial state (true scale); |+> when null
     const void* cost;

@@ -310,143 +310,6 @@ __global__ __launch_bounds__(256) void reverse_kernel(float2* psi, uint64_t N) {
     *hi = make_float4(a.z, a.w, a.x, a.y);
 }
 
-// ---------------------------------------------------------------------------
-// Whole circuit in one workgroup for n <= 14 (state resident in LDS).
-// ---------------------------------------------------------------------------
-
-// LDS slot of amplitude x: one pad slot per 16, so that the threads of the
-// bits-0..3 pass, each holding 16 consecutive amplitudes, fall in different
-// banks instead of all in one (a stride of 16 float2 is 32 banks).
-__device__ __forceinline__ uint32_t rslot(uint32_t x) { return x + (x >> 4); }
-
-// 1024 threads: one workgroup's LDS (the 136 KiB state, uint8 costs) leaves
-// room for no second one on a CU, so its own waves (four per SIMD) hide the
-// LDS latency.
-constexpr int kResidentThreads = 1024;
-
-// Radix-2^NBP butterfly passes of one layer over the LDS state: each task
-// holds the 2^nb amplitudes of one coset of nb consecutive qubits.
-template <int NBP>
-__device__ __forceinline__ void resident_mix(float2* s, int n, uint32_t N, float t) {
-    for (int g0 = 0; g0 < n; g0 += NBP) {
-        const int nb = n - g0 < NBP ? n - g0 : NBP;
-        const uint32_t tasks = N >> nb;
-        for (uint32_t task = threadIdx.x; task < tasks; task += kResidentThreads) {
-            const uint32_t bs = ((task >> g0) << (g0 + nb)) | (task & ((1u << g0) - 1u));
-            float2 v[1 << NBP];
-#pragma unroll
-            for (int i = 0; i < (1 << NBP); ++i)
-                v[i] = i < (1 << nb) ? s[rslot(bs | ((uint32_t)i << g0))] : make_float2(0.f, 0.f);
-            if (nb > 0) bfly<(1 << NBP), 0>(v, t);
-            if (NBP > 1 && nb > 1) bfly<(1 << NBP), (NBP > 1 ? 1 : 0)>(v, t);
-            if (NBP > 2 && nb > 2) bfly<(1 << NBP), (NBP > 2 ? 2 : 0)>(v, t);
-            if (NBP > 3 && nb > 3) bfly<(1 << NBP), (NBP > 3 ? 3 : 0)>(v, t);
-#pragma unroll
-            for (int i = 0; i < (1 << NBP); ++i)
-                if (i < (1 << nb)) s[rslot(bs | ((uint32_t)i << g0))] = v[i];
-        }
-        __syncthreads();
-    }
-}
-
-// Qubits per pass: four at n = 14 (1024 cosets, one per thread), three
-// below (at n = 12 and 13 measured 1-2 us faster per solve than four).
-constexpr int kResidentSmallNbp = 3;
-
-template <typename CT>
-__device__ __forceinline__ void resident_body(const ResidentArgs& a) {
-    constexpr uint32_t NT = kResidentThreads;
-    __shared__ float2 s[(1 << 14) + (1 << 10)];
-    __shared__ double red[3][NT / 64];
-    // uint8 costs are read from global memory once and kept beside the state
-    // (16 KiB at n = 14); uint16 ones would not fit and are read per layer.
-    constexpr bool COST_LDS = sizeof(CT) == 1;
-    __shared__ CT cs[COST_LDS ? 1 << 14 : 1];
-    const int n = a.n;
-    const uint32_t N = 1u << n;
-    const uint32_t tid = threadIdx.x;
-    const CT* const cost_g = (const CT*)a.cost;
-    if (COST_LDS) {
-        for (uint32_t x = tid; x < N; x += NT) cs[x] = cost_g[x];
-        __syncthreads();
-    }
-    const CT* const cost = COST_LDS ? cs : cost_g;
-    const uint32_t last = (uint32_t)a.lut_len - 1u;
-    const int layers = a.p > 0 ? a.p : 1;
-    // The butterflies drop the X of the cot form; `flip` records that the
-    // stored state is the true one with every qubit flipped.
-    uint32_t flip = 0u;
-    for (int l = 0; l < layers; ++l) {
-        const float2* lut = a.luts + (size_t)l * a.lut_len;
-        for (uint32_t x = tid; x < N; x += NT) {
-            const float2 e = lut[min((uint32_t)cost[x ^ flip], last)];
-            s[rslot(x)] = l > 0 ? cmul(s[rslot(x)], e) : a.state_in ? cmul(a.state_in[x], e) : e;
-        }
-        __syncthreads();
-        if (a.p == 0) break;
-    const MixForm f = a.forms[l];
-        if (n >= 14) resident_mix<4>(s, n, N, f.t);
-        else if (n == 13) resident_mix<3>(s, n, N, f.t);
-        else resident_mix<kResidentSmallNbp>(s, n, N, f.t);
-        if (f.flip) flip ^= N - 1u;
-    }
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f;
-    for (uint32_t x = tid; x < N; x += NT) {
-        const float2 q = s[rslot(x)];
-        const float pr = fmaf(q.x, q.x, q.y * q.y);
-        const uint32_t cx = cost[x ^ flip];
-        s2 += pr;
-        s1 = fmaf((float)cx, pr, s1);
-        s0 += cx == 0u ? pr : 0.f;
-        if (a.state_out) a.state_out[x ^ flip] = cmul(q, a.store_scale);
-    }
-    double d0 = s0, d1 = s1, d2 = s2;
-    for (int off = 32; off > 0; off >>= 1) {
-        d0 += __shfl_xor(d0, off);
-        d1 += __shfl_xor(d1, off);
-        d2 += __shfl_xor(d2, off);
-    }
-    if ((tid & 63u) == 0) {
-        red[0][tid >> 6] = d0;
-        red[1][tid >> 6] = d1;
-        red[2][tid >> 6] = d2;
-    }
-    __syncthreads();
-    if (tid < 3) {
-        double sum = 0.0;
-        for (uint32_t w = 0; w < NT / 64; ++w) sum += red[tid][w];
-        a.out[tid] = sum;
-    }
-}
-
-template <typename CT>
-__global__ __launch_bounds__(kResidentThreads) void resident_kernel(const ResidentArgs a) {
-    resident_body<CT>(a);
-}
-
-// Tables from the kernel arguments, staged in LDS (3.5 KiB beside the
-// state and costs: 156 of the CU's 160 KiB) and read through generic
-// pointers.
-template <typename CT>
-__global__ __launch_bounds__(kResidentThreads) void resident_inline_kernel(const ResidentInlineArgs ia) {
-    __shared__ float2 tab[kResidentInline];
-    const int layers = ia.a.p > 0 ? ia.a.p : 1;
-    const int count = layers * ia.a.lut_len + ia.a.p;
-    for (int i = threadIdx.x; i < count; i += kResidentThreads) tab[i] = ia.tab[i];
-    __syncthreads();
-    ResidentArgs a = ia.a;
-    a.luts = tab;
-    a.forms = (const MixForm*)(tab + layers * ia.a.lut_len);
-    resident_body<CT>(a);
-}
-
-// Many small instances, one workgroup each.
-template <typename CT>
-__global__ __launch_bounds__(kResidentThreads) void resident_batch_kernel(const ResidentArgs* args) {
-    const ResidentArgs a = args[blockIdx.x];
-    resident_body<CT>(a);
-}
-
 __device__ __forceinline__ void final_reduce_body(const double* partials, int64_t blocks, double* out) {
     __shared__ double red[3][16];
     double t0 = 0.0, t1 = 0.0, t2 = 0.0;
@@ -563,32 +426,6 @@ hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s) {
     const uint64_t threads = N / 4;
     hipLaunchKernelGGL(reverse_kernel, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, psi, N);
-    return hipGetLastError();
-}
-
-hipError_t launch_resident(int dtype, const ResidentArgs& a, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL((resident_kernel<uint8_t>), dim3(1), dim3(kResidentThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((resident_kernel<uint16_t>), dim3(1), dim3(kResidentThreads), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_resident_inline(int dtype, const ResidentInlineArgs& a, hipStream_t s) {
-    const int layers = a.a.p > 0 ? a.a.p : 1;
-    if ((int64_t)layers * a.a.lut_len + a.a.p > kResidentInline) return hipErrorInvalidValue;
-    if (dtype == 1)
-        hipLaunchKernelGGL((resident_inline_kernel<uint8_t>), dim3(1), dim3(kResidentThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((resident_inline_kernel<uint16_t>), dim3(1), dim3(kResidentThreads), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL((resident_batch_kernel<uint8_t>), dim3(count), dim3(kResidentThreads), 0, s, args);
-    else
-        hipLaunchKernelGGL((resident_batch_kernel<uint16_t>), dim3(count), dim3(kResidentThreads), 0, s, args);
     return hipGetLastError();
 }
 

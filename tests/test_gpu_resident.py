@@ -1,0 +1,64 @@
+"""One-workgroup circuits on both sides of every size that has a kernel of its
+own (n = 9 .. 14), against the FP64 oracle with whole final states, and the same
+instances in one batch, whose workgroups hold more waves than most of them use:
+8- and 16-bit costs, both directions of the relabelling, tables in the kernel
+arguments, in LDS and too long for it."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import instances as inst
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    import paper_2401_02852_amd as q
+    q.load_library()
+    return q
+
+
+def setup(n, m, p, pred, u16, cots, seed):
+    import torch
+    cost = oracle.cost(inst.instance(n, min(n, 3), min(m, 250), seed), n, pred)
+    rng = np.random.default_rng(seed)
+    b = rng.uniform(-0.7, 0.7, p)
+    b[:cots] = 1.2
+    dev = torch.from_numpy(cost.astype(np.uint16 if u16 else np.uint8)).cuda()
+    return cost, dev, rng.uniform(-1, 1, p), b
+
+
+def check(got, psi, cost, n, g, b):
+    ref, ref_psi = oracle.qaoa(cost, n, g, b), oracle.state(cost, n, g, b)
+    assert abs(got[0] - ref[0]) <= 1e-5
+    assert abs(got[1] - ref[1]) <= 1e-5 * ref[1] + 1e-9
+    assert abs(got[2] - 1.0) <= 1e-5
+    # FP32: a few rounding errors of 6e-8 per layer and qubit on the amplitude scale
+    assert np.max(np.abs(psi.cpu().numpy() - ref_psi)) <= 6e-8 * 4 * n * max(len(g), 1) * np.max(np.abs(ref_psi))
+
+
+# (m, p): tables in the kernel arguments; in LDS; longer than that
+SHAPES = [(40, 3), (40, 0), (100, 8), (250, 12)]
+
+
+@pytest.mark.parametrize("n", [1, 6, 9, 10, 11, 12, 13, 14])
+@pytest.mark.parametrize("m,p", SHAPES)
+@pytest.mark.parametrize("u16", [False, True])
+def test_single_and_batched(q, n, m, p, u16):
+    import torch
+    jobs = []
+    for i, pred in enumerate(("nae", "sat", "sat")):
+        cost, dev, g, b = setup(n, m, p, pred, u16, min(i, p), 100 * n + i)
+        psi = torch.full((1 << n,), 7.0, dtype=torch.complex64, device="cuda")
+        r = q.qaoa_run(dev, n, m, g, b, state=psi)
+        check((r.p_success, r.expected_cost, r.norm), psi, cost, n, g, b)
+        jobs.append((dev, g, b, r, psi))
+    states = [torch.full((1 << n,), 7.0, dtype=torch.complex64, device="cuda") for _ in jobs]
+    got = q.qaoa_run_batched([j[0] for j in jobs], [n] * 3, [m] * 3, [j[1] for j in jobs], [j[2] for j in jobs],
+                             states=states)
+    for (dev, g, b, r, psi), st, x in zip(jobs, states, got):
+        assert torch.equal(st, psi)
+        assert abs(x.p_success - r.p_success) <= 1e-12 and abs(x.expected_cost - r.expected_cost) <= 1e-12 * (1 + m)
