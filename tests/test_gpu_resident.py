@@ -62,3 +62,26 @@ def test_single_and_batched(q, n, m, p, u16):
     for (dev, g, b, r, psi), st, x in zip(jobs, states, got):
         assert torch.equal(st, psi)
         assert abs(x.p_success - r.p_success) <= 1e-12 and abs(x.expected_cost - r.expected_cost) <= 1e-12 * (1 + m)
+
+
+# (m, p, checkpoint_every): short and long phase tables, with and without checkpoints
+@pytest.mark.parametrize("n", [9, 10, 11, 12, 13])
+@pytest.mark.parametrize("m,p,every", [(40, 0, 0), (40, 1, 0), (40, 7, 3), (250, 12, 0), (2600, 5, 2)])
+@pytest.mark.parametrize("u16", [False, True])
+def test_gradients(q, n, m, p, every, u16):
+    if m > 255 and not u16:
+        m = 255
+    for i, pred in enumerate(("nae", "sat")):
+        cost, dev, g, b = setup(n, m, p, pred, u16, min(i, p), 7 * n + i)
+        dg, db, r = q.qaoa_grad(dev, n, m, g, b, w_psucc=1.0, w_energy=0.1, checkpoint_every=every)
+        ref = oracle.qaoa(cost, n, g, b)
+        assert abs(r.p_success - ref[0]) <= 1e-5
+        assert abs(r.expected_cost - ref[1]) <= 1e-5 * ref[1] + 1e-9
+        assert abs(r.norm - 1.0) <= 1e-5
+        if p == 0:
+            continue
+        rg, rb, _ = oracle.qaoa_grad(cost, n, g, b, 1.0, 0.1)
+        scale = max(np.max(np.abs(rg)), np.max(np.abs(rb)))
+        # the two states carry a few rounding errors of 6e-8 per layer and qubit: below 6e-8 * 4 * 13 * 12 of the scale
+        assert np.max(np.abs(dg - rg)) <= 1e-4 * scale + 1e-5
+        assert np.max(np.abs(db - rb)) <= 1e-4 * scale + 1e-5
