@@ -36,11 +36,9 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS position of tile element e: two padding slots after every 64 elements
-// (conflict-free in every layout: 16 consecutive lanes with single elements hit
-// 16 distinct 8-byte bank pairs, 8 consecutive lanes with pairs 8 distinct
-// 16-byte groups). The map is additive over disjoint bit sets of e, so an
-// address is a per-thread base plus a compile-time constant per slot.
+// LDS position of element e of a reverse tile: two padding slots after every 64
+// elements. The map is additive over disjoint bit sets of e, so an address is
+// a per-thread base plus a compile-time constant per slot.
 __device__ __forceinline__ constexpr uint32_t phys(uint32_t e) { return e + 2u * (e >> 6); }
 template <int TB>
 constexpr uint32_t lds_elems() { return phys((1u << TB) - 1u) + 1u; }
@@ -154,13 +152,14 @@ __device__ __forceinline__ void s_swap(float2 (&v)[16]) {
     }
 }
 
-// LDS place of element e: phys for whole float2 elements, and for component
-// planes (one float per element, half the LDS) e + sum of c_i over its set
-// bits i >= 6, non-decreasing sums chosen so that b32 accesses of 32 lanes in
-// layouts 2, 3 (e{0, 7..10}) and 4, 5 (e{0..3, 10}) hit 32 distinct banks.
-template <bool PLANES>
+// LDS place of element e, of whole float2 elements and of component planes (one
+// float per element, half the LDS): e + sum of c_i over its set bits i >= 6,
+// non-decreasing sums chosen so that accesses of 32 lanes in layouts 2, 3
+// (e{0, 7..10}) and 4, 5 (e{0..3, 10}) hit 32 distinct banks (b32) or bank pairs
+// (b64). Two padding slots per 64 elements, which serve 16 lanes, put e10's lanes
+// on the same pairs as the others': 4 conflict cycles per access in the half
+// state's middle kind, half state n = 27, p = 10 3.93 -> 3.91 ms.
 __device__ __forceinline__ constexpr uint32_t splace(uint32_t e) {
-    if (!PLANES) return phys(e);
     constexpr uint32_t c[7] = {0, 2, 4, 8, 16, 32, 64};
     uint32_t p = e;
     for (int i = 0; i < 7; ++i) p += ((e >> (6 + i)) & 1u) * c[i];
@@ -169,7 +168,7 @@ __device__ __forceinline__ constexpr uint32_t splace(uint32_t e) {
 // floats of LDS a tile takes
 template <int TB, bool PLANES>
 constexpr uint32_t s_lds_floats() {
-    return PLANES ? (splace<true>((1u << TB) - 1u) + 2u) / 2u * 2u : 2u * lds_elems<TB>();
+    return (PLANES ? 1u : 2u) * ((splace((1u << TB) - 1u) + 2u) / 2u * 2u);
 }
 
 // Calls f(j, place) for every slot j of layout LY.
@@ -178,12 +177,12 @@ __device__ __forceinline__ void s_places(uint32_t lane, uint32_t wave, F&& f) {
     constexpr uint32_t top = 1u << (TB - 1), slots = ss<TB, LY>(15) & ~top;  // slot bits but the top one
     constexpr uint32_t threads = ((1u << TB) - 1u) & ~slots & ~top;
     const uint32_t t = st<TB, LY>(lane, wave);
-    const uint32_t b = splace<PLANES>(t);
-    const uint32_t bc = VIRT && LY >= 4 ? splace<PLANES>(top | (threads ^ t)) : b;
+    const uint32_t b = splace(t);
+    const uint32_t bc = VIRT && LY >= 4 ? splace(top | (threads ^ t)) : b;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        if (VIRT && LY >= 4 && (ss<TB, LY>(j) & top)) f(j, bc + splace<PLANES>(slots ^ (ss<TB, LY>(j) & ~top)));
-        else f(j, b + splace<PLANES>(ss<TB, LY>(j)));
+        if (VIRT && LY >= 4 && (ss<TB, LY>(j) & top)) f(j, bc + splace(slots ^ (ss<TB, LY>(j) & ~top)));
+        else f(j, b + splace(ss<TB, LY>(j)));
     }
 }
 
@@ -191,10 +190,10 @@ __device__ __forceinline__ void s_places(uint32_t lane, uint32_t wave, F&& f) {
 template <int TB, int LY, bool VIRT>
 __device__ __forceinline__ void to_s(float2* lds, const float2 (&v)[16], uint32_t lane, uint32_t wave) {
     if constexpr (LY < 2) {
-        float2* const b = lds + phys(st<TB, LY>(lane, wave));
+        float2* const b = lds + splace(st<TB, LY>(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj)
-            *(float4*)(b + phys(ss<TB, LY>(2 * jj))) =
+            *(float4*)(b + splace(ss<TB, LY>(2 * jj))) =
                 make_float4(v[2 * jj].x, v[2 * jj].y, v[2 * jj + 1].x, v[2 * jj + 1].y);
     } else {
         s_places<TB, LY, VIRT, false>(lane, wave, [&](int j, uint32_t at) { lds[at] = v[j]; });
@@ -203,10 +202,10 @@ __device__ __forceinline__ void to_s(float2* lds, const float2 (&v)[16], uint32_
 template <int TB, int LY, bool VIRT>
 __device__ __forceinline__ void from_s(const float2* lds, float2 (&v)[16], uint32_t lane, uint32_t wave) {
     if constexpr (LY < 2) {
-        const float2* const b = lds + phys(st<TB, LY>(lane, wave));
+        const float2* const b = lds + splace(st<TB, LY>(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
-            const float4 q = *(const float4*)(b + phys(ss<TB, LY>(2 * jj)));
+            const float4 q = *(const float4*)(b + splace(ss<TB, LY>(2 * jj)));
             v[2 * jj] = make_float2(q.x, q.y);
             v[2 * jj + 1] = make_float2(q.z, q.w);
         }
@@ -218,10 +217,10 @@ __device__ __forceinline__ void from_s(const float2* lds, float2 (&v)[16], uint3
 template <int TB, int LY, bool VIRT, int C>
 __device__ __forceinline__ void to_s_plane(float* lds, const float2 (&v)[16], uint32_t lane, uint32_t wave) {
     if constexpr (LY < 2) {
-        float* const b = lds + splace<true>(st<TB, LY>(lane, wave));
+        float* const b = lds + splace(st<TB, LY>(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj)
-            *(float2*)(b + splace<true>(ss<TB, LY>(2 * jj))) = make_float2(part<C>(v[2 * jj]), part<C>(v[2 * jj + 1]));
+            *(float2*)(b + splace(ss<TB, LY>(2 * jj))) = make_float2(part<C>(v[2 * jj]), part<C>(v[2 * jj + 1]));
     } else {
         s_places<TB, LY, VIRT, true>(lane, wave, [&](int j, uint32_t at) { lds[at] = part<C>(v[j]); });
     }
@@ -229,10 +228,10 @@ __device__ __forceinline__ void to_s_plane(float* lds, const float2 (&v)[16], ui
 template <int TB, int LY, bool VIRT, int C>
 __device__ __forceinline__ void from_s_plane(const float* lds, float2 (&v)[16], uint32_t lane, uint32_t wave) {
     if constexpr (LY < 2) {
-        const float* const b = lds + splace<true>(st<TB, LY>(lane, wave));
+        const float* const b = lds + splace(st<TB, LY>(lane, wave));
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
-            const float2 q = *(const float2*)(b + splace<true>(ss<TB, LY>(2 * jj)));
+            const float2 q = *(const float2*)(b + splace(ss<TB, LY>(2 * jj)));
             set_part<C>(v[2 * jj], q.x);
             set_part<C>(v[2 * jj + 1], q.y);
         }
