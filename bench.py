@@ -5,6 +5,9 @@ A step is the whole hot path on one instance: build the cost diagonal from the
 clauses, run p layers of phase and mixer from |+>, and read out p_succ and
 E[C]. The default workload is n = 30 variables, m = 63 clauses (r = 2.1),
 p = 10 linear-ramp layers, complex64 state (8 GiB) and a uint8 cost diagonal.
+Every run finds out from the diagonal it is given that it is flip-symmetric (NAE
+costs are) and then stores one amplitude of each mirrored pair; rates count all
+2^n, bytes the stored ones.
 The instance is the first satisfiable seed recorded in
 tests/golden/workloads.json.
 
