@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqnae.so")
 SOURCES = ["runtime.cpp", "qnae.cpp", "batch.cpp", "grad.cpp", "server.cpp", "tune.cpp", "sample.cpp", "prologue.cpp", "noalloc.hip",
-           "cost.hip", "sweep.hip", "sweep14.hip", "resident.hip", "adjoint.hip", "sample.hip", "tables.hip"]
+           "cost.hip", "sweep.hip", "sweep14.hip", "resident.hip", "resident_grad.hip", "adjoint.hip", "sample.hip", "tables.hip"]
 ARCH = os.environ.get("QNAE_OFFLOAD_ARCH", "gfx950")
 COMMON = ["-fPIC", "-O3", "-std=c++17", "-Wall", "-Wno-unused-result"]
 # Keep the device compiler from forming packed FP32 instructions

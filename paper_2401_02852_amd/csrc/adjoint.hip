@@ -510,177 +510,6 @@ __global__ __launch_bounds__(kQThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     }
 }
 
-// ---------------------------------------------------------------------------
-// Whole gradient for n <= 13 in one workgroup.
-// ---------------------------------------------------------------------------
-
-// 1024 threads: the two resident states fill 128 KiB of a CU's LDS, so no
-// second workgroup fits and the workgroup's own waves (four per SIMD) hide
-// the LDS latency.
-constexpr int kResidentGradThreads = 1024;
-
-// LDS slot of element x: one pad slot per 16, so that threads that hold runs
-// of four or eight elements fall in different banks.
-__device__ __forceinline__ uint32_t gslot(uint32_t x) { return x + (x >> 4); }
-
-// NB consecutive bits from g0 of the resident states at once: a task holds the
-// 2^NB elements of one coset of p (and of l), and for each bit first sums
-// Im<l|X_j|p> (REV), then applies a' = c a - i s b. Three bits a pass touch
-// LDS a third as often as one, and need a third of the barriers.
-template <int NB, bool REV>
-__device__ __forceinline__ float resident_pass(float2* l, float2* p, uint32_t N, int g0, float c, float s) {
-    constexpr int K = 1 << NB;
-    float acc = 0.f;
-    for (uint32_t task = threadIdx.x; task < (N >> NB); task += kResidentGradThreads) {
-        const uint32_t b = ((task >> g0) << (g0 + NB)) | (task & ((1u << g0) - 1u));
-        float2 pv[K], lv[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const uint32_t at = gslot(b | ((uint32_t)i << g0));
-            pv[i] = p[at];
-            if (REV) lv[i] = l[at];
-        }
-        auto rotate = [&](float2& x, float2& y) {
-            const float2 u = x, w = y;
-            x = make_float2(fmaf(c, u.x, s * w.y), fmaf(c, u.y, -s * w.x));
-            y = make_float2(fmaf(c, w.x, s * u.y), fmaf(c, w.y, -s * u.x));
-        };
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                if (i & (1 << q)) continue;
-                const int k = i | (1 << q);
-                if (REV) {
-                    acc = fmaf(lv[i].x, pv[k].y, acc);
-                    acc = fmaf(-lv[i].y, pv[k].x, acc);
-                    acc = fmaf(lv[k].x, pv[i].y, acc);
-                    acc = fmaf(-lv[k].y, pv[i].x, acc);
-                    rotate(lv[i], lv[k]);
-                }
-                rotate(pv[i], pv[k]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const uint32_t at = gslot(b | ((uint32_t)i << g0));
-            p[at] = pv[i];
-            if (REV) l[at] = lv[i];
-        }
-    }
-    __syncthreads();
-    return acc;
-}
-
-// Every bit of a layer's mixer.
-template <bool REV>
-__device__ __forceinline__ float resident_layer(float2* l, float2* p, uint32_t N, int n, float c, float s) {
-    float acc = 0.f;
-    int g = 0;
-    for (; g + 3 <= n; g += 3) acc += resident_pass<3, REV>(l, p, N, g, c, s);
-    if (n - g == 2) acc += resident_pass<2, REV>(l, p, N, g, c, s);
-    else if (n - g == 1) acc += resident_pass<1, REV>(l, p, N, g, c, s);
-    return acc;
-}
-
-// Sum over the workgroup: wave sums, then the wave totals in wave order.
-__device__ __forceinline__ double block_sum(double v, double* red) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    __syncthreads();
-    if ((threadIdx.x & 63u) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double sum = 0.0;
-    for (int w = 0; w < kResidentGradThreads / 64; ++w) sum += red[w];
-    return sum;
-}
-
-template <typename CT>
-__device__ __forceinline__ void resident_grad_body(const ResidentGradArgs& a) {
-    __shared__ float2 ls[(1 << 13) + (1 << 9)];
-    __shared__ float2 ps[(1 << 13) + (1 << 9)];
-    __shared__ double red[kResidentGradThreads / 64];
-    constexpr uint32_t NT = kResidentGradThreads;
-    const int n = a.n;
-    const uint32_t N = 1u << n;
-    const uint32_t tid = threadIdx.x;
-    const CT* cost = (const CT*)a.cost;
-    const uint32_t last = (uint32_t)a.lut_len - 1u;
-    const float amp = __builtin_ldexpf(1.0f, -n) == 0.f ? 0.f : sqrtf(__builtin_ldexpf(1.0f, -n));
-    // forward
-    for (int l = 0; l < a.p; ++l) {
-        const float2* lut = a.luts + (size_t)l * a.lut_len;
-        for (uint32_t x = tid; x < N; x += NT) {
-            const float2 e = lut[min((uint32_t)cost[x], last)];
-            ps[gslot(x)] = l == 0 ? make_float2(amp * e.x, amp * e.y) : cmul(ps[gslot(x)], e);
-        }
-        __syncthreads();
-        const float2 cs = a.cs[l];
-        resident_layer<false>(nullptr, ps, N, n, cs.x, cs.y);
-        if ((l + 1) % a.every == 0 && l + 1 < a.p) {
-            float2* ck = a.ckpt + (size_t)((l + 1) / a.every - 1) * N;
-            for (uint32_t x = tid; x < N; x += NT) ck[x] = ps[gslot(x)];
-        }
-    }
-    if (a.p == 0)
-        for (uint32_t x = tid; x < N; x += NT) ps[gslot(x)] = make_float2(amp, 0.f);
-    __syncthreads();
-    // readout and lam = W psi
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (uint32_t x = tid; x < N; x += NT) {
-        const float2 v = ps[gslot(x)];
-        const uint32_t c = cost[x];
-        const float pr = fmaf(v.x, v.x, v.y * v.y);
-        s2 += pr;
-        s1 += (double)c * pr;
-        s0 += c == 0u ? pr : 0.0;
-        const float w = (float)a.w_energy * (float)c + (c == 0u ? (float)a.w_psucc : 0.f);
-        ls[gslot(x)] = make_float2(w * v.x, w * v.y);
-    }
-    s0 = block_sum(s0, red);
-    s1 = block_sum(s1, red);
-    s2 = block_sum(s2, red);
-    if (tid == 0) {
-        a.out[0] = s0;
-        a.out[1] = s1;
-        a.out[2] = s2;
-    }
-    __syncthreads();
-    // reverse
-    for (int l = a.p - 1; l >= 0; --l) {
-        const float2 cs = a.cs[l];
-        const float accb = resident_layer<true>(ls, ps, N, n, cs.x, -cs.y);
-        const float2* lut = a.luts + (size_t)l * a.lut_len;
-        float accg = 0.f;
-        for (uint32_t x = tid; x < N; x += NT) {
-            const uint32_t c = cost[x];
-            const float2 lv = ls[gslot(x)], pv = ps[gslot(x)];
-            accg = fmaf((float)c, fmaf(lv.x, pv.y, -lv.y * pv.x), accg);
-            const float2 e = lut[min(c, last)];
-            const float2 ec = make_float2(e.x, -e.y);
-            ls[gslot(x)] = cmul(lv, ec);
-            ps[gslot(x)] = cmul(pv, ec);
-        }
-        const double db = block_sum((double)accb, red);
-        const double dg = block_sum((double)accg, red);
-        if (tid == 0) {
-            a.out[3 + l] = 2.0 * dg;
-            a.out[3 + a.p + l] = 2.0 * db;
-        }
-        if (l % a.every == 0 && l > 0) {
-            const float2* ck = a.ckpt + (size_t)(l / a.every - 1) * N;
-            for (uint32_t x = tid; x < N; x += NT) ps[gslot(x)] = ck[x];
-        }
-        __syncthreads();
-    }
-}
-
-// One workgroup per gradient.
-template <typename CT>
-__global__ __launch_bounds__(kResidentGradThreads) void resident_grad_batch_kernel(const ResidentGradArgs* args) {
-    const ResidentGradArgs a = args[blockIdx.x];
-    resident_grad_body<CT>(a);
-}
-
 template <typename CT, bool NT, bool USE1, bool VIRT>
 hipError_t launch_adjoint_q(int kind, const AdjointArgs& a, hipStream_t s, bool weigh) {
     const dim3 grid(1u << a.nw), block(kQThreads);
@@ -728,16 +557,6 @@ hipError_t launch_adjoint(int dtype, int kind, const AdjointArgs& a, hipStream_t
                   : launch_adjoint_ct<uint8_t, false>(kind, a, s, weigh);
     return nt ? launch_adjoint_ct<uint16_t, true>(kind, a, s, weigh)
               : launch_adjoint_ct<uint16_t, false>(kind, a, s, weigh);
-}
-
-hipError_t launch_resident_grad_batch(int dtype, const ResidentGradArgs* args, int count, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL(resident_grad_batch_kernel<uint8_t>, dim3((uint32_t)count), dim3(kResidentGradThreads), 0, s,
-                           args);
-    else
-        hipLaunchKernelGGL(resident_grad_batch_kernel<uint16_t>, dim3((uint32_t)count), dim3(kResidentGradThreads), 0, s,
-                           args);
-    return hipGetLastError();
 }
 
 }  // namespace qnae

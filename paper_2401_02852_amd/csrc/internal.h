@@ -244,9 +244,8 @@ constexpr int kAdjointTileBits = 13;
 hipError_t launch_adjoint(int dtype, int kind, const AdjointArgs& a, hipStream_t s, bool weigh = false);
 
 
-// Whole gradient for n <= 13 in one workgroup (lam and psi resident in LDS):
-// forward with exact butterflies (checkpoints of psi every `every` layers in
-// ckpt), readout, then the reverse pass with psi refreshed at checkpoints.
+// Whole gradient for n <= 13 in one workgroup (resident_grad.hip): forward
+// (checkpoints of psi every `every` layers in ckpt), readout, then the reverse pass with psi refreshed at checkpoints.
 struct ResidentGradArgs {
     const void* cost;
     const float2* luts;    // p forward tables exp(-i gamma_l c)
