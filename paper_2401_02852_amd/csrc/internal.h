@@ -171,6 +171,12 @@ hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args
 int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask);
 hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
 
+// Do `rows` phase table rows of `len` entries fit `room` entries? (In 64 bits: a
+// call may have up to 100000 rows of 65536.)
+__host__ __device__ constexpr bool rows_fit(int32_t rows, int32_t len, int32_t room) {
+    return (int64_t)rows * len <= room;
+}
+
 // Whole circuit for n <= 14 in one workgroup (resident.hip).
 struct ResidentArgs {
     const float2* state_in;  // optional initial state (true scale); |+> when null

@@ -122,7 +122,7 @@ __device__ __forceinline__ void reg_body(const ResidentArgs& a, float2* lds, flo
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int layers = a.p > 0 ? a.p : 1;
-    if (!in_tab && layers * a.lut_len <= kTabMax) {
+    if (!in_tab && rows_fit(layers, a.lut_len, kTabMax)) {
         for (int i = threadIdx.x; i < layers * a.lut_len; i += blockDim.x) tab[i] = a.luts[i];
         in_tab = true;
     }

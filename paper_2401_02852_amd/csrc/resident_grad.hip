@@ -343,7 +343,7 @@ __device__ __forceinline__ void reg_body(const ResidentGradArgs& a, float2* ldl,
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // 1: every row in tab, 2: the row in use, 0: none
-    const int mode = (int64_t)a.p * a.lut_len <= kGradTab ? 1 : NT >= 256 && a.lut_len <= kGradTab ? 2 : 0;
+    const int mode = rows_fit(a.p, a.lut_len, kGradTab) ? 1 : NT >= 256 && a.lut_len <= kGradTab ? 2 : 0;
     const int begin = mode == 1 ? a.p * a.lut_len : mode == 2 ? a.lut_len : 0;
     for (int i = threadIdx.x; i < begin; i += kResidentGradThreads) tab[i] = a.luts[i];
     __syncthreads();
