@@ -165,7 +165,7 @@ struct qnae_ctx {
     // sampling: tile masses and prefix sums, uniforms and outcomes
     qnae_host::DevBuf s_dev;
     qnae_host::HostBuf h_sample;
-    uint32_t flip_ticket = 0;           // flip checks launched so far
+    uint32_t flip_ticket = 0;           // of the last flip check (next_ticket)
     qnae_host::DevBuf f_jobs;           // batched flip checks: jobs; pinned: answer, flags, jobs
     qnae_host::HostBuf h_flip;
     int tile_bits = 13;                 // tile size of the plain sweeps (log2 amplitudes)
@@ -209,6 +209,10 @@ constexpr int kFlipEarlyMaxN = 22;
 int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void* cost, int dtype, int n,
              hipStream_t s);
 int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric);
+// The next check's ticket, of single and batched checks alike: 1 .. 2^31 - 1 in
+// turn, so that an answer word cleared to 0 or left by an earlier check is not taken
+// for this one's.
+inline uint32_t next_ticket(uint32_t* last) { return *last = *last % 0x7fffffffu + 1u; }
 // The same for the instances of a batch: the tiled ones with half[i] = 0 are
 // checked, when their states together hold kFlipBatchAmps amplitudes or more
 // (smaller batches are bound by launches, not by bytes). end sets half[i] = 2

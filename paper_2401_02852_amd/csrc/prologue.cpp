@@ -23,8 +23,8 @@ int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void
     a.answer = (uint32_t*)((char*)ctx->h_small.ptr + kSmallFlipAt);
     a.ticket = 0;
     if (cost) {
-        a.ticket = ++ctx->flip_ticket & 0x7fffffffu;
-        *(volatile uint32_t*)a.answer = 2u * (a.ticket ^ 1u);  // another ticket's
+        a.ticket = next_ticket(&ctx->flip_ticket);
+        *(volatile uint32_t*)a.answer = 0u;
     }
     HIP_TRY(timed(ctx, K_PROLOGUE, (double)cost_bytes + (double)bytes, s,
                   [&] { return qnae::launch_prologue(a, dtype, s); }));
@@ -43,7 +43,7 @@ static int wait_ticket(const volatile uint32_t* word, int shift, uint32_t ticket
 
 int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric) {
     const volatile uint32_t* const answer = (const volatile uint32_t*)((char*)ctx->h_small.ptr + kSmallFlipAt);
-    if (int rc = wait_ticket(answer, 1, ctx->flip_ticket & 0x7fffffffu, s)) return rc;
+    if (int rc = wait_ticket(answer, 1, ctx->flip_ticket, s)) return rc;
     *symmetric = (*answer & 1u) == 0u;
     return QNAE_OK;
 }
@@ -81,7 +81,7 @@ int flip_batch_begin(qnae_ctx* ctx, const qnae_instance* inst, int count, const 
         most = std::max(most, fj[q].quads);
         bytes += 16.0 * fj[q].quads;
     }
-    const uint32_t ticket = f->ticket = ++ctx->flip_ticket | 1u;  // never zero
+    const uint32_t ticket = f->ticket = next_ticket(&ctx->flip_ticket);
     *answer = 0u;
     if (int rc = prologue(ctx, ctx->f_jobs.ptr, fj, jobs_bytes, nullptr, QNAE_U8, 0, s)) return rc;
     uint32_t* const word = (uint32_t*)((char*)ctx->small.ptr + kSmallFlipAt);
