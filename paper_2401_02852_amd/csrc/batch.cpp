@@ -336,6 +336,7 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     if (count == 0) return QNAE_OK;
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
+    DrainOnExit drain{s};
 
     // ---- flip-symmetric diagonals run on half the state; the tables are built
     // and uploaded while the check runs (behind a cost build, say) --------------
@@ -513,7 +514,7 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     double* d_results = (double*)ctx->b_results.ptr;
     HIP_TRY(hipMemcpyAsync(ctx->h_results.ptr, d_results, sizeof(double) * 3 * count, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipEventRecord(ctx->staging_done, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     const double* r = (const double*)ctx->h_results.ptr;
     for (int i = 0; i < count; ++i) {
         const double sc = std::norm(scale[i]) * (inst[i].half ? 2.0 : 1.0);

@@ -30,6 +30,7 @@ namespace {
 // through pinned memory that the kernels write.
 int resident_grads(qnae_ctx* ctx, const qnae_grad_job* jobs, const std::vector<int>& pick, double w_psucc,
                    double w_energy, int every, qnae_result* out, hipStream_t s) {
+    DrainOnExit drain{s};
     Blob B, C, T;  // uploaded; checkpoints; tables
     size_t rows = 0;
     int max_m = 0;
@@ -100,7 +101,7 @@ int resident_grads(qnae_ctx* ctx, const qnae_grad_job* jobs, const std::vector<i
                                                     (int)group[g].size(), s);
         }));
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     const double* r = ho;
     for (int i : pick) {
         const qnae_grad_job& j = jobs[i];
@@ -140,6 +141,7 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     }
 
     // ---- tiled path ----------------------------------------------------------
+    DrainOnExit drain{s};
     const int TB = qnae::kAdjointTileBits;
     const int nseg = p > 0 ? (p + every - 1) / every : 1;
     const std::vector<Group> groups = make_groups(n, TB, ctx->min_low_run, ctx->page_bit, 0);
@@ -347,7 +349,7 @@ int qnae_qaoa_grad(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int3
     }
     const double* r = (const double*)(h + res_at);  // the reduction writes pinned memory: no copy follows it
     HIP_TRY(qnae::launch_final_reduce_rows(parts, tiles, (double*)(h + res_at), total_aops + 1, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     const double twice = half ? 4.0 : 2.0;
     for (int l = 0; l < p; ++l) dgammas[l] = dbetas[l] = 0.0;
     for (int k = 0; k < total_aops; ++k) {

@@ -185,6 +185,22 @@ namespace qnae_host {
 // Makes the context's device current, waits until pinned staging is free and
 // orders s behind the context's last cost build.
 int enter(qnae_ctx* ctx, hipStream_t s);
+// Waits for the stream when a call leaves before its own wait (an error, an
+// exception): launches still in flight read the context's pinned staging and write
+// its scratch, which the next call reuses, perhaps from another stream.
+struct DrainOnExit {
+    hipStream_t s;
+    bool on = true;
+    ~DrainOnExit() {
+        if (on) (void)hipStreamSynchronize(s);
+    }
+};
+// The call's own wait.
+inline hipError_t finish(DrainOnExit& d) {
+    const hipError_t e = hipStreamSynchronize(d.s);
+    d.on = e != hipSuccess;
+    return e;
+}
 // With the context's device current: looks up that device's static scratch
 // array of qnae_qaoa_run_noalloc (once per device) and reserves the
 // context's fixed pinned staging for it.

@@ -96,6 +96,7 @@ extern "C" int qnae_qaoa_run_noalloc(qnae_ctx* ctx, const void* cost_dev, int32_
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     if (!ctx->na_dev || ctx->na_host.bytes < kHostBytes) return fail(QNAE_EINVAL, "context without no-alloc scratch");
     hipStream_t s = (hipStream_t)stream;
+    DrainOnExit drain{s};
     const bool keep = state_dev != nullptr;
 
     char* const dev = (char*)ctx->na_dev;
@@ -155,7 +156,7 @@ extern "C" int qnae_qaoa_run_noalloc(qnae_ctx* ctx, const void* cost_dev, int32_
         if (keep && !half && p > 0 && h_flips[p]) HIP_TRY(qnae::launch_reverse(psi, 1ull << n, s));
         HIP_TRY(qnae::launch_final_reduce(d_partials, tiles >> (half ? 1 : 0), h_result, s));
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     const double readout_scale = std::norm(final_scale) * (half ? 2.0 : 1.0);
     out->p_success = h_result[0] * readout_scale;
     out->expected_cost = h_result[1] * readout_scale;

@@ -176,6 +176,7 @@ int run(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int32_t n, int3
         return fail(QNAE_EINVAL, "n=%d: half-state runs need n > %d (smaller n: qnae_qaoa_run)", n, kResidentMaxN);
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
+    DrainOnExit drain{s};
     const bool keep = state_dev != nullptr;
     const int T = p > 0 ? p : 1;
     const int lut_len = m + 1;
@@ -270,7 +271,7 @@ int run(qnae_ctx* ctx, const void* cost_dev, int32_t cost_dtype, int32_t n, int3
             return qnae::launch_final_reduce((const double*)ctx->partials.ptr, blocks, sums, s);
         }));
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     const double readout_scale = std::norm(final_scale) * (half ? 2.0 : 1.0);
     out->p_success = sums[0] * readout_scale;
     out->expected_cost = sums[1] * readout_scale;

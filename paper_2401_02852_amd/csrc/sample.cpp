@@ -26,6 +26,7 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
             return fail(QNAE_EINVAL, "uniforms[%d]=%g outside [0, 1)", q, uniforms[q]);
     if (int rc = enter(ctx, (hipStream_t)stream)) return rc;
     hipStream_t s = (hipStream_t)stream;
+    DrainOnExit drain{s};
     const size_t T = (((size_t)1 << n) + (1u << qnae::kSampleTileBits) - 1) >> qnae::kSampleTileBits;
     Blob B;
     const size_t mass_at = B.take(sizeof(double) * T);
@@ -53,7 +54,7 @@ int qnae_sample(qnae_ctx* ctx, const void* state_dev, int32_t n, const void* cos
         HIP_TRY(qnae::launch_sample_draws(psi, n, cost_dev, cost_dtype, u, count, mass, pref, seg,
                                           (uint64_t*)(h + out_at),
                                           sample_costs ? (int32_t*)(h + cost_at) : nullptr, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(finish(drain));
     if (count == 0) return QNAE_OK;
     const uint64_t* o = (const uint64_t*)(h + out_at);
     if (o[0] == ~0ull) return fail(QNAE_EINVAL, "state has zero norm");

@@ -160,10 +160,64 @@ void tickets() {
     CHECK(qnae_destroy(ctx) == QNAE_OK);
 }
 
+// Every call of `fn` that ends in an error has waited for what it had launched,
+// whichever step failed; then the same call succeeds.
+template <typename F>
+void drains(const char* what, F&& fn) {
+    for (bool symmetric : {false, true}) {
+        g_symmetric = symmetric;
+        for (int at = 1;; ++at) {
+            CHECK(at < 500);
+            qnae_ctx* ctx = nullptr;
+            CHECK(qnae_create(&ctx, 0) == QNAE_OK);
+            g_calls = 0;
+            g_in_flight = 0;
+            g_fail_at = at;
+            const int rc = fn(ctx);
+            const bool failed = g_calls >= at;
+            g_fail_at = 0;
+            if ((rc != QNAE_OK) != failed || g_in_flight != 0) {
+                std::printf("%s, step %d: status %d, %d launches in flight\n", what, at, rc, g_in_flight);
+                std::exit(1);
+            }
+            CHECK(fn(ctx) == QNAE_OK && g_in_flight == 0);
+            CHECK(qnae_destroy(ctx) == QNAE_OK);
+            if (!failed) break;
+        }
+    }
+}
+
+void error_exits() {
+    double dg[3], db[3];
+    qnae_result out[16];
+    for (int n : {12, 16, 20, 23})
+        for (int m : {40, 255})
+            drains("run", [&](qnae_ctx* ctx) {
+                return qnae_qaoa_run(ctx, g_cost, QNAE_U8, n, m, g_angles, g_angles, 3, nullptr, out, nullptr);
+            });
+    for (int n : {12, 16, 20, 23})
+        drains("gradient", [&](qnae_ctx* ctx) {
+            return qnae_qaoa_grad(ctx, g_cost, QNAE_U8, n, 40, g_angles, g_angles, 3, 1.0, 0.0, 2, dg, db, out, nullptr);
+        });
+    for (int n : {12, 18, 20})
+        drains("batch", [&](qnae_ctx* ctx) {
+            auto jobs = batch(8, n);
+            jobs[0].n = 14;
+            jobs[7].n = 20;
+            return qnae_qaoa_run_batched(ctx, jobs.data(), 8, out, nullptr);
+        });
+    drains("sample", [&](qnae_ctx* ctx) {
+        const double u[4] = {0.1, 0.5, 0.7, 0.9};
+        uint64_t x[4];
+        return qnae_sample(ctx, g_cost, 16, nullptr, QNAE_U8, u, 4, x, nullptr, nullptr);
+    });
+}
+
 }  // namespace
 
 int main() {
     tickets();
+    error_exits();
     std::printf("host paths ok\n");
     return 0;
 }
