@@ -9,12 +9,15 @@
 //   chunk level  C[i]: sums of chunk masses, sequential within groups of 32
 //                chunks and over the groups;
 //   tile level   P[t] = C[i] + (sequential sum of the tile masses before t in
-//                its chunk), tiles of 4096 consecutive amplitudes;
+//                its chunk), but at most C[i + 1]; tiles of 4096 consecutive
+//                amplitudes;
 //   segments     S[k]: where each 256 amplitudes start in their tile (sums of
 //                16 consecutive probabilities, their block-wide exclusive scan).
-// The first two are nondecreasing by construction (sequential sums of
-// nonnegative terms, and FP64 addition of a fixed offset is monotone). The
-// in-tile scan is a shuffle tree whose rounding may differ from a sequential
+// The first two are nondecreasing by construction: sequential sums of nonnegative
+// terms are, FP64 addition of a fixed offset keeps order, and the bound by the next
+// chunk's start takes back the unit by which (C + before) + tile can round above C +
+// (before + tile). The search counts the places at or below its target and relies
+// on it: its tile never starts above the target. The in-tile scan is a shuffle tree whose rounding may differ from a sequential
 // sum, so a draw takes the highest segment with mass whose start is at or below
 // its remainder, in it the highest lane of four amplitudes likewise and, if
 // rounding carries the remainder past that lane's walk, the lane's last nonzero
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(64) void chunk_run_kernel(const double* __restrict_
 }
 
 // The chunk and tile levels together: P[t] = C[t / chunk] + (prefix within the
-// chunk), one tile per thread, and P[T] = the total. Every workgroup forms C
+// chunk), bounded by the next chunk's start, one tile per thread, and P[T] = the total. Every workgroup forms C
 // for itself, 32 groups of 32 chunks: prefixes within the groups, 32 threads
 // at once, then over the groups (two chains of 32 additions; one thread over
 // all 1024 took 13 us and a launch of its own).
@@ -179,9 +182,11 @@ __global__ __launch_bounds__(256) void chunk_add_kernel(double* __restrict__ pre
     }
     __syncthreads();
     const uint32_t t = blockIdx.x * 256u + tid;
+    auto start = [&](uint32_t i) { return i < kSampleChunks ? g[i / kGroup] + c[i + i / kGroup] : g[kGroup]; };
     if (t < T) {
         const uint32_t i = t >> chunk_bits;
-        pref[t] = (g[i / kGroup] + c[i + i / kGroup]) + pref[t];
+        const double p = start(i) + pref[t], next = start(i + 1u);
+        pref[t] = p < next ? p : next;
     }
     if (t == 0) pref[T] = g[kGroup];
 }

@@ -186,3 +186,31 @@ def test_sample_of_an_infinite_mass_stays_in_range(q, n, at):
     st[0] = float("nan")
     with pytest.raises(Exception):
         q.sample(st, n, u, cost=c)
+
+
+def test_sample_targets_between_roundings_of_a_chunk_start(q):
+    """A target one unit above 1/2 where the mass before tile 68, 1/2 and two pieces
+    of 0.6 units, rounds to one unit more when it is summed in another order (n = 23:
+    chunks of 2 tiles, groups of 32 chunks). Tile 67, the last of its chunk, has a
+    mass far below a unit that is not in its first amplitude. Whatever the order,
+    a draw has an amplitude, and one beside the target."""
+    import torch
+    n, tile, unit = 23, 4096, 2.0 ** -53
+    psi = np.zeros(1 << n, dtype=np.complex64)
+    psi[5] = 0.5 + 0.5j                                          # mass 1/2 exactly, in the first group
+    psi[64 * tile + 9] = psi[66 * tile + 11] = np.sqrt(0.6 * unit)
+    psi[67 * tile + 700] = 1e-18                                 # 1e-36
+    psi[68 * tile + 3] = 0.5                                     # mass 1/4
+    total = 0.75 + unit
+    u = [0.0, 0.25]
+    for k in range(-2, 5):                                       # targets 1/2 + k units, each hit exactly
+        target = 0.5 + k * unit
+        v = target / total
+        v = next(x for x in (v, np.nextafter(v, 0), np.nextafter(v, 1)) if x * total == target)
+        u.append(v)
+    got, _ = q.sample(torch.from_numpy(psi).cuda(), n, u)
+    x = got.astype(np.int64)
+    print("\n[sample] outcomes", [(int(i) // tile, int(i) % tile) for i in x], flush=True)
+    assert np.all(psi[x] != 0), "an outcome without an amplitude"
+    assert np.all(np.diff(x) >= 0), "outcomes follow the uniforms"
+    assert x[0] == x[1] == x[2] == x[3] == 5 and x[-1] == 68 * tile + 3
