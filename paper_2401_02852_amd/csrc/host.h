@@ -221,9 +221,10 @@ constexpr int kFlipEarlyMaxN = 22;
 // hold that many) of pinned src to dst and, unless cost is null, checks the
 // diagonal; flip_answer waits for the check's answer by watching the pinned
 // word that it writes, so that work queued behind it need not be waited for.
-// One check at a time on a context.
+// One check at a time on a context. profiled: as the context's profiler has it
+// (which allocates: never from the no-alloc run).
 int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void* cost, int dtype, int n,
-             hipStream_t s);
+             hipStream_t s, bool profiled = true);
 int flip_answer(qnae_ctx* ctx, hipStream_t s, bool* symmetric);
 // The next check's ticket, of single and batched checks alike: 1 .. 2^31 - 1 in
 // turn, so that an answer word cleared to 0 or left by an earlier check is not taken

@@ -114,7 +114,7 @@ extern "C" int qnae_qaoa_run_noalloc(qnae_ctx* ctx, const void* cost_dev, int32_
     for (int l = 0; l < p; ++l) h_flips[l + 1] = h_flips[l] ^ h_forms[l].flip;
     const bool check = p > 0 && n >= kFlipMinN;  // as qnae_qaoa_run
     if (int rc = prologue(ctx, d_tables, h_tables, sizeof(float2) * ((size_t)T * lut_len + p),
-                          check ? cost_dev : nullptr, cost_dtype, n, s))
+                          check ? cost_dev : nullptr, cost_dtype, n, s, false))
         return rc;
     bool half = false;
 

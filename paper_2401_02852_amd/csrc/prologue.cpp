@@ -11,7 +11,7 @@ namespace qnae_host {
 static constexpr size_t kFlipFlagsAt = 64;  // pinned: the ticket, then a flag per checked instance, then the jobs
 
 int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void* cost, int dtype, int n,
-             hipStream_t s) {
+             hipStream_t s, bool profiled) {
     qnae::PrologueArgs a;
     a.dst = (uint4*)dst;
     a.src = (const uint4*)src;
@@ -26,8 +26,8 @@ int prologue(qnae_ctx* ctx, void* dst, const void* src, size_t bytes, const void
         a.ticket = next_ticket(&ctx->flip_ticket);
         *(volatile uint32_t*)a.answer = 0u;
     }
-    HIP_TRY(timed(ctx, K_PROLOGUE, (double)cost_bytes + (double)bytes, s,
-                  [&] { return qnae::launch_prologue(a, dtype, s); }));
+    auto launch = [&] { return qnae::launch_prologue(a, dtype, s); };
+    HIP_TRY(profiled ? timed(ctx, K_PROLOGUE, (double)cost_bytes + (double)bytes, s, launch) : launch());
     return QNAE_OK;
 }
 

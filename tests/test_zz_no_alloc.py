@@ -100,3 +100,24 @@ def test_noalloc_rejects_sizes_beyond_its_scratch(q):
                                        ctypes.byref(out), None)
         assert rc == -1 and msg in lib.qnae_last_error(ctx.handle), (n, m, p)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [12, 16, 20])
+def test_noalloc_stays_out_of_the_profiler(q, n):
+    """Profiling allocates events and records, so this call takes no part in it:
+    with profiling on it leaves no entry, not one of its launches, and the
+    same results."""
+    import torch
+    ctx = q.Context()
+    cl = inst.instance(n, 3, 40, n)
+    cost = q.build_cost_diagonal(cl, n, ctx=ctx)
+    state = torch.empty(1 << n, dtype=torch.complex64, device="cuda")
+    g, b = np.array([0.3, 0.8]), np.array([0.4, 1.3])
+    want = noalloc(q, ctx, cost, n, 40, g, b, state)
+    ctx.profile(True)
+    for _ in range(3):
+        assert noalloc(q, ctx, cost, n, 40, g, b, state) == want
+    assert ctx.profile_read() == {}
+    assert tuple(q.qaoa_run(cost, n, 40, g, b, state=state, ctx=ctx)) == want
+    assert ctx.profile_read() != {}
+    ctx.close()
