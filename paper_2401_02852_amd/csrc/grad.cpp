@@ -24,6 +24,13 @@ using qnae::SweepArgs;
 
 namespace {
 
+// g modulo 2 pi, for phases exp(i g c) with whole c that are formed from the product
+// g c: its rounding turns them by up to g c 2^-53, which shows in FP32 from g c = 1e8
+// on. The library's sine and cosine reduce their argument exactly.
+double reduced(double g) {
+    return std::fabs(g) <= 3.2 ? g : std::atan2(std::sin(g), std::cos(g));
+}
+
 // The gradients of the jobs `pick` (n <= 13), one launch per cost type. Uploaded:
 // a record per phase table row, the (cos, sin) of the mixers and the kernel
 // arguments; the tables are built on the device, the results come back
@@ -83,7 +90,7 @@ int resident_grads(qnae_ctx* ctx, const qnae_grad_job* jobs, const std::vector<i
         a.every = every;
         res += 3 + 2 * (size_t)j.p;
         for (int l = 0; l < j.p; ++l, ++row) {
-            hr[row] = {j.gammas[l], 1.0, 0.0, -1.0, tables + (size_t)l * (size_t)(j.m + 1), j.m, 0};
+            hr[row] = {reduced(j.gammas[l]), 1.0, 0.0, -1.0, tables + (size_t)l * (size_t)(j.m + 1), j.m, 0};
             hc[row] = make_float2((float)std::cos(j.betas[l]), (float)std::sin(j.betas[l]));
         }
     }

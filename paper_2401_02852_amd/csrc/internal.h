@@ -81,7 +81,8 @@ struct FlipJob {
 hipError_t launch_flip_batch(FlipJob* jobs, int count, uint32_t max_quads, uint32_t* flags, uint32_t* word,
                              uint32_t ticket, uint32_t* answer, hipStream_t s);
 
-// A phase table row: out[c] = (re + i im) exp(sign i g c), c = 0 .. m.
+// A phase table row: out[c] = (re + i im) exp(sign i g c), c = 0 .. m; |g| <= 3.2, as
+// the phase is formed from the rounded product g c.
 struct PhaseRow {
     double g, re, im, sign;
     float2* out;

@@ -255,3 +255,34 @@ def test_adam_steps_raise_success_probability(q):
         opt.step()
         first = ps.item() if first is None else first
     assert ps.item() > 2 * first
+
+
+def _reduced(x):
+    """x modulo 2 pi in (-pi, pi], from the correctly reduced sine and cosine."""
+    return np.arctan2(np.sin(x), np.cos(x))
+
+
+@pytest.mark.parametrize("n,m,u16", [(6, 40, False), (12, 250, False), (13, 700, True)])
+@pytest.mark.parametrize("size", [1e3, 1e8, 1e12, 1e300])
+def test_gradient_at_large_angles(q, n, m, u16, size):
+    """A phase exp(-i gamma c) has the period 2 pi in gamma because c is an integer,
+    so gradients at large gammas are those at the reduced ones, and their readout is
+    that of the run at the same angles. (Rounding gamma c itself would turn the phase
+    by up to gamma c 2^-53: half a turn at gamma = 1e14, 1e-4 at 1e10, c = 100.)"""
+    import torch
+    rng = np.random.default_rng(n)
+    cost = rng.integers(0, m + 1, 1 << n)
+    cost[:5] = 0
+    dev = torch.from_numpy(cost.astype(np.uint16 if u16 else np.uint8)).cuda()
+    g = size * rng.uniform(-1.0, 1.0, 4)
+    b = np.array([0.4, -0.3, 1.2, 0.5])
+    r = _reduced(g)
+    dg, db, res = q.qaoa_grad(dev, n, m, g, b, w_psucc=1.0, w_energy=0.01)
+    run = q.qaoa_run(dev, n, m, g, b)
+    ref = oracle.qaoa(cost, n, r, b)
+    rg, rb, _ = oracle.qaoa_grad(cost, n, r, b, 1.0, 0.01)
+    assert abs(res.p_success - ref[0]) <= 1e-5 and abs(run.p_success - ref[0]) <= 1e-5
+    assert abs(res.expected_cost - ref[1]) <= 1e-5 * ref[1]
+    scale = max(np.max(np.abs(rg)), np.max(np.abs(rb)))
+    assert np.max(np.abs(dg - rg)) <= 1e-4 * scale + 1e-5
+    assert np.max(np.abs(db - rb)) <= 1e-4 * scale + 1e-5
