@@ -180,7 +180,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
     auto off3 = [&](int j) -> uint64_t { return scat(ss<TB, IN>(j)); };
     auto at3 = [&](int j) -> uint64_t { return up3(j) ? a.mir - o3 - off3(j) : o3 + off3(j); };
 
-    uint32_t cvp[NC];
+    // What the tile reads goes out together, before any of it is waited for: the
+    // table, the costs, the state. (With the costs packed before the state was asked for,
+    // the compiler made a chain of two costs at a time of them in the final kind
+    // and with 16-bit costs: whole state, n = 30, one layer 6.76 -> 6.36 ms, ten with 16-bit
+    // costs 73.5 -> 65.4, half state 37.5 -> 33.2.)
+    static_assert(!LUT_LDS || NT >= 256, "a table entry per thread");
+    float2 entry = make_float2(0.f, 0.f);
+    if (NEED_LUT && LUT_LDS && (int)threadIdx.x < a.lut_len) entry = a.lut[threadIdx.x];
+    CT raw[COST3 ? 16 : 1];
     if (COST3) {
         // with cflip (never on a half state) the costs are read at the complemented index
         const uint64_t all = (1ull << a.n) - 1ull;
@@ -188,23 +196,36 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         const CT* const c3 = (const CT*)a.cost + (cf ? o3 ^ all : o3);
         const CT* const cv = VIRT ? (const CT*)a.cost + (a.mir - o3) : c3;
 #pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int64_t d = (int64_t)off3(j);
+            raw[j] = up3(j) ? cv[-d] : c3[cf ? -d : d];
+        }
+    }
+    float2 v[16];
+    if (!INIT) {
+        const float2* const p0 = a.psi_in + base0 + scat(st<TB, 0>(lane, wave));
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const float4 q = ld_state(p0 + scat(ss<TB, 0>(2 * jj)));
+            v[2 * jj] = make_float2(q.x, q.y);
+            v[2 * jj + 1] = make_float2(q.z, q.w);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (NEED_LUT && LUT_LDS && (int)threadIdx.x < a.lut_len) lut_s[threadIdx.x] = entry;
+    uint32_t cvp[NC];
+    if (COST3) {
+#pragma unroll
         for (int i = 0; i < NC; ++i) {
             uint32_t wv = 0u;
 #pragma unroll
-            for (int q = 0; q < PK; ++q) {
-                const int j = PK * i + q;
-                const int64_t d = (int64_t)off3(j);
-                const CT c = up3(j) ? cv[-d] : c3[cf ? -d : d];
-                wv |= (uint32_t)c << (8 * sizeof(CT) * q);
-            }
+            for (int q = 0; q < PK; ++q) wv |= (uint32_t)raw[PK * i + q] << (8 * sizeof(CT) * q);
             cvp[i] = wv;
         }
-        // packed as they arrive; the state loads issued after them stay in flight
+        // packed as they arrive, with the state loads still in flight
 #pragma unroll
         for (int i = 0; i < NC; ++i) asm volatile("" : "+v"(cvp[i]));
     }
-    if (NEED_LUT && LUT_LDS)
-        for (int i = threadIdx.x; i < a.lut_len; i += NT) lut_s[i] = a.lut[i];
     // Cost values above m are a caller error; the clamp keeps table reads in bounds.
     const uint32_t lut_last = (uint32_t)a.lut_len - 1u;
     auto lut = [&](uint32_t c) -> float2 { return LUT_LDS ? lut_s[c] : a.lut[min(c, lut_last)]; };
@@ -212,7 +233,6 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         return (cvp[j / PK] >> (8 * sizeof(CT) * (j % PK))) & (sizeof(CT) == 1 ? 0xffu : 0xffffu);
     };
 
-    float2 v[16];
     if (KIND == SK_FIRST) {
         // adjacent costs of a slot pair along tile bit 0; 64 lanes cover 128
         using PT = typename std::conditional<sizeof(CT) == 1, uint16_t, uint32_t>::type;
@@ -233,13 +253,6 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
 #pragma unroll
         for (int j = 0; j < 16; ++j) v[j] = lut(cval(j));
     } else {
-        const float2* const p0 = a.psi_in + base0 + scat(st<TB, 0>(lane, wave));
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            const float4 q = ld_state(p0 + scat(ss<TB, 0>(2 * jj)));
-            v[2 * jj] = make_float2(q.x, q.y);
-            v[2 * jj + 1] = make_float2(q.z, q.w);
-        }
         mix_down<TB, USE1, VIRT, PLANES>(lds, v, a.pre_mask, a.pre_t, lane, wave);
     }
     if (CKPT) {
@@ -255,8 +268,21 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, uint32_t t, doubl
         }
     }
     if (PHASE) {
+        if constexpr (LUT_LDS) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = cmul(v[j], lut(cval(j)));
+            for (int j = 0; j < 16; ++j) v[j] = cmul(v[j], lut(cval(j)));
+        } else {
+            // eight reads of the table in memory at a time: left alone they are a chain of 16
+#pragma unroll
+            for (int h = 0; h < 16; h += 8) {
+                float2 e[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) e[j] = lut(cval(h + j));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[h + j] = cmul(v[h + j], e[j]);
+            }
+        }
         mix_up<TB, USE1, VIRT, PLANES>(lds, v, a.post_mask, a.post_t, lane, wave);
         float2* const p0 = a.psi + base0 + scat(st<TB, 1>(lane, wave));
 #pragma unroll
