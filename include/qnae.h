@@ -387,9 +387,12 @@ typedef struct {
  * `reps` four-layer runs of
  * an n-qubit state in the context's scratch memory, on `stream`, ranks them
  * by the time per layer of a ten-layer run (extrapolated linearly in the
- * layer count from the two; written to ms_per_layer), keeps the fastest for
+ * layer count from the two), keeps the fastest for
  * later qnae_qaoa_run calls at this n and cost type on this context, and
- * writes it to *out. Needs 2^n * (8 + cost bytes) of device memory. For n <= 14 the
+ * writes it to *out. From n = 20 on, where flip-symmetric diagonals run on half
+ * the state, both the whole-state run and the half-state run are timed, and the
+ * rank is the sum of their times per stored amplitude. ms_per_layer is the
+ * whole-state run's. Needs 2^n * (8 + cost bytes) of device memory. For n <= 14 the
  * whole circuit runs in one workgroup and there is nothing to tune: *out is
  * all zeros. Synchronous. Errors: QNAE_EINVAL (n outside [1, QNAE_MAX_N], bad
  * cost_dtype, reps outside [1, 1000], null out), QNAE_ENOMEM, QNAE_EHIP. */

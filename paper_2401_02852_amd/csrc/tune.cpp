@@ -129,14 +129,13 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
         }
         return hipSuccess;
     };
-    qnae_tune best{0, 0, 0, 0, 1e300};
     hipError_t err = hipSuccess;
     // Mean time of one run of a plan of `layers` layers under shape t.
-    auto time_plan = [&](const qnae_tune& t, int layers, double* ms_out) -> hipError_t {
+    auto time_plan = [&](const qnae_tune& t, int layers, bool half, double* ms_out) -> hipError_t {
         SweepPlan P;
         plan_sweeps(P, n, m, layers, cost_dtype, t.tile_bits, t.low_run_bits, t.page_bit, t.split, false, forms,
                     final_scale);
-        P.half = n >= kFlipMinN;  // as a run on this (flip-symmetric) diagonal
+        P.half = half;
         hipError_t e = run(P, t.tile_bits);  // warm-up
         if (e || (e = hipEventRecord(ev[0], s))) return e;
         for (int r = 0; r < reps && !e; ++r) e = run(P, t.tile_bits);
@@ -146,17 +145,32 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
         *ms_out = ms / reps;
         return hipSuccess;
     };
-    qnae_tune best_of[3] = {best, best, best};  // fastest split-0 shape per tile size
-    auto time_shape = [&](const qnae_tune& t) {
+    struct Timed {
+        qnae_tune shape{0, 0, 0, 0, 0.0};
+        double rank = 1e300;
+    };
+    Timed best, best_of[3];  // of all; the fastest split-0 shape per tile size
+    auto per_layer = [&](const qnae_tune& t, bool half) -> double {
         double t_lo = 0.0, t_hi = 0.0;
-        if ((err = time_plan(t, p_lo, &t_lo)) || (err = time_plan(t, p, &t_hi))) return;
+        if ((err = time_plan(t, p_lo, half, &t_lo)) || (err = time_plan(t, p, half, &t_hi))) return 0.0;
         // (timing noise on a tiny state could make the four-layer run look no
         // slower than the two-layer one: then its own time per layer is used)
-        const double ten = t_hi > t_lo ? t_lo + (10.0 - p_lo) * (t_hi - t_lo) / (p - p_lo) : t_hi * 10.0 / p;
-        const qnae_tune timed{t.tile_bits, t.low_run_bits, t.page_bit, t.split, ten / 10.0};
-        if (timed.ms_per_layer < best.ms_per_layer) best = timed;
-        qnae_tune& b = best_of[t.tile_bits - 12];
-        if (t.split == 0 && timed.ms_per_layer < b.ms_per_layer) b = timed;
+        return (t_hi > t_lo ? t_lo + (10.0 - p_lo) * (t_hi - t_lo) / (p - p_lo) : t_hi * 10.0 / p) / 10.0;
+    };
+    // One shape serves diagonals with and without flip symmetry (its key is n and
+    // the cost type), so where those run on different plans both are timed and count
+    // alike per stored amplitude. Ranked so, a ten-layer run is within 1.6% of its own
+    // best shape at n = 20 .. 30, whole or half; ranked on the half-state plan alone a
+    // whole one was 7.6% off at n = 24 (14-bit tiles, page bit 64 against 18: half
+    // 358 and 364 us, whole 706 and 656), on the whole one alone a half one 5.6% at n = 26.
+    auto time_shape = [&](const qnae_tune& t) {
+        const double whole = per_layer(t, false);
+        const double half = n >= kFlipMinN && !err ? per_layer(t, true) : 0.0;
+        if (err) return;
+        const Timed timed{{t.tile_bits, t.low_run_bits, t.page_bit, t.split, whole}, whole + 2.0 * half};
+        if (timed.rank < best.rank) best = timed;
+        Timed& b = best_of[t.tile_bits - 12];
+        if (t.split == 0 && timed.rank < b.rank) b = timed;
     };
     for (int TB = 12; TB <= 14 && !err; ++TB)
         for (int low = 4; low <= 5 && !err; ++low)
@@ -165,15 +179,17 @@ int qnae_autotune(qnae_ctx* ctx, int32_t n, int32_t cost_dtype, int32_t reps, qn
     // The splits of the fastest shape of every tile size: a split can
     // reorder the tile sizes (at n = 30, 14-bit tiles led 13-bit ones
     // without splits, and 13-bit tiles with split 1 were fastest overall).
-    for (const qnae_tune& base : best_of)
+    for (const Timed& b : best_of) {
+        const qnae_tune& base = b.shape;
         if (!err && base.tile_bits != 0 && has_split(n, base))
             for (int split = 1; split <= 3 && !err; ++split)
                 time_shape(qnae_tune{base.tile_bits, base.low_run_bits, base.page_bit, split, 0.0});
+    }
     (void)hipEventDestroy(ev[0]);
     (void)hipEventDestroy(ev[1]);
     if (err) return fail(QNAE_EHIP, "autotune: %s", hipGetErrorString(err));
-    ctx->tunes[{n, cost_dtype}] = best;
-    *out = best;
+    ctx->tunes[{n, cost_dtype}] = best.shape;
+    *out = best.shape;
     return QNAE_OK;
 } catch (...) {
     return host_exception();

@@ -22,6 +22,8 @@ int g_fail_at = 0;   // the call that fails, counted from 1 (0: none)
 int g_calls = 0;     // calls that can fail, so far
 int g_in_flight = 0; // launches and copies since the last wait
 bool g_symmetric = false;
+double g_time = 0.0;          // ms that the sweeps launched so far take
+double g_sweep_ms[2][15];     // per sweep: whole or half state, tile bits
 std::vector<uint32_t> g_tickets;
 
 hipError_t step(hipError_t error) { return ++g_calls == g_fail_at ? error : hipSuccess; }
@@ -54,11 +56,13 @@ hipError_t hipHostFree(void* p) { return std::free(p), hipSuccess; }
 hipError_t hipMemset(void* p, int v, size_t n) { return std::memset(p, v, n), hipSuccess; }
 hipError_t hipMemsetAsync(void*, int, size_t, hipStream_t) { return launched(); }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return launched(); }
-hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)std::malloc(1), hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)std::malloc(sizeof(double)), hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { return std::free((void*)e), hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.f, hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return step(hipErrorUnknown); }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+    return *ms = (float)(*(double*)b - *(double*)a), hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { return *(double*)e = g_time, step(hipErrorUnknown); }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)std::malloc(1), hipSuccess; }
@@ -96,7 +100,10 @@ hipError_t launch_flip_batch(FlipJob*, int count, uint32_t, uint32_t* flags, uin
     return hipSuccess;
 }
 hipError_t launch_phase_rows(const PhaseRow*, int, int, hipStream_t) { return launched(); }
-hipError_t launch_sweep(int, int, int, const SweepArgs&, hipStream_t) { return launched(); }
+hipError_t launch_sweep(int tb, int, int, const SweepArgs& a, hipStream_t) {
+    g_time += g_sweep_ms[a.half ? 1 : 0][tb];
+    return launched();
+}
 hipError_t launch_sweep_ckpt(int, const SweepArgs&, hipStream_t) { return launched(); }
 hipError_t launch_sweep_batch(int, int, int, const SweepArgs*, const uint32_t*, int, uint32_t, hipStream_t, bool, int) {
     return launched();
@@ -213,11 +220,34 @@ void error_exits() {
     });
 }
 
+// The tile shape is ranked on whole-state and half-state runs together where
+// diagonals with and without the symmetry share it, on whole-state ones below.
+void autotune() {
+    qnae_ctx* ctx = nullptr;
+    CHECK(qnae_create(&ctx, 0) == QNAE_OK);
+    const double whole[3] = {100.0, 60.0, 50.0}, half[3] = {10.0, 11.0, 40.0};
+    for (int i = 0; i < 3; ++i) {
+        g_sweep_ms[0][12 + i] = whole[i];
+        g_sweep_ms[1][12 + i] = half[i];
+    }
+    qnae_tune t;
+    CHECK(qnae_autotune(ctx, 20, QNAE_U8, 2, &t, nullptr) == QNAE_OK);
+    CHECK(t.tile_bits == 13);  // 100 + 20, 60 + 22, 50 + 80
+    // two groups, p + 1 sweeps: three and five of them timed, eleven for ten layers
+    CHECK(t.ms_per_layer > 65.9 && t.ms_per_layer < 66.1);
+    CHECK(qnae_autotune(ctx, 19, QNAE_U8, 2, &t, nullptr) == QNAE_OK);
+    CHECK(t.tile_bits == 14 && t.ms_per_layer > 54.9 && t.ms_per_layer < 55.1);
+    qnae_tune in_use;
+    CHECK(qnae_get_tune(ctx, 20, QNAE_U8, &in_use) == QNAE_OK && in_use.tile_bits == 13);
+    CHECK(qnae_destroy(ctx) == QNAE_OK);
+}
+
 }  // namespace
 
 int main() {
     tickets();
     error_exits();
+    autotune();
     std::printf("host paths ok\n");
     return 0;
 }
