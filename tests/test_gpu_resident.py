@@ -85,3 +85,35 @@ def test_gradients(q, n, m, p, every, u16):
         # the two states carry a few rounding errors of 6e-8 per layer and qubit: below 6e-8 * 4 * 13 * 12 of the scale
         assert np.max(np.abs(dg - rg)) <= 1e-4 * scale + 1e-5
         assert np.max(np.abs(db - rb)) <= 1e-4 * scale + 1e-5
+
+
+# Row lengths around what one thread fetches of the next phase row (256 threads at n = 12, 512
+# at n = 13), the last that fits the LDS row and the first that does not; p rows
+# that do not all fit, so rows come one at a time. Every entry of a row is read.
+@pytest.mark.parametrize("n", [11, 12, 13])
+@pytest.mark.parametrize("rows", [256, 257, 512, 513, 1025, 2304, 2305, 2559, 2560, 2561])
+def test_gradients_with_long_phase_rows(q, n, rows):
+    import torch
+    m, p = rows - 1, 12
+    rng = np.random.default_rng(rows + n)
+    cost = rng.integers(0, rows, 1 << n)
+    cost[rng.permutation(1 << n)[:rows]] = np.arange(rows)[: 1 << n]
+    dev = torch.from_numpy(cost.astype(np.uint16)).cuda()
+    g, b = rng.uniform(-1, 1, p), rng.uniform(-0.7, 0.7, p)
+    b[p // 2] = 1.2
+    # (the weights keep E[C], about m / 2, and p_succ of one scale)
+    we = 1.0 / m
+    dg, db, r = q.qaoa_grad(dev, n, m, g, b, w_psucc=1.0, w_energy=we, checkpoint_every=3)
+    ref = oracle.qaoa(cost, n, g, b)
+    assert abs(r.p_success - ref[0]) <= 1e-5
+    assert abs(r.expected_cost - ref[1]) <= 1e-5 * ref[1]
+    assert abs(r.norm - 1.0) <= 1e-5
+    rg, rb, _ = oracle.qaoa_grad(cost, n, g, b, 1.0, we)
+    scale = max(np.max(np.abs(rg)), np.max(np.abs(rb)))
+    # as test_gradients: 6e-8 * 4 * 13 * 12 of the scale, with its room
+    assert np.max(np.abs(dg - rg)) <= 1e-4 * scale + 1e-5
+    assert np.max(np.abs(db - rb)) <= 1e-4 * scale + 1e-5
+    # side by side with others: the same, bit for bit
+    one = q.qaoa_grad_batched([dev] * 3, [n] * 3, [m] * 3, [g] * 3, [b] * 3, w_psucc=1.0, w_energy=we, checkpoint_every=3)
+    for x, y in zip(one[0], one[1]):
+        assert np.array_equal(x, dg) and np.array_equal(y, db)
