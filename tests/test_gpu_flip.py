@@ -69,3 +69,20 @@ def test_symmetric_and_nearly_symmetric(q, n, u16, tb):
             cost[at] = (cost[at] + 1) % (m + 1)
         check_run(q, cost, n, m, p, u16, ctx)
     ctx.close()
+
+
+# n = 22 and 23: the last size whose first sweep is launched ahead of the check's
+# answer, and the first that waits for it
+@pytest.mark.parametrize("n,u16,tb", [(22, False, 13), (23, False, 13), (23, True, 14), (23, False, 12)])
+def test_both_sides_of_the_wait(q, n, u16, tb):
+    m = 300 if u16 else 40
+    base = oracle.cost(inst.instance(n, 3, m, n + tb), n)
+    ctx = q.Context()
+    ctx.set_tune(n, {"tile_bits": tb, "low_run_bits": 4, "page_bit": 18, "split": 0}, "u16" if u16 else "u8")
+    for at in (None, (1 << (n - 1)) - 1):  # symmetric; the last pair in the middle differs
+        print(f"\n[flip] n={n} u16={u16} tb={tb} at={at}", flush=True)
+        cost = base.copy()
+        if at is not None:
+            cost[at] = (cost[at] + 1) % (m + 1)
+        check_run(q, cost, n, m, 2, u16, ctx)
+    ctx.close()
