@@ -214,3 +214,15 @@ def test_sample_targets_between_roundings_of_a_chunk_start(q):
     assert np.all(psi[x] != 0), "an outcome without an amplitude"
     assert np.all(np.diff(x) >= 0), "outcomes follow the uniforms"
     assert x[0] == x[1] == x[2] == x[3] == 5 and x[-1] == 68 * tile + 3
+
+
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 1000, 512 * 64 - 1, 512 * 64, 512 * 64 + 1, 100000])
+def test_sample_reads_every_uniform(q, count):
+    """Exact sums (|+> at n = 12): each draw is floor(u 2^12), however the uniforms
+    are dealt to the workgroups that fetch them."""
+    import torch
+    n = 12
+    st = torch.full((1 << n,), 2.0 ** (-n / 2), dtype=torch.complex64, device="cuda")
+    u = np.random.default_rng(count).random(count)
+    got, _ = q.sample(st, n, u)
+    assert np.array_equal(got, np.floor(u * 2 ** n).astype(np.uint64))
