@@ -179,7 +179,7 @@ int qnae_qaoa_run_noalloc(qnae_ctx *ctx, const void *cost_dev, int32_t cost_dtyp
  * applies the inverse layers to lam and psi together and restarts psi from
  * each checkpoint, so rounding in the uncomputed psi spans at most one segment.
  * Device memory: ceil(p / checkpoint_every) + 1 states of 2^n complex64 (n >
- * 13; half of each for a flip-symmetric diagonal with n > 24), held by the
+ * 13; half of each for a flip-symmetric diagonal with n > 22), held by the
  * context.
  *
  *   dgammas, dbetas  host, p doubles each (may be NULL when p = 0)

@@ -223,8 +223,9 @@ class Context:
                 for i in range(min(cnt.value, 16))}
 
     def autotune(self, n: int, cost_dtype: str = "u8", reps: int = 3, stream=None) -> dict:
-        """Time the sweep tile shapes at n (scratch memory, two-layer runs)
-        and keep the fastest for this context; returns it ({} for n <= 14)."""
+        """Time the sweep tile shapes at n (scratch memory; whole-state runs
+        and, from n = 20, half-state ones) and keep the fastest for this
+        context; returns it ({} for n <= 14)."""
         t = _CTune()
         _check(load_library().qnae_autotune(self.handle, int(n), _dtype_code(cost_dtype), int(reps), ctypes.byref(t),
                                             _stream(stream)))

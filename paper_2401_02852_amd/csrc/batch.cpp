@@ -3,9 +3,9 @@
 //
 // A batch is planned on the host: small instances (n <= 14) run whole in one
 // workgroup each; larger ones follow their own sweep plan, and step s of every
-// plan goes into the same launch, one launch per (sweep kind, cost type). All
-// tables and kernel arguments are packed into one pinned blob and uploaded
-// with a single copy before the launches.
+// plan goes into the same launch, one launch per SweepBucket (sweep kind, cost
+// type, mirrored tiles or not, layouts, tile bits). Two uploads precede the
+// launches: the tables, built while the flip check runs, and the kernel arguments.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -2,7 +2,8 @@
 // adjoint pass (include/qnae.h). See adjoint.hip for the formulas.
 //
 // n <= 13: one workgroup does the forward pass, the readout and the reverse
-// pass with both states in LDS. Larger n: the forward pass runs as one sweep
+// pass, with both states in registers from n = 10 on, in LDS below
+// (resident_grad.hip). Larger n: the forward pass runs as one sweep
 // plan that also stores the state after every `every` layers (checkpoints:
 // the ends of segments); then for each segment from the last, reverse sweeps
 // take lam (the first one forms lam = W psi_p) and that segment's checkpoint

@@ -141,8 +141,8 @@ struct qnae_ctx {
     int device = 0;
     qnae_host::Profiler prof;
     // single-instance path
-    qnae_host::DevBuf state, partials, luts, clauses, small;  // small: zeros counter + 3 result doubles
-    qnae_host::HostBuf h_luts, h_clauses, h_small;
+    qnae_host::DevBuf state, partials, luts, clauses, small;  // small: zeros counter, flip check's counter
+    qnae_host::HostBuf h_luts, h_clauses, h_small;  // h_small: a run's 3 sums (or a build's zeros), flip check's answer
     // batched path: uploaded tables and work lists, states, partial sums, results
     qnae_host::DevBuf b_blob, b_tabs, b_states, b_partials, b_results;
     // gradient: checkpoints + adjoint state, tables, partial sums
@@ -215,7 +215,10 @@ constexpr int kFlipMinN = 20;
 // check's answer is known: it covers the wait (about 10 us), and its lower
 // half is what a half-state run goes on from. Above, a whole first sweep
 // costs more than the wait (two layers, waiting and not, us: n = 20 53 and 50,
-// n = 21 54 and 52, n = 22 57 and 56, n = 23 98 and 100, n = 24 158 and 167).
+// n = 21 54 and 52, n = 22 57 and 56, n = 23 98 and 100, n = 24 158 and 167). Diagonals
+// without the symmetry pay for the wait, 6-9 us (one layer, 3-SAT, against no check
+// at all: n = 23 91 and 93, n = 24 145 and 148, n = 25 232 and 240); the first sweep ahead
+// there too would give them 87, 143 and 234, and the others 70, 107 and 170 for 66, 97 and 149.
 constexpr int kFlipEarlyMaxN = 22;
 // The launch ahead of a run: copies `bytes` (rounded up to 16; both buffers
 // hold that many) of pinned src to dst and, unless cost is null, checks the
@@ -273,7 +276,9 @@ hipError_t timed(qnae_ctx* ctx, int kind, double bytes, hipStream_t s, F&& fn) {
 
 // Clause records for the cost kernel (drops clauses that can never be
 // violated); returns the number written to `out` (room for m records), those
-// with a variable below 5 first (*num_low, when given, of them).
+// with a variable below 5 first (*num_low, when given, of them): the kernel takes
+// records in any order, but counts fastest when its two lists fill one after the other
+// (n = 29, m = 261: 405 us, 433 in input order).
 int make_clause_records(const int32_t* clauses, int32_t m, int32_t k, qnae::ClauseRec* out,
                         int predicate = QNAE_PRED_NAE, int* num_low = nullptr);
 // QNAE_EINVAL if some literal is 0 or outside +-[1, n].

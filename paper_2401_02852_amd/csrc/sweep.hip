@@ -9,12 +9,12 @@
 // exp(-i gamma C(x)), Section 3.2) and the selected qubit butterflies, and
 // writes it back.
 //
-// Each thread holds 16 amplitudes in 32 registers: about 50-64 registers in
-// all, so a CU holds 16 to 32 waves of two to four workgroups, which hide each
+// Each thread holds 16 amplitudes in 32 registers: 50 to 65 registers in all
+// (boundary kind 60 to 85), so a CU holds 16 to 32 waves of two to four workgroups, which hide each
 // other's loads, LDS transposes and barriers. (Tiles of 32 amplitudes a thread
 // at two waves per SIMD: n = 17, p = 8 with cost build 147 us, n = 22 full
 // state, p = 12, 269 us, n = 30 half state, p = 10, 32.9 ms; with 16 125 us, 240 us
-// and 31.9 ms; tiles of 2^14 amplitudes keep 32 a thread, see sweep14.hip.)
+// and 31.6 ms; tiles of 2^14 amplitudes keep 32 a thread, see sweep14.hip.)
 // Layouts and transposes: tile.h.
 //
 // The butterfly on a pair (a, b) is own' = own - i t partner (two FMAs per

@@ -2,8 +2,9 @@
 // FP64 and rounded to FP32, as the host's phase_row builds them by angle
 // addition (their entries differ by at most its 1e-13 before rounding). For
 // calls with many long rows: 800 rows of 2124 entries took the host's eight
-// threads and two 13.6 MB copies over PCIe about 0.7 ms, here 40-byte row
-// records travel instead. Bound by the FP64 sine and cosine.
+// threads and two 13.6 MB copies over PCIe about 0.7 ms, here 48-byte row
+// records travel instead. Bound by the FP64 sine and cosine. Rows come with |g| <= 3.2
+// (the host reduces larger ones), so that the rounding of g c stays below 3e-11.
 #include "internal.h"
 
 namespace qnae {

@@ -49,8 +49,8 @@ def check_run(q, cost_np, n, m, p, u16, ctx):
     assert abs(r.norm - 1.0) <= 1e-5
 
 
-# n = 20: the smallest checked size; 24 and 25: the first sweep is launched
-# ahead of the check's answer, or after it; tile sizes with two and three groups
+# n = 20: the smallest checked size; up to 22 the first sweep is launched ahead of
+# the check's answer, above after it; tile sizes with two and three groups
 @pytest.mark.parametrize("n,u16,tb", [(19, False, 13), (20, False, 12), (20, True, 13), (21, False, 14), (22, True, 12),
                                       (24, False, 14), (25, False, 13)])
 def test_symmetric_and_nearly_symmetric(q, n, u16, tb):
