@@ -231,7 +231,7 @@ typedef struct {
  * qnae_set_tune). Results equal qnae_qaoa_run on each instance alone up to
  * FP32 rounding order. A batch of the same shape as one of the last 8 (the
  * same sizes, cost types, tile shapes and buffers) reuses its plan and
- * replays its captured launch sequence: only the angles' tables are rebuilt. States the caller does not
+ * replays the graph of its launches: only the angles' tables are rebuilt. States the caller does not
  * provide live in context scratch (sum of 2^n * 8 bytes). Synchronous.
  * Errors: QNAE_EINVAL (names the offending instance), QNAE_ENOMEM,
  * QNAE_EHIP. */

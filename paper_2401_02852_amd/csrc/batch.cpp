@@ -138,7 +138,7 @@ namespace qnae_host {
 // Everything about a batch of solves that depends on its shape (instance
 // sizes, cost types, tile shapes and buffers) and not on its angles: the
 // sweep plans, the grouping of their steps into launches, the layout of the
-// uploaded blob with a host image of its angle-free part, and the captured
+// uploaded blob with a host image of its angle-free part, and the graph of the
 // launch sequence. A repeated shape reuses it, so a call rebuilds only the
 // phase tables and the angle fields of the kernel arguments.
 struct BatchPlan {
@@ -178,7 +178,7 @@ struct BatchPlan {
     size_t red_part_at = 0, red_blocks_at = 0, red_out_at = 0, size = 0;
     std::vector<unsigned char> fixed;  // host image of the blob (angle fields filled per call)
     hipGraphExec_t exec = nullptr;
-    uint64_t exec_reverse = 0;  // the final-state reversals the captured sequence holds
+    uint64_t exec_reverse = 0;  // the final-state reversals the graph holds
     ~BatchPlan() {
         if (exec) (void)hipGraphExecDestroy(exec);
     }
@@ -447,9 +447,9 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
         return inst[i].state_dev ? (float2*)inst[i].state_dev : (float2*)P->states + P->jobs[i].state_at;
     };
     // All launches of the batch; `prof` brackets each with timing events.
-    auto enqueue = [&](hipStream_t st, bool prof) -> int {
+    auto enqueue = [&](qnae::LaunchTo to, bool prof) -> int {
         auto run = [&](int kind, double bytes, auto&& fn) -> hipError_t {
-            return prof ? timed(ctx, kind, bytes, st, fn) : fn();
+            return prof ? timed(ctx, kind, bytes, to.stream, fn) : fn();
         };
         for (int g = 0; g < 2; ++g) {
             if (P->res_members[g].empty()) continue;
@@ -457,27 +457,27 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
             for (int i : P->res_members[g]) rbytes += std::ldexp((g ? 2.0 : 1.0) * P->jobs[i].T, inst[i].n);
             HIP_TRY(run(K_BATCH_RESIDENT, rbytes, [&] {
                 return qnae::launch_resident_batch(g ? QNAE_U16 : QNAE_U8, (const qnae::ResidentArgs*)(d + P->res_at[g]),
-                                                   (int)P->res_members[g].size(), st);
+                                                   (int)P->res_members[g].size(), to);
             }));
         }
         for (const BatchPlan::Launch& L : P->launches) {
             HIP_TRY(run(K_BATCH_SWEEP, L.bytes, [&] {
                 return qnae::launch_sweep_batch(L.as.tb, L.as.dtype, L.as.kind, (const SweepArgs*)(d + L.args_at),
-                                                (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, st,
+                                                (const uint32_t*)(d + L.first_at), (int)L.members.size(), L.blocks, to,
                                                 L.as.virt, L.as.l1);
             }));
         }
         for (int i : P->sweep_members) {
             const SweepPlan& S = P->jobs[i].plan;
             if (S.keep && !S.half && S.p > 0 && S.flips_before[S.p])
-                HIP_TRY(qnae::launch_reverse(psi_of(i), 1ull << inst[i].n, st));
+                HIP_TRY(qnae::launch_reverse(psi_of(i), 1ull << inst[i].n, to));
         }
         if (!P->sweep_members.empty()) {
             HIP_TRY(run(K_BATCH_REDUCE, 24.0 * P->part_elems / 3, [&] {
                 return qnae::launch_final_reduce_batch((const double* const*)(d + P->red_part_at),
                                                        (const uint32_t*)(d + P->red_blocks_at),
                                                        (double* const*)(d + P->red_out_at),
-                                                       (int)P->sweep_members.size(), st);
+                                                       (int)P->sweep_members.size(), to);
             }));
         }
         return QNAE_OK;
@@ -487,24 +487,19 @@ int qnae_qaoa_run_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     } else {
         // The launch sequence depends only on the plan (the arguments were just
         // uploaded to where it reads them) and on which final states are
-        // reversed, so its capture is replayed while those stay the same.
+        // reversed, so its graph is replayed while those stay the same.
         if (P->exec && P->exec_reverse != reverse) {
             (void)hipGraphExecDestroy(P->exec);
             P->exec = nullptr;
         }
         if (!P->exec) {
-            HIP_TRY(hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
-            const int rc = enqueue(ctx->capture_stream, false);
-            hipGraph_t graph = nullptr;
-            const hipError_t ec = hipStreamEndCapture(ctx->capture_stream, &graph);
-            if (rc) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return rc;
-            }
-            HIP_TRY(ec);
+            qnae::GraphChain chain;
+            HIP_TRY(hipGraphCreate(&chain.graph, 0));
+            const int rc = enqueue(&chain, false);
             hipGraphExec_t exec = nullptr;
-            const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
+            const hipError_t ei = rc ? hipSuccess : hipGraphInstantiate(&exec, chain.graph, nullptr, nullptr, 0);
+            (void)hipGraphDestroy(chain.graph);
+            if (rc) return rc;
             HIP_TRY(ei);
             P->exec = exec;
             P->exec_reverse = reverse;

@@ -149,9 +149,8 @@ struct qnae_ctx {
     qnae_host::DevBuf g_states, g_blob, g_partials, g_tables;
     qnae_host::HostBuf h_blob, h_btabs, h_results;
     hipEvent_t staging_done = nullptr;  // last async copy out of pinned staging
-    // plans of recent batch shapes, with their captured launch sequences (most recent last)
+    // plans of recent batch shapes, with the graphs of their launches (most recent last)
     bool use_graphs = true;
-    hipStream_t capture_stream = nullptr;
     std::vector<std::unique_ptr<qnae_host::BatchPlan, qnae_host::BatchPlanFree>> batch_plans;
     // batched cost builds: their own staging
     qnae_host::DevBuf c_blob;

@@ -7,6 +7,39 @@
 
 namespace qnae {
 
+// Where a batch's launches go: to a stream, or into a graph, one node behind the
+// other. (Graphs are built node by node: while a stream is being captured the runtime
+// refuses other threads' synchronisations and allocations, or they end the capture.)
+struct GraphChain {
+    hipGraph_t graph = nullptr;
+    hipGraphNode_t last = nullptr;
+};
+struct LaunchTo {
+    hipStream_t stream = nullptr;
+    GraphChain* chain = nullptr;
+    LaunchTo(hipStream_t s) : stream(s) {}
+    LaunchTo(GraphChain* c) : chain(c) {}
+};
+template <typename T>
+struct Exactly {
+    using type = T;
+};
+template <typename... P>
+hipError_t launch_to(LaunchTo to, dim3 grid, dim3 block, void (*kernel)(P...), typename Exactly<P>::type... args) {
+    void* params[] = {(void*)&args...};
+    if (!to.chain) return hipLaunchKernel((const void*)kernel, grid, block, params, 0, to.stream);
+    hipKernelNodeParams k{};
+    k.func = (void*)kernel;
+    k.gridDim = grid;
+    k.blockDim = block;
+    k.kernelParams = params;
+    GraphChain& c = *to.chain;
+    hipGraphNode_t node = nullptr;
+    if (hipError_t e = hipGraphAddKernelNode(&node, c.graph, c.last ? &c.last : nullptr, c.last ? 1 : 0, &k)) return e;
+    c.last = node;
+    return hipSuccess;
+}
+
 // ---------------------------------------------------------------------------
 // Cost diagonal (violated clause count per basis state)
 // ---------------------------------------------------------------------------
@@ -165,12 +198,12 @@ hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s);
 // (12, 13 or 14). virt: every instance's group holds the virtual bit
 // (args[i].vbit >= 0), or none does. l1: sweep_l1 of every instance.
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool virt, int l1);
+                              uint32_t blocks, LaunchTo to, bool virt, int l1);
 // Does a launch of this kind over a group with these mix masks pass its tiles
 // through register layouts 2 and 3? 1 yes, 2 no. (A launch that holds one that does
 // passes every tile through it.)
 int sweep_l1(int tb, int kind, uint32_t pre_mask, uint32_t post_mask);
-hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s);
+hipError_t launch_reverse(float2* psi, uint64_t N, LaunchTo to);
 
 // Do `rows` phase table rows of `len` entries fit `room` entries? (In 64 bits: a
 // call may have up to 100000 rows of 65536.)
@@ -264,13 +297,13 @@ struct ResidentGradArgs {
 };
 // One workgroup per entry of args (count entries, all of one cost type).
 hipError_t launch_resident_grad_batch(int dtype, const ResidentGradArgs* args, int count, hipStream_t s);
-hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, hipStream_t s);
+hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, LaunchTo to);
 
 // Sum of 3-double block partials into out[3], FP64.
 hipError_t launch_final_reduce(const double* partials, int64_t blocks, double* out, hipStream_t s);
 // Instance i: sum of blocks[i] triples at partials[i] -> outs[i][0..2].
 hipError_t launch_final_reduce_batch(const double* const* partials, const uint32_t* blocks, double* const* outs,
-                                     int count, hipStream_t s);
+                                     int count, LaunchTo to);
 
 // Sum i of `count`: `blocks` triples at partials + 3 blocks i -> out[3 i ..].
 hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, double* out, int count, hipStream_t s);

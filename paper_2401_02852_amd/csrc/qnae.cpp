@@ -26,7 +26,6 @@ int qnae_create(qnae_ctx** out, int device) try {
     ctx->device = device;
     hipError_t e = hipEventCreateWithFlags(&ctx->staging_done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->cost_staging_done, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = ctx->small.reserve(kSmallBytes);
     if (e == hipSuccess) e = hipMemset(ctx->small.ptr, 0, kSmallBytes);
     if (e == hipSuccess) e = ctx->h_small.reserve(kSmallBytes);
@@ -67,9 +66,8 @@ int qnae_destroy(qnae_ctx* ctx) try {
                        &ctx->h_sample, &ctx->na_host, &ctx->h_cblob, &ctx->h_flip, &ctx->h_btabs})
         b->release();
     if (ctx->staging_done) (void)hipEventDestroy(ctx->staging_done);
-    ctx->batch_plans.clear();  // destroys their captured launch sequences
+    ctx->batch_plans.clear();  // destroys their graphs
     if (ctx->cost_staging_done) (void)hipEventDestroy(ctx->cost_staging_done);
-    if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     for (auto& r : ctx->prof.pending) {
         (void)hipEventDestroy(r.start);
         (void)hipEventDestroy(r.stop);

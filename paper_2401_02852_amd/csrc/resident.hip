@@ -309,12 +309,9 @@ hipError_t launch_resident_inline(int dtype, const ResidentInlineArgs& a, hipStr
     });
 }
 
-hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, hipStream_t s) {
-    if (dtype == 1)
-        hipLaunchKernelGGL((resident_batch_kernel<uint8_t>), dim3(count), dim3(kResidentThreads), 0, s, args);
-    else
-        hipLaunchKernelGGL((resident_batch_kernel<uint16_t>), dim3(count), dim3(kResidentThreads), 0, s, args);
-    return hipGetLastError();
+hipError_t launch_resident_batch(int dtype, const ResidentArgs* args, int count, LaunchTo to) {
+    return launch_to(to, dim3(count), dim3(kResidentThreads),
+                     dtype == 1 ? resident_batch_kernel<uint8_t> : resident_batch_kernel<uint16_t>, args);
 }
 
 }  // namespace qnae

@@ -404,11 +404,10 @@ hipError_t launch_tb(int kind, const SweepArgs& a, bool ckpt, hipStream_t s) {
 
 template <int TB, typename CT>
 hipError_t launch_batch_tb(int kind, const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool virt,
-                          int l1, hipStream_t s) {
+                          int l1, LaunchTo to) {
     return by_kind(kind, virt, l1 != 2, [&](auto k, auto vi, auto u) {
-        hipLaunchKernelGGL((sweep_batch_kernel<TB, CT, k.value, vi.value, u.value>), dim3(blocks),
-                           dim3(kSweepThreads<TB>), 0, s, args, first, count);
-        return hipGetLastError();
+        return launch_to(to, dim3(blocks), dim3(kSweepThreads<TB>),
+                         sweep_batch_kernel<TB, CT, k.value, vi.value, u.value>, args, first, count);
     });
 }
 
@@ -436,23 +435,22 @@ hipError_t launch_sweep_ckpt(int dtype, const SweepArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_sweep_batch(int tb, int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                              uint32_t blocks, hipStream_t s, bool virt, int l1) {
+                              uint32_t blocks, LaunchTo to, bool virt, int l1) {
     auto run = [&](auto tbits) {
-        return dtype == 1 ? launch_batch_tb<tbits.value, uint8_t>(kind, args, first, count, blocks, virt, l1, s)
-                          : launch_batch_tb<tbits.value, uint16_t>(kind, args, first, count, blocks, virt, l1, s);
+        return dtype == 1 ? launch_batch_tb<tbits.value, uint8_t>(kind, args, first, count, blocks, virt, l1, to)
+                          : launch_batch_tb<tbits.value, uint16_t>(kind, args, first, count, blocks, virt, l1, to);
     };
     switch (tb) {
         case 12: return run(std::integral_constant<int, 12>{});
         case 13: return run(std::integral_constant<int, 13>{});
-        case 14: return launch_sweep14_batch(dtype, kind, args, first, count, blocks, s, virt, l1);
+        case 14: return launch_sweep14_batch(dtype, kind, args, first, count, blocks, to, virt, l1);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_reverse(float2* psi, uint64_t N, hipStream_t s) {
+hipError_t launch_reverse(float2* psi, uint64_t N, LaunchTo to) {
     const uint64_t threads = N / 4;
-    hipLaunchKernelGGL(reverse_kernel, dim3((uint32_t)((threads + 255) / 256)), dim3(256), 0, s, psi, N);
-    return hipGetLastError();
+    return launch_to(to, dim3((uint32_t)((threads + 255) / 256)), dim3(256), reverse_kernel, psi, N);
 }
 
 hipError_t launch_final_reduce(const double* partials, int64_t blocks, double* out, hipStream_t s) {
@@ -466,9 +464,8 @@ hipError_t launch_final_reduce_rows(const double* partials, int64_t blocks, doub
 }
 
 hipError_t launch_final_reduce_batch(const double* const* partials, const uint32_t* blocks, double* const* outs,
-                                     int count, hipStream_t s) {
-    hipLaunchKernelGGL(final_reduce_batch_kernel, dim3(count), dim3(1024), 0, s, partials, blocks, outs);
-    return hipGetLastError();
+                                     int count, LaunchTo to) {
+    return launch_to(to, dim3(count), dim3(1024), final_reduce_batch_kernel, partials, blocks, outs);
 }
 
 }  // namespace qnae

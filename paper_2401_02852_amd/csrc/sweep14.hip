@@ -351,11 +351,10 @@ hipError_t launch_ct(int kind, const SweepArgs& a, hipStream_t s) {
 
 template <typename CT>
 hipError_t launch_batch_ct(int kind, const SweepArgs* args, const uint32_t* first, int count, uint32_t blocks, bool virt,
-                           int l1, hipStream_t s) {
+                           int l1, LaunchTo to) {
     return by_kind(kind, virt, l1 != 2, [&](auto k, auto vi, auto u) {
-        hipLaunchKernelGGL((sweep14_batch_kernel<CT, k.value, vi.value, u.value>), dim3(blocks), dim3(NT), 0, s, args,
-                           first, count);
-        return hipGetLastError();
+        return launch_to(to, dim3(blocks), dim3(NT), sweep14_batch_kernel<CT, k.value, vi.value, u.value>, args, first,
+                         count);
     });
 }
 
@@ -366,9 +365,9 @@ hipError_t launch_sweep14(int dtype, int kind, const SweepArgs& a, hipStream_t s
 }
 
 hipError_t launch_sweep14_batch(int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                                uint32_t blocks, hipStream_t s, bool virt, int l1) {
-    return dtype == 1 ? launch_batch_ct<uint8_t>(kind, args, first, count, blocks, virt, l1, s)
-                      : launch_batch_ct<uint16_t>(kind, args, first, count, blocks, virt, l1, s);
+                                uint32_t blocks, LaunchTo to, bool virt, int l1) {
+    return dtype == 1 ? launch_batch_ct<uint8_t>(kind, args, first, count, blocks, virt, l1, to)
+                      : launch_batch_ct<uint16_t>(kind, args, first, count, blocks, virt, l1, to);
 }
 
 }  // namespace qnae

@@ -11,7 +11,7 @@ namespace qnae {
 // 14-bit tiles (sweep14.hip); see launch_sweep and launch_sweep_batch.
 hipError_t launch_sweep14(int dtype, int kind, const SweepArgs& a, hipStream_t s);
 hipError_t launch_sweep14_batch(int dtype, int kind, const SweepArgs* args, const uint32_t* first, int count,
-                                uint32_t blocks, hipStream_t s, bool virt, int l1);
+                                uint32_t blocks, LaunchTo to, bool virt, int l1);
 
 namespace {
 

@@ -233,7 +233,7 @@ int qnae_autotune_batched(qnae_ctx* ctx, const qnae_instance* inst, int32_t coun
     qnae_tune best_of[3] = {best, best, best};  // fastest split-0 shape per tile size
     auto time_shape = [&](const qnae_tune& shape) -> int {
         for (const auto& c : classes) ctx->tunes[c] = shape;
-        // one warm-up run plans the shape and captures its launches
+        // one warm-up run plans the shape and builds its graph
         int rc = qnae_qaoa_run_batched(ctx, inst, count, res.data(), stream);
         const auto t0 = std::chrono::steady_clock::now();
         for (int r = 0; r < reps && !rc; ++r) rc = qnae_qaoa_run_batched(ctx, inst, count, res.data(), stream);

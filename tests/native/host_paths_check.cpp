@@ -67,8 +67,10 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)std::malloc(1), hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { return std::free((void*)s), hipSuccess; }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return step(hipErrorUnknown); }
-hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { return *g = (hipGraph_t)std::malloc(1), hipSuccess; }
+hipError_t hipGraphCreate(hipGraph_t* g, unsigned) {
+    if (hipError_t e = step(hipErrorOutOfMemory)) return e;
+    return *g = (hipGraph_t)std::malloc(1), hipSuccess;
+}
 hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t, hipGraphNode_t*, char*, size_t) {
     if (hipError_t e = step(hipErrorOutOfMemory)) return e;
     return *x = (hipGraphExec_t)std::malloc(1), hipSuccess;
@@ -105,18 +107,18 @@ hipError_t launch_sweep(int tb, int, int, const SweepArgs& a, hipStream_t) {
     return launched();
 }
 hipError_t launch_sweep_ckpt(int, const SweepArgs&, hipStream_t) { return launched(); }
-hipError_t launch_sweep_batch(int, int, int, const SweepArgs*, const uint32_t*, int, uint32_t, hipStream_t, bool, int) {
+hipError_t launch_sweep_batch(int, int, int, const SweepArgs*, const uint32_t*, int, uint32_t, LaunchTo, bool, int) {
     return launched();
 }
 int sweep_l1(int, int, uint32_t, uint32_t) { return 1; }
-hipError_t launch_reverse(float2*, uint64_t, hipStream_t) { return launched(); }
+hipError_t launch_reverse(float2*, uint64_t, LaunchTo) { return launched(); }
 hipError_t launch_resident(int, const ResidentArgs&, hipStream_t) { return launched(); }
 hipError_t launch_resident_inline(int, const ResidentInlineArgs&, hipStream_t) { return launched(); }
-hipError_t launch_resident_batch(int, const ResidentArgs*, int, hipStream_t) { return launched(); }
+hipError_t launch_resident_batch(int, const ResidentArgs*, int, LaunchTo) { return launched(); }
 hipError_t launch_resident_grad_batch(int, const ResidentGradArgs*, int, hipStream_t) { return launched(); }
 hipError_t launch_adjoint(int, int, const AdjointArgs&, hipStream_t, bool) { return launched(); }
 hipError_t launch_final_reduce(const double*, int64_t, double*, hipStream_t) { return launched(); }
-hipError_t launch_final_reduce_batch(const double* const*, const uint32_t*, double* const*, int, hipStream_t) {
+hipError_t launch_final_reduce_batch(const double* const*, const uint32_t*, double* const*, int, LaunchTo) {
     return launched();
 }
 hipError_t launch_final_reduce_rows(const double*, int64_t, double*, int, hipStream_t) { return launched(); }

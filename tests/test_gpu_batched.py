@@ -322,3 +322,52 @@ def test_prepared_batch_and_cost_build_match(q):
         ref = np.array(q.qaoa_run_batched(costs, ns, ms, list(g), list(b)))
         assert np.array_equal(pb.run(g, b), ref), rep
         assert np.array_equal(pb.run(list(g), list(b)), ref), rep
+
+
+def test_new_batch_shapes_beside_allocating_threads(q):
+    """A batch of a new shape captures its launches while other threads' contexts
+    allocate their buffers and torch allocates tensors: neither gets in the other's
+    way, and every result is that of the same call alone."""
+    import threading
+    import torch
+    n, m = 15, 31
+    cost = q.build_cost_diagonal(inst.instance(n, 3, m, 3), n)
+    torch.cuda.synchronize()
+    shapes = [(c, p) for c in (1, 2, 3, 4) for p in (1, 2, 3)]
+    angles = {p: np.linspace(0.2, 0.6, p) for p in (1, 2, 3)}
+
+    def solve(ctx, c, p):
+        return q.qaoa_run_batched([cost] * c, [n] * c, [m] * c, [angles[p]] * c, [angles[p]] * c, ctx=ctx)
+
+    want = {s: solve(q.default_context(), *s) for s in shapes}
+    errors, rounds, stop = [], [0], threading.Event()
+
+    def allocate():
+        try:
+            while not stop.is_set():
+                ctx = q.Context()
+                q.qaoa_run(cost, n, m, angles[3], angles[3], ctx=ctx)
+                q.qaoa_grad(cost, n, m, angles[2], angles[2], ctx=ctx)
+                x = torch.empty(3 << 20, dtype=torch.uint8, device="cuda")
+                del x
+                torch.cuda.empty_cache()
+                ctx.close()
+                rounds[0] += 1
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=allocate) for _ in range(2)]
+    for t in threads:
+        t.start()
+    try:
+        for _ in range(25):
+            ctx = q.Context()  # no plans yet: every shape is captured
+            for s in shapes:
+                assert solve(ctx, *s) == want[s]
+            ctx.close()
+    finally:
+        stop.set()
+        for t in threads:
+            t.join()
+    assert not errors, errors
+    assert rounds[0] > 0
